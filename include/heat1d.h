@@ -22,7 +22,9 @@
  *    The scalar arguments r, c1, cN are passed as double and rounded to the
  *    array precision once.  Every kernel evaluates one step as
  *    c + r*((a + b) - 2c) with fused multiply-adds (algebraically Eq.3), so all
- *    kernels of one precision produce bitwise-identical results.
+ *    kernels of one precision that take single steps produce bitwise-identical
+ *    results; fused sweeps (opts.fuse_steps) and band passes (HEAT1D_SYNC_AUTO)
+ *    apply several steps at once and agree with them to rounding.
  *  - Memory: every array argument is a DEVICE pointer owned by the caller,
  *    except where a parameter name ends in _host.  Arrays are dense and
  *    contiguous.  The library never allocates device memory; scratch space is
@@ -68,7 +70,20 @@ enum heat1d_dtype { HEAT1D_F32 = 0, HEAT1D_F64 = 1 };
 
 /* Synchronous kernel choice (heat1d_opts.sync_kernel). */
 enum heat1d_sync_kernel {
-    HEAT1D_SYNC_AUTO = 0,     /* plan's default, or the autotuner's choice        */
+    HEAT1D_SYNC_AUTO = 0,     /* plan's default, or the autotuner's choice.  A plan that
+                                 also leaves depth_t, pts_per_lane, waves and
+                                 fuse_steps open (waves and pts_per_lane may shape
+                                 an asynchronous kernel, nsub > 0) takes band passes
+                                 for runs of 64 steps or more: many steps at once as
+                                 one banded matrix, the power of Eq.3's stencil
+                                 (weights beyond a reach where all of them together
+                                 are below a sixteenth of a rounding are dropped).
+                                 The same iteration with far fewer roundings: results
+                                 agree with the stepping kernels within the stated
+                                 tolerances, not bit for bit; a point that is not
+                                 finite spreads as steps spread it.  A run without a
+                                 workspace (allowed where the default is RESIDENT)
+                                 steps */
     HEAT1D_SYNC_STEP = 1,     /* one launch per step, two global buffers          */
     HEAT1D_SYNC_TILED = 2,    /* depth-T temporal blocking, T steps per launch    */
     HEAT1D_SYNC_RESIDENT = 3, /* whole rod in one workgroup's registers, K steps  */
@@ -176,7 +191,8 @@ int heat1d_plan_batched(heat1d_plan_t *out, int32_t nrods, const int64_t *N_host
 void heat1d_plan_destroy(heat1d_plan_t plan);
 
 /* Bytes of workspace each call needs.  For the sync path this is one state
- * (N*B elements); the async path adds its halo ring and flags; the adjoint adds
+ * (N*B elements), and for a plan that may take band passes their weights and
+ * tile records (33 KB, and 8 bytes per 256 points); the async path adds its halo ring and flags; the adjoint adds
  * its checkpoints for K steps; the batched path holds its work queues. */
 size_t heat1d_sync_workspace_bytes(heat1d_plan_t plan);  /* any sync kernel */
 size_t heat1d_async_workspace_bytes(heat1d_plan_t plan);

@@ -15,6 +15,7 @@
 #include <string>
 #include <vector>
 
+#include "heat1d_band.h"
 #include "heat1d_ensemble.h"
 #include "heat1d_launch.h"
 #include "heat1d_observe.h"
@@ -23,6 +24,13 @@
 using namespace heat1d;
 
 namespace {
+
+// Synchronous runs of at least this many steps take band passes.  A run of K
+// steps is three short launches there, 13 us up to 2^16 points; stepping (AUTO's
+// default kernel) against that, at K = 32 / 64 / 128: 4096 points 11 / 19 / 37
+// us against 11 / 13 / 13; 2^23 points 28 / 54 / 105 us against 36 / 43 / 46;
+// 2^26 points 158 / 330 / 657 us against 200 / 242 / 271 (all FP32).
+constexpr int32_t kBandFrom = 64;
 
 constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -47,6 +55,9 @@ struct heat1d_plan_s {
   int fuse = 1;  // steps per register sweep on tiles without a rod end
   int tile_waves = 1;  // tiled kernel: wavefronts per tile (1, or 4 / 8 for wide tiles)
   int waves = 16;
+  // runs of at least this many steps take band passes (0: none); only plans
+  // that leave the synchronous kernel open
+  int32_t band_from = 0;
   // asynchronous
   int32_t max_delay = 16;
   int64_t watchdog = int64_t(1) << 22;
@@ -136,6 +147,7 @@ void describe(heat1d_plan_t p) {
                   p->sync_kernel == HEAT1D_SYNC_TILED ? p->tile_waves : 1);
   }
   p->desc = buf;
+  if (p->band_from > 0) p->desc += " band_from=" + std::to_string(p->band_from);
 }
 
 // Default synchronous choice before any tuning.
@@ -305,6 +317,54 @@ size_t sync_state_bytes(heat1d_plan_t p) {
   return align_up((size_t)p->N * p->nrods * esize(p->dtype));
 }
 
+// K steps of nrods rods as band passes (heat1d_band.h): K is cut into equal
+// passes that alternate between out and ping (which a single pass does not
+// touch); the last one leaves u(K) in out, and D A^(K-1) u0 in z when z is
+// given.  dot: the partial sums of the input with dot_with.  scratch:
+// band_scratch_bytes.
+int run_band(heat1d_plan_t p, int64_t nrods, const void* in, void* out, double r, double c1,
+             double cN, int64_t K, void* ping, void* scratch, void* z, const void* dot_with,
+             double* dot, hipStream_t s) {
+  BandPass b;
+  b.dtype = p->dtype;
+  b.r = p->dtype == HEAT1D_F32 ? (double)(float)r : r;
+  const BandRun run = band_run(p->dtype, b.r, K);
+  b.N = p->N;
+  b.nrods = nrods;
+  b.c1 = c1;
+  b.cN = cN;
+  b.ring = p->opts.boundary == HEAT1D_BC_PERIODIC;
+  b.scratch = scratch;
+  for (int64_t i = 0; i < run.passes; ++i) {
+    const bool last = i + 1 == run.passes;
+    const int64_t T = last ? K - i * run.T : run.T;
+    b.in = i == 0 ? in : b.out;
+    b.out = (run.passes - 1 - i) % 2 == 0 ? out : ping;
+    b.z = last ? z : nullptr;
+    b.dot = i == 0 ? dot : nullptr;
+    b.dot_with = dot_with;
+    hipError_t e = hipSuccess;
+    if (i == 0 || T != b.T || b.z != nullptr) {
+      b.T = T;
+      b.slot = 0;  // the weights' launch clears both flags
+      e = launch_band_weights(b, s);
+    } else {
+      b.slot = 1 - b.slot;
+    }
+    if (e != hipSuccess) return hip_status(e);
+    EventPair* ev = timing_begin(p, s);
+    e = launch_band_pass(b, s);
+    timing_end(ev, s);
+    if (e == hipSuccess) e = launch_band_cones(b, s);
+    if (e != hipSuccess) return hip_status(e);
+  }
+  return HEAT1D_OK;
+}
+
+bool takes_band(heat1d_plan_t p, int64_t K, const void* ws) {
+  return p->band_from > 0 && K >= p->band_from && ws != nullptr;
+}
+
 int run_sync_impl(heat1d_plan_t p, const void* u0, void* uK, double r, double c1, double cN,
                   int64_t K, void* ws, hipStream_t s, int kernel, int T, int M, int waves,
                   int fuse) {
@@ -384,6 +444,17 @@ int run_sync_impl(heat1d_plan_t p, const void* u0, void* uK, double r, double c1
     if (err != hipSuccess) return hip_status(err);
   }
   return HEAT1D_OK;
+}
+
+// run_sync_impl with the plan's kernel, or band passes where the plan leaves the
+// choice open and the run is long enough.  ws: heat1d_sync_workspace_bytes.
+int run_sync_plan(heat1d_plan_t p, const void* u0, void* uK, double r, double c1, double cN,
+                  int64_t K, void* ws, hipStream_t s) {
+  if (takes_band(p, K, ws))
+    return run_band(p, p->nrods, u0, uK, r, c1, cN, K, ws, (char*)ws + sync_state_bytes(p),
+                    nullptr, nullptr, nullptr, s);
+  return run_sync_impl(p, u0, uK, r, c1, cN, K, ws, s, p->sync_kernel, p->T, p->M,
+                       p->sync_kernel == HEAT1D_SYNC_TILED ? p->tile_waves : p->waves, p->fuse);
 }
 
 // Split the rods of a batched plan into the three queues, each longest N*K
@@ -526,6 +597,11 @@ int heat1d_plan_create(heat1d_plan_t* out, int64_t N, int32_t dtype, const heat1
       return HEAT1D_EUNSUPPORTED;
     }
   }
+  // A plan that names no synchronous kernel, tile or sweep leaves the choice to
+  // the run's length.
+  if (o.sync_kernel == HEAT1D_SYNC_AUTO && o.depth_t == 0 && o.pts_per_lane == 0 &&
+      o.waves == 0 && o.fuse_steps == 0 && band_applies(dtype, N, p->nrods))
+    p->band_from = kBandFrom;
   describe(p);
   *out = p;
   return HEAT1D_OK;
@@ -582,7 +658,7 @@ const char* heat1d_plan_describe(heat1d_plan_t plan) {
 
 size_t heat1d_sync_workspace_bytes(heat1d_plan_t p) {
   if (!p || p->batched) return 0;
-  return sync_state_bytes(p);
+  return sync_state_bytes(p) + (p->band_from > 0 ? band_scratch_bytes(p->N, p->nrods) : 0);
 }
 
 size_t heat1d_async_workspace_bytes(heat1d_plan_t p) {
@@ -639,15 +715,14 @@ int heat1d_run_sync(heat1d_plan_t p, const void* u0, void* uK, double r, double 
   if (!std::isfinite(c1) || !std::isfinite(cN)) return HEAT1D_EINVAL;
   const size_t bytes = (size_t)p->N * p->nrods * esize(p->dtype);
   if (overlaps(u0, uK, bytes)) return HEAT1D_EINVAL;
-  const bool needs_ws = K > 1 && p->sync_kernel != HEAT1D_SYNC_RESIDENT;
+  // the resident kernel needs no workspace, and is what runs when there is none
   const size_t wsb = heat1d_sync_workspace_bytes(p);
-  if (needs_ws && (!workspace || overlaps(workspace, wsb, u0, bytes) ||
-                   overlaps(workspace, wsb, uK, bytes)))
-    return HEAT1D_EINVAL;
+  const bool ws_ok = workspace && !overlaps(workspace, wsb, u0, bytes) &&
+                     !overlaps(workspace, wsb, uK, bytes);
+  if (K > 1 && p->sync_kernel != HEAT1D_SYNC_RESIDENT && !ws_ok) return HEAT1D_EINVAL;
   if (K > INT32_MAX) return HEAT1D_EUNSUPPORTED;
-  return run_sync_impl(p, u0, uK, r, c1, cN, K, workspace, (hipStream_t)stream, p->sync_kernel,
-                       p->T, p->M,
-                       p->sync_kernel == HEAT1D_SYNC_TILED ? p->tile_waves : p->waves, p->fuse);
+  return run_sync_plan(p, u0, uK, r, c1, cN, K, ws_ok ? workspace : nullptr,
+                       (hipStream_t)stream);
 }
 
 size_t heat1d_observed_workspace_bytes(heat1d_plan_t p) {
@@ -692,8 +767,7 @@ int heat1d_run_sync_observed(heat1d_plan_t p, const void* u0, void* uK, double r
     // the buffers alternate so that the last chunk lands in uK
     void* out = ((nchunks - j) % 2 == 0) ? uK : (void*)extra;
     const int64_t steps = j <= full ? every : rem;
-    const int st = run_sync_impl(p, in, out, r, c1, cN, steps, ws, s, p->sync_kernel, p->T, p->M,
-                                 waves, p->fuse);
+    const int st = run_sync_plan(p, in, out, r, c1, cN, steps, ws, s);
     if (st != HEAT1D_OK) return st;
     if (j <= full) {
       e = launch_state_norms(p->dtype, out, N, B, c1, cN, partials, norms + j, nobs, s, !ring);
@@ -774,6 +848,23 @@ int heat1d_autotune_sync(heat1d_plan_t p, const void* u0, void* uK, double r, in
     if (ms < best) {
       best = ms;
       win = c;
+    }
+  }
+  // band passes against the best of them, where the plan may take them
+  if (status == HEAT1D_OK && p->band_from > 0 && K_probe >= p->band_from) {
+    char* scr = (char*)workspace + sync_state_bytes(p);
+    float ms = 0.f;
+    for (int rep = 0; rep < 2 && status == HEAT1D_OK; ++rep) {
+      hipEventRecord(a, s);
+      status = run_band(p, p->nrods, u0, uK, r, 0.0, 0.0, K_probe, workspace, scr, nullptr,
+                        nullptr, nullptr, s);
+      hipEventRecord(b, s);
+      if (status == HEAT1D_OK && hipEventSynchronize(b) != hipSuccess) status = HEAT1D_EHIP;
+      if (status == HEAT1D_OK) hipEventElapsedTime(&ms, a, b);
+    }
+    if (status == HEAT1D_OK) {
+      if (ms < best) best = ms;
+      else p->band_from = 0;
     }
   }
   hipEventDestroy(a);

@@ -1,0 +1,66 @@
+// heat1d_band.h -- T steps of Eq.3 applied at once, as a banded matrix on the
+// matrix cores (host-side declarations; the kernels are in kernels_band.hip).
+//
+// T steps of Eq.3 (Section 2) are one linear map: away from the ends every
+// point becomes sum_d w_d u_{i+d}, w the coefficients of the T-th power of the
+// three-point stencil (r, 1-2r, r).  Those coefficients are the distribution
+// of a sum of T independent moves of -1, 0, +1, so they fall off like a
+// Gaussian of variance 2 r T: beyond a reach of about 6.3 (FP32) or 9 (FP64)
+// standard deviations all of them together are below a sixteenth of a
+// rounding of the state.  One pass therefore costs 2 reach + 1 multiply-adds
+// per point whatever T is, where stepping costs three instructions per step.
+// The Dirichlet ends are exact under the odd extension of the rod about its
+// ends (u(-i) = 2 c1 - u(i)), which every step preserves.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+#include <stdint.h>
+
+namespace heat1d {
+
+// The largest reach of one pass: the tile with its halos and the weights stay
+// within the LDS of a workgroup.  Longer runs take several equal passes.
+constexpr int kBandMaxReach = 2048;
+
+// Points beyond which the weights of T steps are dropped (at most T): the
+// dropped weights sum to at most 2^-28 (FP32) / 2^-57 (FP64).
+int band_reach(int dtype, double r, int64_t T);
+
+// How a run of K steps is cut into passes of at most T steps each.
+struct BandRun {
+  int64_t passes = 0;
+  int64_t T = 0;  // steps of every pass but the last, which takes the rest
+};
+BandRun band_run(int dtype, double r, int64_t K);
+
+// Bytes of scratch (256-byte aligned) of the passes over nrods rods of N points:
+// two sets of weights, the flags and a record per tile.
+size_t band_scratch_bytes(int64_t N, int64_t nrods);
+
+// One pass of T steps of nrods rods of N points, in -> out.
+struct BandPass {
+  int dtype = 0;
+  const void* in = nullptr;
+  void* out = nullptr;
+  int64_t N = 0, nrods = 1;
+  int64_t T = 0;
+  double r = 0, c1 = 0, cN = 0;
+  int ring = 0;
+  void* scratch = nullptr;
+  int slot = 0;        // passes of one run alternate 0, 1 (whose flag is in use)
+  // z, when not NULL, receives D A^(T-1) applied to the state (D the second
+  // difference): K z is du(K)/dr, see heat1d_backward_checkpointed
+  void* z = nullptr;
+  // dot, when not NULL: partial sums of in . dot_with over each tile's inner
+  // points, one double per tile (band_tiles per rod)
+  const void* dot_with = nullptr;
+  double* dot = nullptr;
+};
+bool band_applies(int dtype, int64_t N, int64_t nrods);
+int64_t band_tiles(int dtype, int64_t N, int64_t nrods);  // tiles per rod
+hipError_t launch_band_weights(const BandPass& p, hipStream_t s);
+hipError_t launch_band_pass(const BandPass& p, hipStream_t s);
+hipError_t launch_band_cones(const BandPass& p, hipStream_t s);
+
+}  // namespace heat1d

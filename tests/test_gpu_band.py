@@ -1,0 +1,115 @@
+"""GPU parity of the band passes (many steps of Eq.3 applied at once on the
+matrix cores) against the FP64 oracle: sizes around the tiles and the reach,
+rods shorter than the reach (several images of the ends), rings shorter than
+it, stacked rods whose starts are not 16-byte aligned, several passes; and
+the cones of points that are not finite against one launch per step."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from paper_1510_08982_amd import abi
+from paper_1510_08982_amd.heat import SyncPlan
+from _helpers import normwise, tol_for, torch_dtype, np_dtype, print_case
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+RING = abi.HEAT1D_BC_PERIODIC
+
+
+def dev(x, dt):
+    return torch.from_numpy(np.ascontiguousarray(x, dtype=np_dtype(dt))).to(DEV)
+
+
+def reference(u0, r, c1, cN, K, ring):
+    if not ring:
+        return oracle.sync(u0, r, c1, cN, K)
+    return oracle.async_ensemble(u0, r, 0.0, 0.0, K, 1, 0, [1], every=K, periodic=True)[0][0]
+
+
+CASES = [  # (N, nrods, K, r)
+    (3, 1, 64, 0.5), (4, 3, 1000, 0.05), (100, 2, 1000, 0.5), (100, 1, 65, 0.37),
+    (255, 1, 300, 0.25), (256, 1, 301, 0.5), (257, 3, 64, 0.45), (1000, 1, 30000, 0.5),
+    (2047, 1, 512, 0.3), (2049, 2, 513, 0.3), (4096, 1, 20000, 0.4), (5003, 3, 777, 0.499),
+    (5001, 600, 100, 0.5),           # 2048 outputs a block, odd rod starts
+    (8192 * 3 + 5, 200, 64, 0.41),   # the largest blocks
+    (100, 1, 400000, 0.5),           # several passes, every image of the ends
+    (20000, 1, 90000, 0.5),          # several passes (FP64), reach near its limit (FP32)
+]
+
+
+@pytest.mark.parametrize("ring", [False, True])
+@pytest.mark.parametrize("dt", ["f32", "f64"])
+@pytest.mark.parametrize("N,B,K,r", CASES)
+def test_band_passes_match_oracle(N, B, K, r, dt, ring):
+    f = np_dtype(dt)
+    rng = np.random.default_rng(N + K)
+    u0 = workloads.as_dtype(rng.uniform(-1, 1, (B, N)), f)
+    r, c1, cN = (workloads.as_dtype(x, f) for x in (r, 0.75, -0.5))
+    plan = SyncPlan(N, torch_dtype(dt), nrods=B, boundary=RING if ring else 0)
+    print_case(test="band", dt=dt, N=N, B=B, K=K, r=r, ring=ring, plan=plan.describe())
+    assert "band_from=" in plan.describe()
+    got = plan.run(dev(u0.reshape(-1), dt), r, c1, cN, K).cpu().numpy().reshape(B, N)
+    for b in sorted({0, B // 2, B - 1}):
+        ref = reference(u0[b], r, c1, cN, K, ring)
+        err = normwise(got[b], ref)
+        print(f"  rod {b}: normwise error {err:.3e}")
+        assert err <= tol_for(dt)
+        if not ring:
+            assert got[b][0] == f(c1) and got[b][-1] == f(cN)
+
+
+@pytest.mark.parametrize("ring", [False, True])
+@pytest.mark.parametrize("dt", ["f32", "f64"])
+@pytest.mark.parametrize("N,B,K,bad", [
+    (5000, 1, 100, {2500: np.nan}), (5000, 1, 100, {50: np.inf, 3000: -np.inf}),
+    (700, 3, 64, {1: np.inf, 600: np.nan, 699: np.nan}),   # an end's own value does not count
+    (3000, 2, 128, {1000: np.inf, 1256: -np.inf, 2000: np.inf}),  # cones that just meet
+    (300, 1, 200, {10: np.nan}), (40, 1, 64, {20: np.inf}), (9000, 1, 64, {8900: -np.inf}),
+])
+def test_points_that_are_not_finite_spread_as_steps_spread_them(N, B, K, bad, dt, ring):
+    """Stepping carries a NaN or an infinity one point a step: outside that cone
+    the run is the one with any finite value in its place."""
+    f = np_dtype(dt)
+    rng = np.random.default_rng(N + K)
+    u0 = rng.uniform(-1, 1, (B, N)).astype(f)
+    for i, v in bad.items():
+        u0[B - 1, i] = v
+    bc = RING if ring else 0
+    print_case(test="cones", dt=dt, N=N, B=B, K=K, bad=bad, ring=ring)
+    x = dev(u0.reshape(-1), dt)
+    got = SyncPlan(N, torch_dtype(dt), nrods=B, boundary=bc).run(x, 0.4, 0.25, -0.5, K)
+    ref = SyncPlan(N, torch_dtype(dt), nrods=B, boundary=bc,
+                   sync_kernel=abi.HEAT1D_SYNC_STEP).run(x, 0.4, 0.25, -0.5, K)
+    got, ref = got.cpu().numpy(), ref.cpu().numpy()
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    fin = np.isfinite(ref)
+    assert np.array_equal(np.isfinite(got), fin)
+    if fin.any():
+        assert normwise(got[fin], ref[fin]) <= tol_for(dt)
+
+
+def test_band_passes_replay_in_a_graph():
+    N, K = 30001, 500
+    plan = SyncPlan(N, torch.float32)
+    xs = [torch.randn(N, generator=torch.Generator().manual_seed(i)).to(DEV) for i in range(3)]
+    want = [plan.run(x, 0.4, 0.25, -0.5, K).clone() for x in xs]
+    x, out = xs[0].clone(), torch.empty(N, device=DEV)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        plan.run(x, 0.4, 0.25, -0.5, K, out=out)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g, stream=s):
+            plan.run(x, 0.4, 0.25, -0.5, K, out=out)
+    torch.cuda.current_stream().wait_stream(s)
+    for i in (1, 2, 0, 1):
+        x.copy_(xs[i])
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[i])
+        _ = SyncPlan(N, torch.float32).run(xs[2], 0.3, 0.0, 0.0, 64)   # eager work in between
+        torch.cuda.synchronize()

@@ -33,6 +33,21 @@ namespace {
 constexpr int32_t kBandFrom = 64;
 
 constexpr size_t kAlign = 256;
+// The same for the rods of a batch, and for the long rods of an emulated
+// asynchronous run.  Shorter runs there agree bit for bit with one launch per
+// step, which callers compare them with, and they are short either way.
+constexpr int32_t kBatchBandFrom = 448;
+
+// FP32 stepping drifts: late in a run the change of a point in one step is a
+// few roundings of its value, and they do not average out.  Against 64 bits
+// the single-step kernels are off by 1e-6 to 2e-5 of the state after K (1 +
+// 0.1 / r) = 6200 steps, growing to 8e-5 at 20000, where one pass stays at 2e-7.
+// Beyond this length FP32 runs keep stepping, or every result of theirs would
+// move by that much.
+bool fp32_drifts(int dtype, double r, int64_t K) {
+  return dtype == HEAT1D_F32 && (double)K * (1.0 + 0.1 / r) > 6200.0;
+}
+
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 size_t esize(int dtype) { return dtype == HEAT1D_F32 ? 4 : 8; }
 int vec_width(int dtype) { return dtype == HEAT1D_F32 ? 4 : 2; }
@@ -320,8 +335,8 @@ size_t sync_state_bytes(heat1d_plan_t p) {
 // K steps of nrods rods as band passes (heat1d_band.h): K is cut into equal
 // passes that alternate between out and ping (which a single pass does not
 // touch); the last one leaves u(K) in out, and D A^(K-1) u0 in z when z is
-// given.  dot: the partial sums of the input with dot_with.  scratch:
-// band_scratch_bytes.
+// given.  dot: K times the partial sums of the input with dot_with.  out may be
+// NULL where a single pass only wants z.  scratch: band_scratch_bytes.
 int run_band(heat1d_plan_t p, int64_t nrods, const void* in, void* out, double r, double c1,
              double cN, int64_t K, void* ping, void* scratch, void* z, const void* dot_with,
              double* dot, hipStream_t s) {
@@ -361,8 +376,9 @@ int run_band(heat1d_plan_t p, int64_t nrods, const void* in, void* out, double r
   return HEAT1D_OK;
 }
 
-bool takes_band(heat1d_plan_t p, int64_t K, const void* ws) {
-  return p->band_from > 0 && K >= p->band_from && ws != nullptr;
+// Whether K steps, of a run of `of` steps in all, take band passes.
+bool takes_band(heat1d_plan_t p, double r, int64_t K, int64_t of, const void* ws) {
+  return p->band_from > 0 && K >= p->band_from && ws != nullptr && !fp32_drifts(p->dtype, r, of);
 }
 
 int run_sync_impl(heat1d_plan_t p, const void* u0, void* uK, double r, double c1, double cN,
@@ -395,6 +411,7 @@ int run_sync_impl(heat1d_plan_t p, const void* u0, void* uK, double r, double c1
   }
   if (K == 0) return hip_status(launch_impose_ends(p->dtype, u0, uK, N, B, c1, cN, s));
   if (kernel == HEAT1D_SYNC_RESIDENT) {
+  b.dot_scale = (double)K;
     EventPair* e = timing_begin(p, s);
     hipError_t err = launch_sync_resident(p->dtype, M, waves, u0, uK, N, B, K, r, c1, cN, s);
     timing_end(e, s);
@@ -447,10 +464,11 @@ int run_sync_impl(heat1d_plan_t p, const void* u0, void* uK, double r, double c1
 }
 
 // run_sync_impl with the plan's kernel, or band passes where the plan leaves the
-// choice open and the run is long enough.  ws: heat1d_sync_workspace_bytes.
+// choice open and the run is long enough: K steps of a run of `of` steps in all.
+// ws: heat1d_sync_workspace_bytes.
 int run_sync_plan(heat1d_plan_t p, const void* u0, void* uK, double r, double c1, double cN,
-                  int64_t K, void* ws, hipStream_t s) {
-  if (takes_band(p, K, ws))
+                  int64_t K, int64_t of, void* ws, hipStream_t s) {
+  if (takes_band(p, r, K, of, ws))
     return run_band(p, p->nrods, u0, uK, r, c1, cN, K, ws, (char*)ws + sync_state_bytes(p),
                     nullptr, nullptr, nullptr, s);
   return run_sync_impl(p, u0, uK, r, c1, cN, K, ws, s, p->sync_kernel, p->T, p->M,
@@ -721,7 +739,7 @@ int heat1d_run_sync(heat1d_plan_t p, const void* u0, void* uK, double r, double 
                      !overlaps(workspace, wsb, uK, bytes);
   if (K > 1 && p->sync_kernel != HEAT1D_SYNC_RESIDENT && !ws_ok) return HEAT1D_EINVAL;
   if (K > INT32_MAX) return HEAT1D_EUNSUPPORTED;
-  return run_sync_plan(p, u0, uK, r, c1, cN, K, ws_ok ? workspace : nullptr,
+  return run_sync_plan(p, u0, uK, r, c1, cN, K, K, ws_ok ? workspace : nullptr,
                        (hipStream_t)stream);
 }
 
@@ -767,7 +785,7 @@ int heat1d_run_sync_observed(heat1d_plan_t p, const void* u0, void* uK, double r
     // the buffers alternate so that the last chunk lands in uK
     void* out = ((nchunks - j) % 2 == 0) ? uK : (void*)extra;
     const int64_t steps = j <= full ? every : rem;
-    const int st = run_sync_plan(p, in, out, r, c1, cN, steps, ws, s);
+    const int st = run_sync_plan(p, in, out, r, c1, cN, steps, K, ws, s);
     if (st != HEAT1D_OK) return st;
     if (j <= full) {
       e = launch_state_norms(p->dtype, out, N, B, c1, cN, partials, norms + j, nobs, s, !ring);
@@ -851,7 +869,7 @@ int heat1d_autotune_sync(heat1d_plan_t p, const void* u0, void* uK, double r, in
     }
   }
   // band passes against the best of them, where the plan may take them
-  if (status == HEAT1D_OK && p->band_from > 0 && K_probe >= p->band_from) {
+  if (status == HEAT1D_OK && takes_band(p, r, K_probe, K_probe, workspace)) {
     char* scr = (char*)workspace + sync_state_bytes(p);
     float ms = 0.f;
     for (int rep = 0; rep < 2 && status == HEAT1D_OK; ++rep) {

@@ -34,6 +34,8 @@ struct BandRun {
 };
 BandRun band_run(int dtype, double r, int64_t K);
 
+constexpr size_t kBandWeightBytes = ((size_t)2 * (kBandMaxReach + 1) * 8 + 16 + 255) / 256 * 256;
+
 // Bytes of scratch (256-byte aligned) of the passes over nrods rods of N points:
 // two sets of weights, the flags and a record per tile.
 size_t band_scratch_bytes(int64_t N, int64_t nrods);
@@ -49,13 +51,17 @@ struct BandPass {
   int ring = 0;
   void* scratch = nullptr;
   int slot = 0;        // passes of one run alternate 0, 1 (whose flag is in use)
+  int32_t* flag = nullptr;  // raise this flag instead, and keep no records: the
+                            // caller does without launch_band_cones, and scratch
+                            // needs kBandWeightBytes only
   // z, when not NULL, receives D A^(T-1) applied to the state (D the second
   // difference): K z is du(K)/dr, see heat1d_backward_checkpointed
   void* z = nullptr;
-  // dot, when not NULL: partial sums of in . dot_with over each tile's inner
-  // points, one double per tile (band_tiles per rod)
+  // dot, when not NULL: dot_scale times the sum of in . dot_with over each
+  // tile's inner points, one double per tile (band_tiles per rod)
   const void* dot_with = nullptr;
   double* dot = nullptr;
+  double dot_scale = 1.0;
 };
 bool band_applies(int dtype, int64_t N, int64_t nrods);
 int64_t band_tiles(int dtype, int64_t N, int64_t nrods);  // tiles per rod

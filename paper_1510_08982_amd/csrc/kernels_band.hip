@@ -33,7 +33,13 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 template <typename F> struct Band;
 template <> struct Band<float> {
   using Acc = f32x4;
+  using Sum = f64x4;
   static constexpr int pad = 4;  // elements of padding per 16 points
+  // chunks (of 16 terms) whose sum is formed in FP32 before it is added to the
+  // whole, which is kept in FP64: one running FP32 sum of all terms rounds a
+  // hundred times at the size of the result (3.5e-7 of it against 64 bits on
+  // the 2^26-point rod, where stepping has 0.9e-7)
+  static constexpr int group = 4;
   static constexpr int nt_large = 8;
   static __device__ __forceinline__ Acc mma(float a, float b, Acc c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -43,7 +49,9 @@ template <> struct Band<float> {
 };
 template <> struct Band<double> {
   using Acc = f64x4;
+  using Sum = f64x4;
   static constexpr int pad = 2;
+  static constexpr int group = 1 << 20;  // one running sum
   static constexpr int nt_large = 4;
   static __device__ __forceinline__ Acc mma(double a, double b, Acc c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
@@ -52,7 +60,8 @@ template <> struct Band<double> {
   static __device__ __forceinline__ int row(int i) { return 4 * (i & 3) + (i >> 2); }
 };
 
-constexpr int kBandTile = 256;       // outputs of one MFMA tile
+constexpr int kBandTile = 256;    // outputs of one MFMA tile
+constexpr int kStepWeights = 64;  // runs whose weights are stepped
 
 // Record of the points of a tile that are not finite: first and last of them,
 // counted from the tile's first point (first > last: none).
@@ -128,8 +137,28 @@ BandRun band_run(int dtype, double r, int64_t K) {
 template <typename F>
 __device__ __forceinline__ void band_weights(F* w, int H, double T, double r, bool lap, int d0,
                                              int step, double* s_g, double* s_c) {
-  const int M = (2 * H + 2 + 15) / 16 * 16, half = M / 2;
   const double steps = lap ? T - 1.0 : T;
+  if (T <= kStepWeights) {
+    // a few steps: step a unit value (weights that are zero come out as zero)
+    double *cur = s_g, *nxt = s_c;
+    const int t = (int)steps, d = threadIdx.x;
+    if (d < kStepWeights + 2) cur[d] = d == 0 ? 1.0 : 0.0;
+    for (int k = 0; k < t + (lap ? 1 : 0); ++k) {
+      __syncthreads();
+      if (d < kStepWeights + 1) {
+        const double c = cur[d], l2 = (d == 0 ? cur[1] : cur[d - 1]) + cur[d + 1] - 2.0 * c;
+        nxt[d] = k < t ? __builtin_fma(r, l2, c) : l2;
+      }
+      if (d == kStepWeights + 1) nxt[d] = 0.0;
+      double* was = cur;
+      cur = nxt;
+      nxt = was;
+    }
+    __syncthreads();
+    if (d0 == 0 && d <= H) w[d] = (F)cur[d];
+    return;
+  }
+  const int M = (2 * H + 2 + 15) / 16 * 16, half = M / 2;
   const bool neg = fmod(steps, 2.0) != 0.0;  // an odd power
   // g^steps <= exp(-steps a), a = 4 r sin^2; |g|^steps <= exp(-steps b), b = 2 - a
   const double lim = steps > 0.0 ? 56.0 / steps : 4.0;
@@ -251,6 +280,12 @@ __device__ __forceinline__ F band_value(const BandRod<F>& a, int64_t j) {
   return a.in[j];
 }
 
+template <typename Sum, typename Acc>
+__device__ __forceinline__ void band_add(Sum& s, const Acc& x) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) s[e] += (double)x[e];
+}
+
 // Blocks are dealt to the 8 XCDs in turn: give each XCD a run of consecutive
 // tiles, whose halos overlap, so that its L2 holds them.
 __device__ __forceinline__ int band_block(int b, int n) {
@@ -263,9 +298,11 @@ __device__ __forceinline__ int band_block(int b, int n) {
 // range of one such set and add their sums in LDS.  dot: see BandPass.
 template <typename F, int NT, int WO, int WS, bool kTwo>
 __device__ __forceinline__ void band_tile(const BandRod<F>& a, int64_t t0, BandRec* rec, int* flag,
-                                          const F* dot_with, double* dot, F* xs) {
+                                          const F* dot_with, double* dot, double dot_scale,
+                                          F* xs) {
   using B = Band<F>;
   using Acc = typename B::Acc;
+  using Sum = typename B::Sum;
   using VT = typename Vec<F>::T;
   constexpr int V = Vec<F>::n;
   constexpr int kThreads = WO * WS * kWave;
@@ -328,7 +365,7 @@ __device__ __forceinline__ void band_tile(const BandRod<F>& a, int64_t t0, BandR
   }
   __syncthreads();
   if (tid == 0) {
-    *rec = BandRec{s_first, s_last};
+    if (rec != nullptr) *rec = BandRec{s_first, s_last};
     if (s_last >= 0) atomicOr(flag, 1);
   }
 
@@ -338,36 +375,46 @@ __device__ __forceinline__ void band_tile(const BandRod<F>& a, int64_t t0, BandR
   const int cb = chunks * ws / WS, ce = chunks * (ws + 1) / WS;
   const F* xl = xs + (wo * NT * 16 + n) * kStride + 4 * g;
   const F* wa = wl + 4 * g + 15 - B::row(n);
-  Acc acc[NT] = {};
-  Acc acc2[kTwo ? NT : 1] = {};
+  Sum acc[NT] = {};
+  Sum acc2[kTwo ? NT : 1] = {};
   // wavefronts past the end of the rod have nothing to write
   if (t0 + wo * NT * kBandTile < N) {
-    for (int c = cb; c < ce; ++c) {
-      F wv[4], wv2[4], x[NT][4];
+    for (int c = cb; c < ce;) {
+      Acc part[NT] = {};
+      Acc part2[kTwo ? NT : 1] = {};
+      const int end = ce - c < B::group ? ce : c + B::group;
+      for (; c < end; ++c) {
+        F wv[4], wv2[4], x[NT][4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) wv[e] = wa[16 * c + e];
-      if constexpr (kTwo) {
+        for (int e = 0; e < 4; ++e) wv[e] = wa[16 * c + e];
+        if constexpr (kTwo) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) wv2[e] = wa[2 * a.Hp + 32 + 16 * c + e];
+          for (int e = 0; e < 4; ++e) wv2[e] = wa[2 * a.Hp + 32 + 16 * c + e];
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const F* px = xl + (16 * t + c) * kStride;
+#pragma unroll
+          for (int e = 0; e < 4; e += V) {
+            const VT v = *reinterpret_cast<const VT*>(px + e);
+            const F* pv = reinterpret_cast<const F*>(&v);
+#pragma unroll
+            for (int k = 0; k < V; ++k) x[t][e + k] = pv[k];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            part[t] = B::mma(wv[e], x[t][e], part[t]);
+            if constexpr (kTwo) part2[t] = B::mma(wv2[e], x[t][e], part2[t]);
+          }
+        }
       }
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        const F* px = xl + (16 * t + c) * kStride;
-#pragma unroll
-        for (int e = 0; e < 4; e += V) {
-          const VT v = *reinterpret_cast<const VT*>(px + e);
-          const F* pv = reinterpret_cast<const F*>(&v);
-#pragma unroll
-          for (int k = 0; k < V; ++k) x[t][e + k] = pv[k];
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          acc[t] = B::mma(wv[e], x[t][e], acc[t]);
-          if constexpr (kTwo) acc2[t] = B::mma(wv2[e], x[t][e], acc2[t]);
-        }
+        band_add(acc[t], part[t]);
+        if constexpr (kTwo) band_add(acc2[t], part2[t]);
       }
     }
   }
@@ -386,13 +433,14 @@ __device__ __forceinline__ void band_tile(const BandRod<F>& a, int64_t t0, BandR
   }
   if constexpr (WS > 1) {
     __syncthreads();  // every wavefront is done with the state
-    Acc* sums = reinterpret_cast<Acc*>(xs);
+    Sum* sums = reinterpret_cast<Sum*>(xs);
     constexpr int kSets = kTwo ? 2 * NT : NT;
     if (ws > 0) {
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         sums[((wo * (WS - 1) + ws - 1) * kSets + t) * kWave + lane] = acc[t];
-        if constexpr (kTwo) sums[((wo * (WS - 1) + ws - 1) * kSets + NT + t) * kWave + lane] = acc2[t];
+        if constexpr (kTwo)
+          sums[((wo * (WS - 1) + ws - 1) * kSets + NT + t) * kWave + lane] = acc2[t];
       }
     }
     __syncthreads();
@@ -401,7 +449,8 @@ __device__ __forceinline__ void band_tile(const BandRod<F>& a, int64_t t0, BandR
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           acc[t] += sums[((wo * (WS - 1) + o) * kSets + t) * kWave + lane];
-          if constexpr (kTwo) acc2[t] += sums[((wo * (WS - 1) + o) * kSets + NT + t) * kWave + lane];
+          if constexpr (kTwo)
+            acc2[t] += sums[((wo * (WS - 1) + o) * kSets + NT + t) * kWave + lane];
         }
       }
     }
@@ -413,7 +462,7 @@ __device__ __forceinline__ void band_tile(const BandRod<F>& a, int64_t t0, BandR
     __syncthreads();
     if (tid == 0) {
       for (int i = 1; i < WO * WS; ++i) part += s_dot[i];
-      *dot = part;
+      *dot = dot_scale * part;
     }
   }
   if (ws != 0) return;
@@ -428,14 +477,14 @@ __device__ __forceinline__ void band_tile(const BandRod<F>& a, int64_t t0, BandR
     F y[4], y2[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      y[e] = acc[t][e];
-      if constexpr (kTwo) y2[e] = acc2[t][e];
+      y[e] = (F)acc[t][e];
+      if constexpr (kTwo) y2[e] = (F)acc2[t][e];
     }
     const bool inner = a.ring ? q + 4 <= N : (q > 0 && q + 4 < N && !a.straight);
     if (!inner && !a.ring) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        if (a.straight) y[e] = (F)((double)y[e] + band_line(a, q + e));
+        if (a.straight) y[e] = (F)((double)acc[t][e] + band_line(a, q + e));
         if (q + e == 0) y[e] = a.e1;
         if (q + e == N - 1) y[e] = a.eN;
         if constexpr (kTwo)
@@ -537,6 +586,7 @@ struct BandArgs {
   BandRod<F> rod;  // the first
   const F* dot_with;
   double* dot;
+  double dot_scale;
   int* flag;
   BandRec* rec;
   int tiles;       // per rod
@@ -557,9 +607,10 @@ __global__ __launch_bounds__(WO* WS * kWave) void band_kernel(const BandArgs<F> 
   const int block = band_block(blockIdx.x, gridDim.x);
   const int rodi = block / a.tiles;
   const int64_t t0 = (int64_t)(block - rodi * a.tiles) * (NT * WO * kBandTile);
-  band_tile<F, NT, WO, WS, kTwo>(band_rod(a, rodi), t0, a.rec + block, a.flag,
+  band_tile<F, NT, WO, WS, kTwo>(band_rod(a, rodi), t0, a.rec != nullptr ? a.rec + block : nullptr,
+                                 a.flag,
                                  a.dot != nullptr ? a.dot_with + rodi * a.rod.N : nullptr,
-                                 a.dot != nullptr ? a.dot + block : nullptr,
+                                 a.dot != nullptr ? a.dot + block : nullptr, a.dot_scale,
                                  reinterpret_cast<F*>(band_lds));
 }
 
@@ -581,9 +632,10 @@ __global__ __launch_bounds__(256) void band_cone_kernel(const BandArgs<F> a, int
 // CU two blocks and pad a rod by no more than an eighth; else 2048 outputs; else
 // 256, eight wavefronts sharing the K range, so that a rod of a few thousand
 // points still spreads over the chip.
+// Passes that also write z hold twice the sums: half as many tiles.
 template <typename F>
-static int band_out(int64_t N, int64_t nrods) {
-  constexpr int64_t large = (int64_t)Band<F>::nt_large * 4 * kBandTile;
+static int band_out(int64_t N, int64_t nrods, bool two = false) {
+  const int64_t large = (int64_t)Band<F>::nt_large / (two ? 2 : 1) * 4 * kBandTile;
   const int64_t nl = (N + large - 1) / large, nm = (N + 2047) / 2048;
   if (nl * nrods >= 512 && nl * large * 8 <= nm * 2048 * 9) return (int)large;
   if (nm * nrods >= 512 && N >= 1024) return 2048;
@@ -616,9 +668,11 @@ static BandArgs<F> band_args(const BandPass& p) {
   band_ends(a.rod, (F)p.c1, (F)p.cN);
   a.dot_with = (const F*)p.dot_with;
   a.dot = p.dot;
-  a.flag = s.flag + p.slot;
-  a.rec = s.rec;
-  a.tiles = (int)band_tiles(p.dtype, p.N, p.nrods);
+  a.dot_scale = p.dot_scale;
+  a.flag = p.flag != nullptr ? p.flag : s.flag + p.slot;
+  a.rec = p.flag != nullptr ? nullptr : s.rec;
+  const int64_t o = band_out<F>(p.N, p.nrods, p.z != nullptr);
+  a.tiles = (int)((p.N + o - 1) / o);
   return a;
 }
 
@@ -645,7 +699,7 @@ static size_t band_lds_bytes(int Hp) {
   const size_t xs = (size_t)(NT * WO * kBandTile + 2 * Hp) / 16 * kStride;
   size_t lds = (xs + (size_t)(kTwo ? 2 : 1) * (2 * Hp + 32)) * sizeof(F);
   if (WS > 1)
-    lds = std::max(lds, (size_t)WO * (WS - 1) * (kTwo ? 2 : 1) * NT * kWave * 4 * sizeof(F));
+    lds = std::max(lds, (size_t)WO * (WS - 1) * (kTwo ? 2 : 1) * NT * kWave * 4 * 8);
   return lds;
 }
 
@@ -667,10 +721,10 @@ template <typename F, bool kTwo>
 static hipError_t band_dispatch(const BandPass& p, hipStream_t s) {
   const BandArgs<F> a = band_args<F>(p);
   if (a.rod.H > kBandMaxReach) return hipErrorInvalidValue;
-  const int o = band_out<F>(p.N, p.nrods);
+  const int o = band_out<F>(p.N, p.nrods, kTwo);
   if (o == kBandTile) return band_launch<F, 1, 1, 8, kTwo>(a, p.nrods, s);
   if (o == 2048) return band_launch<F, 2, 4, 1, kTwo>(a, p.nrods, s);
-  return band_launch<F, Band<F>::nt_large, 4, 1, kTwo>(a, p.nrods, s);
+  return band_launch<F, Band<F>::nt_large / (kTwo ? 2 : 1), 4, 1, kTwo>(a, p.nrods, s);
 }
 
 hipError_t launch_band_pass(const BandPass& p, hipStream_t s) {
@@ -685,7 +739,7 @@ static hipError_t band_cones(const BandPass& p, hipStream_t s) {
   const int64_t blocks = (int64_t)a.tiles * p.nrods;
   hipLaunchKernelGGL(band_cone_kernel<F>, dim3((unsigned)std::min<int64_t>(blocks, 1024)),
                      dim3(256), 0, s, a, band_scratch(p.scratch).flag + (1 - p.slot), p.T,
-                     band_out<F>(p.N, p.nrods), blocks);
+                     band_out<F>(p.N, p.nrods, p.z != nullptr), blocks);
   return hipGetLastError();
 }
 

@@ -426,7 +426,10 @@ int heat1d_batched_prepare(heat1d_plan_t plan, void *workspace, void *stream);
  * launch.  Rod b occupies elements [offsets[b], offsets[b+1]) of u0 / uK
  * (offsets: int64 device array of nrods+1 entries, offsets[0] = 0, lengths
  * equal to the plan's N_host).  r, c1, cN: double device arrays (one per rod,
- * r in (0, 0.5]); K: int32 device array equal to the plan's K_host. */
+ * r in (0, 0.5]); K: int32 device array equal to the plan's K_host.  Rods of
+ * 448 steps or more (FP32: at most 5166) take a band pass (HEAT1D_SYNC_AUTO)
+ * unless opts.waves or opts.sync_kernel is set; the others step, bit for bit as
+ * one launch per step does. */
 int heat1d_run_batched(heat1d_plan_t plan, const void *u0, void *uK, const int64_t *offsets,
                        const double *r, const double *c1, const double *cN, const int32_t *K,
                        void *workspace, void *stream);

@@ -89,6 +89,10 @@ struct heat1d_plan_s {
   int32_t small_first = 0;  // workgroups that start with the group and wavefront queues
   bool tuned = false;       // the batched work order was chosen by timing
   // timing of the dominant kernel
+  // rods that take a band pass: their tiles, rod indices and weight offsets
+  std::vector<BandItem> band_items;
+  std::vector<int32_t> band_rods, band_woff;
+  int32_t band_hmax = 0;
   bool timing = false;
   std::vector<EventPair> ev;
   size_t ev_used = 0;
@@ -146,10 +150,11 @@ void describe(heat1d_plan_t p) {
   if (p->batched) {
     std::snprintf(buf, sizeof buf,
                   "batched rods=%zu dtype=%s wg_rods=%zu group_rods=%zu wave_rods=%zu groups=%d "
-                  "small_first=%d t_wave=%lld t_group=%lld%s",
+                  "small_first=%d t_wave=%lld t_group=%lld band_rods=%zu%s",
                   p->Nh.size(), p->dtype == HEAT1D_F32 ? "f32" : "f64", p->order[0].size(),
                   p->order[1].size(), p->order[2].size(), p->groups, p->small_first,
-                  (long long)p->t_wave, (long long)p->t_group, p->tuned ? " tuned" : "");
+                  (long long)p->t_wave, (long long)p->t_group, p->band_rods.size(),
+                  p->tuned ? " tuned" : "");
   } else if (p->sync_kernel == HEAT1D_SYNC_STEP) {
     std::snprintf(buf, sizeof buf, "step N=%lld rods=%lld", (long long)p->N, (long long)p->nrods);
   } else if (p->sync_kernel == HEAT1D_SYNC_RESIDENT) {
@@ -560,6 +565,35 @@ int heat1d_plan_create(heat1d_plan_t* out, int64_t N, int32_t dtype, const heat1
   if (p->opts.watchdog_polls > 0) p->watchdog = p->opts.watchdog_polls;
   p->ckpt_stride = p->opts.ckpt_stride;
   default_sync_choice(p);
+// Take the rods of at least kBatchBandFrom steps out of the queues (by_work):
+// they run as band passes, in tiles, the most work first.  Room for the weights
+// of any r; a rod whose reach could pass kBandMaxReach stays in the queues, and
+// so does every rod of a plan that names a block size (opts.waves).
+void batched_split_band(heat1d_plan_t p) {
+  if (p->opts.waves > 0 || p->opts.sync_kernel != HEAT1D_SYNC_AUTO) return;
+  std::vector<int32_t> rest;
+  int64_t tiles = 0, w = 0;
+  for (int32_t b : p->by_work) {
+    const int h = band_reach(p->dtype, 0.5, std::max(p->Kh[b], 1));
+    const int64_t nt = (p->Nh[b] + kBandBatchTile - 1) / kBandBatchTile;
+    // r is known to the run only; 1/2 drifts least
+    if (p->Kh[b] < kBatchBandFrom || fp32_drifts(p->dtype, 0.5, p->Kh[b]) || h > kBandMaxReach || tiles + nt > (1 << 22) ||
+        w + h + 1 > INT32_MAX) {
+      rest.push_back(b);
+      continue;
+    }
+    for (int64_t t = 0; t < nt; ++t)
+      p->band_items.push_back({(int32_t)p->band_rods.size(), (int32_t)t});
+    p->band_rods.push_back(b);
+    p->band_woff.push_back((int32_t)w);
+    p->band_hmax = std::max(p->band_hmax, h);
+    tiles += nt;
+    w += h + 1;
+  }
+  p->band_woff.push_back((int32_t)w);
+  p->by_work = rest;
+}
+
   // explicit choices.  On an asynchronous plan (nsub > 0) with no explicit
   // synchronous kernel, waves and pts_per_lane shape the asynchronous kernel
   // only and the synchronous kernel keeps its defaults.
@@ -701,7 +735,7 @@ size_t batched_queue_off(heat1d_plan_t p, int q) {
 
 size_t heat1d_batched_workspace_bytes(heat1d_plan_t p) {
   if (!p || !p->batched) return 0;
-  return batched_queue_off(p, 3) + align_up(3 * 4);
+  return batched_band_layout(p).total;
 }
 
 int heat1d_set_timing(heat1d_plan_t plan, int32_t enable) {
@@ -716,6 +750,7 @@ double heat1d_last_kernel_ms(heat1d_plan_t plan, int64_t* launches) {
   if (!plan || plan->ev_used == 0) return -1.0;
   double total = 0.0;
   for (size_t i = 0; i < plan->ev_used; ++i) {
+  batched_split_band(p);
     if (hipEventSynchronize(plan->ev[i].b) != hipSuccess) return -1.0;
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, plan->ev[i].a, plan->ev[i].b) != hipSuccess) return -1.0;
@@ -760,6 +795,23 @@ int heat1d_run_sync_observed(heat1d_plan_t p, const void* u0, void* uK, double r
   if (K > INT32_MAX || p->nrods > 65535) return HEAT1D_EUNSUPPORTED;
   const int64_t N = p->N, B = p->nrods;
   const size_t bytes = (size_t)N * B * esize(p->dtype);
+// Behind the queues and their heads: the tiles, rods and weight offsets of the
+// band passes, their flag, records and weights.
+struct BatchedBandLayout {
+  size_t items, rods, woff, flag, rec, w, total;
+};
+BatchedBandLayout batched_band_layout(heat1d_plan_t p) {
+  BatchedBandLayout L{};
+  L.items = batched_queue_off(p, 3) + align_up(3 * 4);
+  L.rods = L.items + align_up(p->band_items.size() * sizeof(BandItem));
+  L.woff = L.rods + align_up(p->band_rods.size() * 4);
+  L.flag = L.woff + align_up(p->band_woff.size() * 4);
+  L.rec = L.flag + align_up(4);
+  L.w = L.rec + align_up(p->band_items.size() * 8);
+  L.total = L.w + align_up((p->band_woff.empty() ? 0 : (size_t)p->band_woff.back()) *
+                           esize(p->dtype));
+  return L;
+}
   const int64_t nobs = K / every + 1;
   const size_t nbytes = (size_t)B * nobs * 8;
   const size_t wsb = heat1d_observed_workspace_bytes(p);
@@ -1431,10 +1483,9 @@ int heat1d_run_batched(heat1d_plan_t p, const void* u0, void* uK, const int64_t*
                        void* workspace, void* stream) {
   const int st = check_batched(p, u0, uK, offsets, r, c1, cN, K, workspace);
   if (st != HEAT1D_OK) return st;
-  const BatchedLaunch b = batched_args(p, u0, uK, offsets, r, c1, cN, K, workspace);
   hipStream_t s = (hipStream_t)stream;
   EventPair* e = timing_begin(p, s);
-  hipError_t err = launch_batched(b, s);
+  hipError_t err = launch_batch(p, u0, uK, offsets, r, c1, cN, K, workspace, s);
   timing_end(e, s);
   return hip_status(err);
 }
@@ -1454,11 +1505,11 @@ int heat1d_autotune_batched(heat1d_plan_t p, const void* u0, void* uK, const int
   // time the plan's current split: the better of two runs
   auto time_current = [&](double* ms) -> int {
     if (heat1d_batched_prepare(p, workspace, stream) != HEAT1D_OK) return HEAT1D_EHIP;
-    const BatchedLaunch b = batched_args(p, u0, uK, offsets, r, c1, cN, K, workspace);
     *ms = 1e30;
     for (int rep = 0; rep < 2; ++rep) {
       if (hipEventRecord(ev[0], s) != hipSuccess) return HEAT1D_EHIP;
-      if (launch_batched(b, s) != hipSuccess) return HEAT1D_EHIP;
+      if (launch_batch(p, u0, uK, offsets, r, c1, cN, K, workspace, s) != hipSuccess)
+        return HEAT1D_EHIP;
       if (hipEventRecord(ev[1], s) != hipSuccess || hipEventSynchronize(ev[1]) != hipSuccess)
         return HEAT1D_EHIP;
       float t = 0.f;
@@ -1520,6 +1571,16 @@ int heat1d_autotune_batched(heat1d_plan_t p, const void* u0, void* uK, const int
   const int up = heat1d_batched_prepare(p, workspace, stream);
   if (rc == HEAT1D_OK) rc = up;
   hipEventDestroy(ev[0]);
+  if (!p->band_items.empty()) {
+    const BatchedBandLayout L = batched_band_layout(p);
+    if (hipMemcpyAsync(ws + L.items, p->band_items.data(), p->band_items.size() * sizeof(BandItem),
+                       hipMemcpyHostToDevice, s) != hipSuccess ||
+        hipMemcpyAsync(ws + L.rods, p->band_rods.data(), p->band_rods.size() * 4,
+                       hipMemcpyHostToDevice, s) != hipSuccess ||
+        hipMemcpyAsync(ws + L.woff, p->band_woff.data(), p->band_woff.size() * 4,
+                       hipMemcpyHostToDevice, s) != hipSuccess)
+      return HEAT1D_EHIP;
+  }
   hipEventDestroy(ev[1]);
   describe(p);
   if (best_ms) *best_ms = best;
@@ -1565,6 +1626,40 @@ int heat1d_forward_checkpointed(heat1d_plan_t p, const void* u0, void* uK, doubl
     if (uK) return hip_status(launch_impose_ends(p->dtype, u0, uK, N, B, c1, cN, s));
     return HEAT1D_OK;
   }
+// The whole batch: the queues' rods in the persistent kernel, the others as
+// band passes.
+hipError_t launch_batch(heat1d_plan_t p, const void* u0, void* uK, const int64_t* offsets,
+                        const double* r, const double* c1, const double* cN, const int32_t* K,
+                        void* workspace, hipStream_t s) {
+  char* ws = (char*)workspace;
+  hipError_t e = hipSuccess;
+  if (!p->band_items.empty()) {
+    const BatchedBandLayout L = batched_band_layout(p);
+    BandBatch b;
+    b.dtype = p->dtype;
+    b.in = u0;
+    b.out = uK;
+    b.offsets = offsets;
+    b.r = r;
+    b.c1 = c1;
+    b.cN = cN;
+    b.K = K;
+    b.items = (const BandItem*)(ws + L.items);
+    b.rods = (const int32_t*)(ws + L.rods);
+    b.woff = (const int32_t*)(ws + L.woff);
+    b.w = ws + L.w;
+    b.flag = (int32_t*)(ws + L.flag);
+    b.rec = ws + L.rec;
+    b.nitems = (int32_t)p->band_items.size();
+    b.nslots = (int32_t)p->band_rods.size();
+    b.hmax = p->band_hmax;
+    e = launch_band_batch(b, s);
+  }
+  if (e == hipSuccess && !p->by_work.empty())
+    e = launch_batched(batched_args(p, u0, uK, offsets, r, c1, cN, K, workspace), s);
+  return e;
+}
+
   for (int64_t j = 0; j < L.nseg; ++j) {
     const int steps = (int)std::min<int64_t>(L.S, K - j * L.S);
     const void* in = ws + L.ckpt_off + j * L.state_bytes;

@@ -69,4 +69,31 @@ hipError_t launch_band_weights(const BandPass& p, hipStream_t s);
 hipError_t launch_band_pass(const BandPass& p, hipStream_t s);
 hipError_t launch_band_cones(const BandPass& p, hipStream_t s);
 
+// Rods of uneven length, step count and r: tiles of kBandBatchTile points, one
+// workgroup each.  All pointers are device memory.
+constexpr int kBandBatchTile = 2048;
+struct BandItem {
+  int32_t slot;  // index into rods / woff
+  int32_t tile;
+};
+struct BandBatch {
+  int dtype = 0;
+  const void* in = nullptr;
+  void* out = nullptr;
+  const int64_t* offsets = nullptr;
+  const double* r = nullptr;
+  const double* c1 = nullptr;
+  const double* cN = nullptr;
+  const int32_t* K = nullptr;
+  const BandItem* items = nullptr;  // a rod's tiles one after the other
+  const int32_t* rods = nullptr;    // of each slot
+  const int32_t* woff = nullptr;    // slots + 1: where a slot's weights start
+  void* w = nullptr;
+  int32_t* flag = nullptr;
+  void* rec = nullptr;              // 8 bytes per item
+  int32_t nitems = 0, nslots = 0;
+  int32_t hmax = 0;                 // the longest reach that woff leaves room for
+};
+hipError_t launch_band_batch(const BandBatch& b, hipStream_t s);
+
 }  // namespace heat1d

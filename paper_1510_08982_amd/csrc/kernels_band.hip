@@ -747,4 +747,135 @@ hipError_t launch_band_cones(const BandPass& p, hipStream_t s) {
   return p.dtype == 0 ? band_cones<float>(p, s) : band_cones<double>(p, s);
 }
 
+// ---- rods of uneven length ------------------------------------------------
+template <typename F>
+struct BandBatchArgs {
+  const F* in;
+  F* out;
+  const int64_t* offsets;
+  const double* r;
+  const double* c1;
+  const double* cN;
+  const int32_t* K;
+  const BandItem* items;
+  const int32_t* rods;
+  const int32_t* woff;
+  F* w;
+  int* flag;
+  BandRec* rec;
+  int nitems;
+};
+
+// r of a slot as the run uses it; 0 where the caller's is not a number in
+// [0, 1/2] (its rod is then written as NaN).
+template <typename F>
+__device__ __forceinline__ bool band_batch_r(const BandBatchArgs<F>& a, int rod, double* r) {
+  const double x = (double)(F)a.r[rod];
+  const bool ok = x >= 0.0 && x <= 0.5;
+  *r = ok ? x : 0.0;
+  return ok;
+}
+
+template <typename F>
+__device__ __forceinline__ int band_batch_reach(const BandBatchArgs<F>& a, int slot, double r,
+                                                int K) {
+  return min(band_reach_of<F>(r, (double)K), a.woff[slot + 1] - a.woff[slot] - 1);
+}
+
+template <typename F>
+__device__ __forceinline__ BandRod<F> band_batch_rod(const BandBatchArgs<F>& a, int slot) {
+  const int rod = a.rods[slot];
+  const int64_t off = a.offsets[rod];
+  double r;
+  band_batch_r(a, rod, &r);
+  BandRod<F> b;
+  b.in = a.in + off;
+  b.out = a.out + off;
+  b.z = nullptr;
+  b.w = a.w + a.woff[slot];
+  b.w2 = nullptr;
+  b.N = a.offsets[rod + 1] - off;
+  b.H = band_batch_reach(a, slot, r, a.K[rod]);
+  b.Hp = (b.H + 15) / 16 * 16;
+  b.ring = false;
+  band_ends(b, (F)a.c1[rod], (F)a.cN[rod]);
+  return b;
+}
+
+template <typename F>
+__global__ __launch_bounds__(256) void band_batch_weights_kernel(const BandBatchArgs<F> a) {
+  __shared__ double s_g[kBandMaxReach + 16], s_c[kBandMaxReach + 16];
+  const int slot = blockIdx.x, rod = a.rods[slot];
+  if (slot == 0 && threadIdx.x == 0) *a.flag = 0;
+  double r;
+  const bool ok = band_batch_r(a, rod, &r);
+  const int H = band_batch_reach(a, slot, r, a.K[rod]);
+  F* w = a.w + a.woff[slot];
+  band_weights<F>(w, H, (double)a.K[rod], r, false, 0, 256, s_g, s_c);
+  if (!ok && threadIdx.x == 0) w[0] = (F)__builtin_nan("");
+}
+
+// One tile per workgroup of four wavefronts: 22 thousand tiles for 4096 rods
+// of 256 to 65536 points, so the chip stays even to the end without queues.
+template <typename F>
+__global__ __launch_bounds__(256) void band_batch_kernel(const BandBatchArgs<F> a) {
+  extern __shared__ __align__(16) char band_lds[];
+  const int i = band_block(blockIdx.x, gridDim.x);
+  const BandItem it = a.items[i];
+  band_tile<F, 2, 4, 1, false>(band_batch_rod(a, uniform(it.slot)),
+                               (int64_t)uniform(it.tile) * kBandBatchTile, a.rec + i, a.flag,
+                               nullptr, nullptr, 0.0, reinterpret_cast<F*>(band_lds));
+}
+
+template <typename F>
+__global__ __launch_bounds__(256) void band_batch_cone_kernel(const BandBatchArgs<F> a) {
+  if (*a.flag == 0) return;
+  for (int i = blockIdx.x; i < a.nitems; i += gridDim.x) {
+    const BandItem it = a.items[i];
+    const BandRod<F> rod = band_batch_rod(a, it.slot);
+    band_cone(rod, it.tile, (rod.N + kBandBatchTile - 1) / kBandBatchTile, kBandBatchTile,
+              a.rec + (i - it.tile), (int64_t)a.K[a.rods[it.slot]]);
+  }
+}
+
+template <typename F>
+static hipError_t band_batch(const BandBatch& b, hipStream_t s) {
+  BandBatchArgs<F> a;
+  a.in = (const F*)b.in;
+  a.out = (F*)b.out;
+  a.offsets = b.offsets;
+  a.r = b.r;
+  a.c1 = b.c1;
+  a.cN = b.cN;
+  a.K = b.K;
+  a.items = b.items;
+  a.rods = b.rods;
+  a.woff = b.woff;
+  a.w = (F*)b.w;
+  a.flag = b.flag;
+  a.rec = (BandRec*)b.rec;
+  a.nitems = b.nitems;
+  hipLaunchKernelGGL(band_batch_weights_kernel<F>, dim3((unsigned)b.nslots), dim3(256), 0, s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const size_t lds = band_lds_bytes<F, 2, 4, 1, false>((b.hmax + 15) / 16 * 16);
+  if (lds > 65536) {
+    e = hipFuncSetAttribute((const void*)band_batch_kernel<F>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(band_batch_kernel<F>, dim3((unsigned)b.nitems), dim3(256), (unsigned)lds, s,
+                     a);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(band_batch_cone_kernel<F>, dim3((unsigned)std::min(b.nitems, 1024)),
+                     dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_band_batch(const BandBatch& b, hipStream_t s) {
+  if (b.hmax > kBandMaxReach || b.nitems < 1) return hipErrorInvalidValue;
+  return b.dtype == 0 ? band_batch<float>(b, s) : band_batch<double>(b, s);
+}
+
 }  // namespace heat1d

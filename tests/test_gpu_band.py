@@ -10,7 +10,7 @@ import torch
 import oracle
 import workloads
 from paper_1510_08982_amd import abi
-from paper_1510_08982_amd.heat import SyncPlan
+from paper_1510_08982_amd.heat import BatchedPlan, SyncPlan
 from _helpers import normwise, tol_for, torch_dtype, np_dtype, print_case
 
 pytestmark = pytest.mark.gpu
@@ -118,3 +118,38 @@ def test_band_passes_replay_in_a_graph():
         assert torch.equal(out, want[i])
         _ = SyncPlan(N, torch.float32).run(xs[2], 0.3, 0.0, 0.0, 64)   # eager work in between
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dt", ["f32", "f64"])
+def test_batched_band_rods_match_oracle(dt):
+    """Rods on both sides of the step count where band passes begin, lengths
+    around the tiles, one rod with a NaN."""
+    f = np_dtype(dt)
+    n = np.array([3, 4, 17, 255, 256, 257, 600, 2047, 2048, 2049, 4100, 9001, 20000, 5000, 1000])
+    K = np.array([448, 5000, 447, 449, 900, 5100 if dt == "f32" else 20000, 1, 600, 2000, 447,
+                  3000, 500, 700, 460, 448])
+    rng = np.random.default_rng(7)
+    r = workloads.as_dtype(np.append(rng.uniform(0.05, 0.5, n.size - 2), [0.5, 0.05]), f)
+    c1, cN = (workloads.as_dtype(rng.uniform(-1, 1, n.size), f) for _ in range(2))
+    off = np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
+    u0 = workloads.as_dtype(rng.uniform(-1, 1, int(off[-1])), f)
+    print_case(test="batched_band", dt=dt)
+    with BatchedPlan(n, K, torch_dtype(dt)) as plan:
+        assert "band_rods=12" in plan.describe()
+        args = [dev(off, "f64").to(torch.int64)] + [
+            torch.from_numpy(np.ascontiguousarray(x)).to(DEV) for x in (r, c1, cN)] + [
+            torch.from_numpy(K.astype(np.int32)).to(DEV)]
+        got = plan.run(dev(u0, dt), *args).cpu().numpy()
+        x = u0.astype(f)
+        x[off[11] + 4000] = np.nan
+        bad = plan.run(dev(x, dt), *args).cpu().numpy()
+    for b in range(n.size):
+        sl = slice(off[b], off[b + 1])
+        ref = oracle.sync(u0[sl], r[b], c1[b], cN[b], int(K[b]))
+        err = normwise(got[sl], ref)
+        print(f"  rod {b}: N={n[b]} K={K[b]} normwise error {err:.3e}")
+        assert err <= tol_for(dt)
+        if b != 11:
+            assert np.array_equal(bad[sl], got[sl])
+    i = np.arange(n[11])
+    assert np.array_equal(np.isnan(bad[off[11]:off[12]]), np.abs(i - 4000) <= K[11])

@@ -289,6 +289,41 @@ AdjLayout adjoint_layout(heat1d_plan_t p, int64_t K) {
   a.part_off = a.lam_off + a.state_bytes;
   a.rod_off = a.part_off + align_up((size_t)std::max<int64_t>(a.nlaunch, 1) * p->nrods *
                                     std::max<int64_t>(a.gs.tiles_per_rod, 1) * 8);
+// The FP64 adjoint by band passes, on plans that name no synchronous kernel (the
+// FP32 gradients stay those of the stepped states: dL/dr sums their roundings,
+// 3e-7 of it, in double).  All
+// the matrices of the run commute: with A the step and D the second difference,
+// u(K) = A^K u0 (ends included), lambda(0) = A^K gK and
+//   dL/dr = sum_k lambda(k+1) . D u(k) = K gK . (D A^(K-1) u0),
+// so the forward pass leaves z = D A^(K-1) u0 (one state) in the workspace in
+// place of the checkpoints, and the backward pass is one product and one dot
+// product.  z comes from weights of its own, not from differences of u(K),
+// whose rounding would be as large as z.
+struct BandAdjLayout {
+  size_t z_off, ping_off, spare_off, scr_off, part_off, rod_off, total;
+};
+
+bool band_adjoint(heat1d_plan_t p) {
+  return p->dtype == HEAT1D_F64 && p->opts.sync_kernel == HEAT1D_SYNC_AUTO &&
+         band_applies(p->dtype, p->N, p->nrods);
+}
+
+BandAdjLayout band_adjoint_layout(heat1d_plan_t p, int64_t K) {
+  BandAdjLayout a{};
+  const size_t st = align_up((size_t)p->N * p->nrods * esize(p->dtype));
+  // r = 1/2 reaches furthest: no r takes more passes
+  const bool one = band_run(p->dtype, 0.5, K).passes <= 1;
+  a.z_off = 0;
+  a.ping_off = st;
+  a.spare_off = a.ping_off + (one ? 0 : st);
+  a.scr_off = a.spare_off + (one ? 0 : st);
+  a.part_off = a.scr_off + band_scratch_bytes(p->N, p->nrods);
+  a.rod_off = a.part_off +
+              align_up((size_t)band_tiles(p->dtype, p->N, p->nrods) * p->nrods * 8);
+  a.total = a.rod_off + align_up((size_t)p->nrods * 8);
+  return a;
+}
+
   // per-rod dL/dr when the plan reports their sum (opts.grad_sum)
   a.total = a.rod_off + align_up((size_t)p->nrods * 8);
   return a;
@@ -721,7 +756,7 @@ size_t heat1d_async_workspace_bytes(heat1d_plan_t p) {
 
 size_t heat1d_adjoint_workspace_bytes(heat1d_plan_t p, int64_t K) {
   if (!p || p->batched || K < 0) return 0;
-  return adjoint_layout(p, K).total;
+  return band_adjoint(p) ? band_adjoint_layout(p, K).total : adjoint_layout(p, K).total;
 }
 
 // Batched workspace: the three queues (int32, 256-byte aligned) and three heads.
@@ -1612,11 +1647,11 @@ int heat1d_forward_checkpointed(heat1d_plan_t p, const void* u0, void* uK, doubl
   if (periodic(p)) return HEAT1D_EUNSUPPORTED;
   if (K > INT32_MAX) return HEAT1D_EUNSUPPORTED;
   const AdjLayout L = adjoint_layout(p, K);
-  if (L.g.tiles_per_rod <= 0) return HEAT1D_EUNSUPPORTED;
+  if (!band && L.g.tiles_per_rod <= 0) return HEAT1D_EUNSUPPORTED;
   const size_t bytes = (size_t)p->N * p->nrods * esize(p->dtype);
   char* ws = (char*)workspace;
-  if (overlaps(ws, L.total, u0, bytes) ||
-      (uK && (overlaps(ws, L.total, uK, bytes) || overlaps(u0, uK, bytes))))
+  if (overlaps(ws, wsb, u0, bytes) ||
+      (uK && (overlaps(ws, wsb, uK, bytes) || overlaps(u0, uK, bytes))))
     return HEAT1D_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   const int64_t N = p->N, B = p->nrods;
@@ -1681,19 +1716,31 @@ int heat1d_backward_checkpointed(heat1d_plan_t p, const void* gK, double r, doub
   if (periodic(p)) return HEAT1D_EUNSUPPORTED;
   if (K > INT32_MAX) return HEAT1D_EUNSUPPORTED;
   const AdjLayout L = adjoint_layout(p, K);
-  if (L.g.tiles_per_rod <= 0 || L.gs.tiles_per_rod <= 0 || L.gsub.tiles_per_rod <= 0)
+  if (!band &&
+      (L.g.tiles_per_rod <= 0 || L.gs.tiles_per_rod <= 0 || L.gsub.tiles_per_rod <= 0))
     return HEAT1D_EUNSUPPORTED;
   const size_t bytes = (size_t)p->N * p->nrods * esize(p->dtype);
   char* ws = (char*)workspace;
   const size_t gb = (size_t)(p->opts.grad_sum ? 1 : p->nrods) * 8;
-  if (overlaps(gK, grad_u0, bytes) || overlaps(ws, L.total, gK, bytes) ||
-      overlaps(ws, L.total, grad_u0, bytes) || overlaps(grad_r, gb, ws, L.total) ||
+  if (overlaps(gK, grad_u0, bytes) || overlaps(ws, wsb, gK, bytes) ||
+      overlaps(ws, wsb, grad_u0, bytes) || overlaps(grad_r, gb, ws, wsb) ||
       overlaps(grad_r, gb, gK, bytes) || overlaps(grad_r, gb, grad_u0, bytes))
     return HEAT1D_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   const int64_t N = p->N, B = p->nrods;
   const int S2 = stretch_steps(p->dtype);
-  double* partials = (double*)(ws + L.part_off);
+  if (band && K > 0) {
+    const BandAdjLayout Z = band_adjoint_layout(p, K);
+    double* part = (double*)(ws + Z.part_off);
+    const int st = run_band(p, B, gK, grad_u0, r, 0.0, 0.0, K, ws + Z.ping_off, ws + Z.scr_off,
+                            nullptr, ws + Z.z_off, part, s);
+    if (st != HEAT1D_OK) return st;
+    const int64_t tiles = band_tiles(p->dtype, N, B);
+    // one sum over all tiles, or one for each rod
+    return hip_status(p->opts.grad_sum ? launch_reduce_partials(part, tiles * B, 1, grad_r, s)
+                                       : launch_reduce_partials(part, tiles, B, grad_r, s));
+  }
+  double* partials = (double*)(ws + (band ? band_adjoint_layout(p, K).part_off : L.part_off));
   if (K == 0) {
     hipError_t e = launch_impose_ends(p->dtype, gK, grad_u0, N, B, 0.0, 0.0, s);
     if (e != hipSuccess) return hip_status(e);
@@ -1748,20 +1795,30 @@ namespace {
 // Layout of the end-gradient workspace: w, the zero start, the ping-pong
 // state of its run, then the dot-product partials.
 struct EndsLayout {
-  size_t w_off, z_off, ping_off, part_off, rod_off, total;
+  size_t w_off, z_off, ping_off, part_off, rod_off, scr_off, total;
 };
 EndsLayout ends_layout(heat1d_plan_t p) {
   EndsLayout L{};
   const size_t st = align_up((size_t)p->N * esize(p->dtype));
+  const bool band = band_adjoint(p);
   L.w_off = 0;
   L.z_off = st;
   L.ping_off = 2 * st;
+  const size_t wsb = heat1d_adjoint_workspace_bytes(p, K);
   L.part_off = 3 * st;
   L.rod_off = L.part_off + align_up((size_t)2 * norm_partials(p->N, p->nrods) * 8);
   // per-rod dL/dc1 and dL/dcN when the plan reports their sums (opts.grad_sum)
-  L.total = L.rod_off + 2 * align_up((size_t)p->nrods * 8);
+  L.scr_off = L.rod_off + 2 * align_up((size_t)p->nrods * 8);
+  L.total = L.scr_off + band_scratch_bytes(p->N, 1);
   return L;
 }
+  if (band && K > 0) {
+    const BandAdjLayout Z = band_adjoint_layout(p, K);
+    const bool one = band_run(p->dtype, r, K).passes <= 1;
+    return run_band(p, B, u0, uK || one ? uK : ws + Z.spare_off, r, c1, cN, K, ws + Z.ping_off,
+                    ws + Z.scr_off, ws + Z.z_off, nullptr, nullptr, s);
+  }
+  if (band) return uK ? hip_status(launch_impose_ends(p->dtype, u0, uK, N, B, c1, cN, s)) : HEAT1D_OK;
 }  // namespace
 
 size_t heat1d_adjoint_ends_workspace_bytes(heat1d_plan_t p) {
@@ -1788,10 +1845,12 @@ int heat1d_adjoint_ends(heat1d_plan_t p, const void* gK, double r, int64_t K, do
   // of Eq.3 in (u0, c1, cN) it is du(K)/dc1, and its mirror image is du(K)/dcN
   hipError_t e = launch_zero(ws + L.z_off, L.ping_off - L.z_off, s);
   if (e != hipSuccess) return hip_status(e);
+  const bool band = band_adjoint(p);
   heat1d_plan_s one = *p;
   one.nrods = 1;
   one.timing = false;
   // one rod fills few CUs, so the run is bound by launches and per-step
+  const size_t wsb = heat1d_adjoint_workspace_bytes(p, K);
   // latency: 64-step passes over short (8 points per lane) tiles measured
   // fastest for a 2^16-point rod; smaller tiles for short rods, else steps
   int kern = HEAT1D_SYNC_STEP, T = 1, M = 4;
@@ -1800,8 +1859,12 @@ int heat1d_adjoint_ends(heat1d_plan_t p, const void* gK, double r, int64_t K, do
   } else if (tile_geometry(p->dtype, 4, 32, p->N).tiles_per_rod > 0) {
     kern = HEAT1D_SYNC_TILED, T = 32, M = 4;
   }
-  const int st = run_sync_impl(&one, ws + L.z_off, ws + L.w_off, r, 1.0, 0.0, K, ws + L.ping_off,
-                               s, kern, T, M, 1, 1);
+  const int st =
+      band_adjoint(&one) && K >= kBandFrom
+          ? run_band(&one, 1, ws + L.z_off, ws + L.w_off, r, 1.0, 0.0, K, ws + L.ping_off,
+                     ws + L.scr_off, nullptr, nullptr, nullptr, s)
+          : run_sync_impl(&one, ws + L.z_off, ws + L.w_off, r, 1.0, 0.0, K, ws + L.ping_off, s,
+                          kern, T, M, 1, 1);
   if (st != HEAT1D_OK) return st;
   double* g1 = grad_c1;
   double* gN = grad_cN;

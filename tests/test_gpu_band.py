@@ -10,7 +10,7 @@ import torch
 import oracle
 import workloads
 from paper_1510_08982_amd import abi
-from paper_1510_08982_amd.heat import BatchedPlan, SyncPlan
+from paper_1510_08982_amd.heat import AdjointPlan, BatchedPlan, SyncPlan
 from _helpers import normwise, tol_for, torch_dtype, np_dtype, print_case
 
 pytestmark = pytest.mark.gpu
@@ -153,3 +153,35 @@ def test_batched_band_rods_match_oracle(dt):
             assert np.array_equal(bad[sl], got[sl])
     i = np.arange(n[11])
     assert np.array_equal(np.isnan(bad[off[11]:off[12]]), np.abs(i - 4000) <= K[11])
+
+
+@pytest.mark.parametrize("N,B,K,r", [(3, 2, 1, 0.5), (100, 3, 400, 0.5), (257, 1, 2, 0.3),
+                                     (5001, 2, 700, 0.45), (2048, 300, 65, 0.25),
+                                     (300, 1, 150000, 0.5)])
+def test_band_adjoint_matches_oracle(N, B, K, r):
+    """dL/du0 and dL/dr by band passes (FP64): one step, rods shorter than the
+    reach, several rods, several passes; u(K) asked for and not."""
+    dt, f = "f64", np.float64
+    rng = np.random.default_rng(N + K)
+    # a loss whose sum for dL/dr does not cancel: gK against the state's own curvature
+    u0, gK = (workloads.as_dtype(rng.uniform(0, 1, (B, N)), f) for _ in range(2))
+    r, c1, cN = (workloads.as_dtype(x, f) for x in (r, 0.75, -0.5))
+    print_case(test="band_adjoint", dt=dt, N=N, B=B, K=K, r=r)
+    plan = AdjointPlan(N, K, torch_dtype(dt), nrods=B)
+    x, g = dev(u0.reshape(-1), dt), dev(gK.reshape(-1), dt)
+    gu, gr, uK = plan.adjoint(x, g, r, c1, cN, want_uK=True)
+    gu2, gr2, _ = plan.adjoint(x, g, r, c1, cN)
+    assert torch.equal(gu, gu2) and torch.equal(gr, gr2)
+    gu, gr, uK = (t.cpu().numpy() for t in (gu, gr, uK))
+    for b in sorted({0, B - 1}):
+        sl = slice(b * N, (b + 1) * N)
+        rgu, rgr = oracle.adjoint(u0[b], gK[b], r, c1, cN, K)
+        line = oracle.sync(u0[b], r, c1, cN, K)
+        assert normwise(uK[sl], line) <= tol_for(dt)
+        assert normwise(gu[sl], rgu) <= tol_for(dt)
+        # the sum's terms are K gK . D A^(K-1) u0: the tolerance on its magnitude
+        scale = max(abs(rgr), K * float(np.abs(gK[b]).max()) * float(
+            np.abs(np.diff(oracle.sync(u0[b], r, c1, cN, K - 1), 2)).sum()))
+        print(f"  rod {b}: dL/dr {gr[b]:.6e}, off {abs(gr[b] - rgr) / scale:.3e}")
+        assert abs(gr[b] - rgr) <= tol_for(dt) * scale
+        assert gu[sl][0] == 0 and gu[sl][-1] == 0

@@ -253,6 +253,13 @@ int heat1d_run_sync_observed(heat1d_plan_t plan, const void *u0, void *uK, doubl
  *     delta(k,p,side) = ((x >> 32) * (d+1)) >> 32,
  *     x = sm64(seed ^ sm64(((k*P + p) << 1) | side)), sm64 = SplitMix64 output
  *     function; reads before step 0 read step 0.  Deterministic.
+ *     On plans that leave opts.sync_kernel and opts.jitter open, runs of 448
+ *     steps or more without `stats`, whose subdomains are longer than twice the
+ *     reach of a stage of steps, go as independent strips about the subdomain
+ *     edges instead of subdomains that trade values (the same values: delays are
+ *     a function of the seed), the points between them by band passes
+ *     (HEAT1D_SYNC_AUTO) to rounding; a point that is not finite sends the run
+ *     back to the persistent kernel.
  *   mode HEAT1D_ASYNC_HARDWARE: the workgroup uses the newest value its
  *     neighbour has published (never newer than step k) and waits only while
  *     that value would be older than k - d.  Not reproducible run to run.

@@ -19,6 +19,7 @@
 #include "heat1d_ensemble.h"
 #include "heat1d_launch.h"
 #include "heat1d_observe.h"
+#include "heat1d_strips.h"
 #include "heat1d_weights.h"
 
 using namespace heat1d;
@@ -32,7 +33,6 @@ namespace {
 // 2^26 points 158 / 330 / 657 us against 200 / 242 / 271 (all FP32).
 constexpr int32_t kBandFrom = 64;
 
-constexpr size_t kAlign = 256;
 // The same for the rods of a batch, and for the long rods of an emulated
 // asynchronous run.  Shorter runs there agree bit for bit with one launch per
 // step, which callers compare them with, and they are short either way.
@@ -48,6 +48,7 @@ bool fp32_drifts(int dtype, double r, int64_t K) {
   return dtype == HEAT1D_F32 && (double)K * (1.0 + 0.1 / r) > 6200.0;
 }
 
+constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 size_t esize(int dtype) { return dtype == HEAT1D_F32 ? 4 : 8; }
 int vec_width(int dtype) { return dtype == HEAT1D_F32 ? 4 : 2; }
@@ -88,11 +89,11 @@ struct heat1d_plan_s {
   int32_t groups = 0;
   int32_t small_first = 0;  // workgroups that start with the group and wavefront queues
   bool tuned = false;       // the batched work order was chosen by timing
-  // timing of the dominant kernel
   // rods that take a band pass: their tiles, rod indices and weight offsets
   std::vector<BandItem> band_items;
   std::vector<int32_t> band_rods, band_woff;
   int32_t band_hmax = 0;
+  // timing of the dominant kernel
   bool timing = false;
   std::vector<EventPair> ev;
   size_t ev_used = 0;
@@ -236,6 +237,34 @@ size_t async_ring_bytes(heat1d_plan_t p, int P) {
   return align_up((size_t)P * 2 * Q * words * 8);
 }
 
+// Asynchronous workspace: the halo ring, the progress hints and the status
+// words, then what a run by strips needs: weights, a flag, the edges' histories
+// and a state to alternate with.  The whole of it stays within what the
+// allocation-free run has, so that both entry points take the same route: a
+// plan whose histories do not fit never runs by strips, one whose state does
+// not fit only where a single stage does.
+struct AsyncLayout {
+  size_t hint_off, err_off, base;          // base: without the strips
+  size_t w_off, flag_off, hist_off, ping_off, total;
+  bool strips, ping;
+};
+AsyncLayout async_layout(heat1d_plan_t p, int P) {
+  AsyncLayout a{};
+  a.hint_off = async_ring_bytes(p, P);
+  a.err_off = a.hint_off + align_up((size_t)P * 2 * 4);
+  a.base = a.err_off + align_up(2 * 4);
+  a.w_off = a.base;
+  a.flag_off = a.w_off + kBandWeightBytes;
+  a.hist_off = a.flag_off + align_up(4);
+  a.ping_off = a.hist_off + strip_history_bytes(p->dtype, P);
+  const size_t state = align_up((size_t)p->N * esize(p->dtype));
+  a.strips = P >= 2 && p->opts.sync_kernel == HEAT1D_SYNC_AUTO && p->opts.jitter == 0 &&
+             band_applies(p->dtype, p->N, 1) && a.ping_off <= kNoAllocScratchBytes;
+  a.ping = a.strips && a.ping_off + state <= kNoAllocScratchBytes;
+  a.total = a.ping ? a.ping_off + state : (a.strips ? a.ping_off : a.base);
+  return a;
+}
+
 // The periodic ring runs in the ensemble entry points (runs and their adjoint),
 // heat1d_run_sync / heat1d_autotune_sync / heat1d_run_sync_observed and the
 // asynchronous run; every other entry point is written for the Dirichlet rod.
@@ -260,35 +289,6 @@ struct AdjLayout {
   size_t ckpt_off, sub_off, lam_off, part_off, rod_off, total;
 };
 
-AdjLayout adjoint_layout(heat1d_plan_t p, int64_t K) {
-  AdjLayout a{};
-  const int S2 = stretch_steps(p->dtype);
-  // default: about sqrt(K) steps between checkpoints, rounded up to whole
-  // sub-stretches so that every sub-stretch but the run's last is full length
-  int S = p->ckpt_stride;
-  if (S <= 0) {
-    S = (int)std::ceil(std::sqrt((double)std::max<int64_t>(K, 1)));
-    S = (S + S2 - 1) / S2 * S2;
-  }
-  S = std::max(1, std::min(S, 480));
-  a.S = S;
-  a.nseg = K > 0 ? (K + S - 1) / S : 0;
-  a.nlaunch = 0;
-  for (int64_t j = 0; j < a.nseg; ++j) {
-    const int64_t len = std::min<int64_t>(S, K - j * S);
-    a.nlaunch += (len + S2 - 1) / S2;
-  }
-  a.g = tile_geometry(p->dtype, 32, S, p->N);
-  a.gsub = tile_geometry(p->dtype, 32, S2, p->N);
-  a.gs = stretch_geometry(p->dtype, p->N);
-  a.state_bytes = align_up((size_t)p->N * p->nrods * esize(p->dtype));
-  const int64_t nsub_max = (S + S2 - 1) / S2;
-  a.ckpt_off = 0;
-  a.sub_off = a.ckpt_off + (size_t)std::max<int64_t>(a.nseg, 1) * a.state_bytes;
-  a.lam_off = a.sub_off + (size_t)std::max<int64_t>(nsub_max - 1, 1) * a.state_bytes;
-  a.part_off = a.lam_off + a.state_bytes;
-  a.rod_off = a.part_off + align_up((size_t)std::max<int64_t>(a.nlaunch, 1) * p->nrods *
-                                    std::max<int64_t>(a.gs.tiles_per_rod, 1) * 8);
 // The FP64 adjoint by band passes, on plans that name no synchronous kernel (the
 // FP32 gradients stay those of the stepped states: dL/dr sums their roundings,
 // 3e-7 of it, in double).  All
@@ -324,6 +324,35 @@ BandAdjLayout band_adjoint_layout(heat1d_plan_t p, int64_t K) {
   return a;
 }
 
+AdjLayout adjoint_layout(heat1d_plan_t p, int64_t K) {
+  AdjLayout a{};
+  const int S2 = stretch_steps(p->dtype);
+  // default: about sqrt(K) steps between checkpoints, rounded up to whole
+  // sub-stretches so that every sub-stretch but the run's last is full length
+  int S = p->ckpt_stride;
+  if (S <= 0) {
+    S = (int)std::ceil(std::sqrt((double)std::max<int64_t>(K, 1)));
+    S = (S + S2 - 1) / S2 * S2;
+  }
+  S = std::max(1, std::min(S, 480));
+  a.S = S;
+  a.nseg = K > 0 ? (K + S - 1) / S : 0;
+  a.nlaunch = 0;
+  for (int64_t j = 0; j < a.nseg; ++j) {
+    const int64_t len = std::min<int64_t>(S, K - j * S);
+    a.nlaunch += (len + S2 - 1) / S2;
+  }
+  a.g = tile_geometry(p->dtype, 32, S, p->N);
+  a.gsub = tile_geometry(p->dtype, 32, S2, p->N);
+  a.gs = stretch_geometry(p->dtype, p->N);
+  a.state_bytes = align_up((size_t)p->N * p->nrods * esize(p->dtype));
+  const int64_t nsub_max = (S + S2 - 1) / S2;
+  a.ckpt_off = 0;
+  a.sub_off = a.ckpt_off + (size_t)std::max<int64_t>(a.nseg, 1) * a.state_bytes;
+  a.lam_off = a.sub_off + (size_t)std::max<int64_t>(nsub_max - 1, 1) * a.state_bytes;
+  a.part_off = a.lam_off + a.state_bytes;
+  a.rod_off = a.part_off + align_up((size_t)std::max<int64_t>(a.nlaunch, 1) * p->nrods *
+                                    std::max<int64_t>(a.gs.tiles_per_rod, 1) * 8);
   // per-rod dL/dr when the plan reports their sum (opts.grad_sum)
   a.total = a.rod_off + align_up((size_t)p->nrods * 8);
   return a;
@@ -381,6 +410,7 @@ int run_band(heat1d_plan_t p, int64_t nrods, const void* in, void* out, double r
              double cN, int64_t K, void* ping, void* scratch, void* z, const void* dot_with,
              double* dot, hipStream_t s) {
   BandPass b;
+  b.dot_scale = (double)K;
   b.dtype = p->dtype;
   b.r = p->dtype == HEAT1D_F32 ? (double)(float)r : r;
   const BandRun run = band_run(p->dtype, b.r, K);
@@ -451,7 +481,6 @@ int run_sync_impl(heat1d_plan_t p, const void* u0, void* uK, double r, double c1
   }
   if (K == 0) return hip_status(launch_impose_ends(p->dtype, u0, uK, N, B, c1, cN, s));
   if (kernel == HEAT1D_SYNC_RESIDENT) {
-  b.dot_scale = (double)K;
     EventPair* e = timing_begin(p, s);
     hipError_t err = launch_sync_resident(p->dtype, M, waves, u0, uK, N, B, K, r, c1, cN, s);
     timing_end(e, s);
@@ -536,6 +565,35 @@ void batched_assign(heat1d_plan_t p, int64_t t_wave, int64_t t_group) {
   }
 }
 
+// Take the rods of at least kBatchBandFrom steps out of the queues (by_work):
+// they run as band passes, in tiles, the most work first.  Room for the weights
+// of any r; a rod whose reach could pass kBandMaxReach stays in the queues, and
+// so does every rod of a plan that names a block size (opts.waves).
+void batched_split_band(heat1d_plan_t p) {
+  if (p->opts.waves > 0 || p->opts.sync_kernel != HEAT1D_SYNC_AUTO) return;
+  std::vector<int32_t> rest;
+  int64_t tiles = 0, w = 0;
+  for (int32_t b : p->by_work) {
+    const int h = band_reach(p->dtype, 0.5, std::max(p->Kh[b], 1));
+    const int64_t nt = (p->Nh[b] + kBandBatchTile - 1) / kBandBatchTile;
+    // r is known to the run only; 1/2 drifts least
+    if (p->Kh[b] < kBatchBandFrom || fp32_drifts(p->dtype, 0.5, p->Kh[b]) || h > kBandMaxReach || tiles + nt > (1 << 22) ||
+        w + h + 1 > INT32_MAX) {
+      rest.push_back(b);
+      continue;
+    }
+    for (int64_t t = 0; t < nt; ++t)
+      p->band_items.push_back({(int32_t)p->band_rods.size(), (int32_t)t});
+    p->band_rods.push_back(b);
+    p->band_woff.push_back((int32_t)w);
+    p->band_hmax = std::max(p->band_hmax, h);
+    tiles += nt;
+    w += h + 1;
+  }
+  p->band_woff.push_back((int32_t)w);
+  p->by_work = rest;
+}
+
 // Workgroups that take the group and wavefront queues first: about twice
 // those queues' share of the point updates (their rods keep fewer points per
 // wavefront busy per step), at most half the grid, all of it when no rod
@@ -600,35 +658,6 @@ int heat1d_plan_create(heat1d_plan_t* out, int64_t N, int32_t dtype, const heat1
   if (p->opts.watchdog_polls > 0) p->watchdog = p->opts.watchdog_polls;
   p->ckpt_stride = p->opts.ckpt_stride;
   default_sync_choice(p);
-// Take the rods of at least kBatchBandFrom steps out of the queues (by_work):
-// they run as band passes, in tiles, the most work first.  Room for the weights
-// of any r; a rod whose reach could pass kBandMaxReach stays in the queues, and
-// so does every rod of a plan that names a block size (opts.waves).
-void batched_split_band(heat1d_plan_t p) {
-  if (p->opts.waves > 0 || p->opts.sync_kernel != HEAT1D_SYNC_AUTO) return;
-  std::vector<int32_t> rest;
-  int64_t tiles = 0, w = 0;
-  for (int32_t b : p->by_work) {
-    const int h = band_reach(p->dtype, 0.5, std::max(p->Kh[b], 1));
-    const int64_t nt = (p->Nh[b] + kBandBatchTile - 1) / kBandBatchTile;
-    // r is known to the run only; 1/2 drifts least
-    if (p->Kh[b] < kBatchBandFrom || fp32_drifts(p->dtype, 0.5, p->Kh[b]) || h > kBandMaxReach || tiles + nt > (1 << 22) ||
-        w + h + 1 > INT32_MAX) {
-      rest.push_back(b);
-      continue;
-    }
-    for (int64_t t = 0; t < nt; ++t)
-      p->band_items.push_back({(int32_t)p->band_rods.size(), (int32_t)t});
-    p->band_rods.push_back(b);
-    p->band_woff.push_back((int32_t)w);
-    p->band_hmax = std::max(p->band_hmax, h);
-    tiles += nt;
-    w += h + 1;
-  }
-  p->band_woff.push_back((int32_t)w);
-  p->by_work = rest;
-}
-
   // explicit choices.  On an asynchronous plan (nsub > 0) with no explicit
   // synchronous kernel, waves and pts_per_lane shape the asynchronous kernel
   // only and the synchronous kernel keeps its defaults.
@@ -721,6 +750,7 @@ int heat1d_plan_batched(heat1d_plan_t* out, int32_t nrods, const int64_t* N_host
   std::stable_sort(p->by_work.begin(), p->by_work.end(), [&](int32_t a, int32_t b) {
     return (double)p->Nh[a] * p->Kh[a] > (double)p->Nh[b] * p->Kh[b];
   });
+  batched_split_band(p);
   p->groups = std::max(1, num_cus());
   batched_assign(p, wave_cap, group_cap);
   p->small_first = batched_rule_small_first(p);
@@ -750,8 +780,7 @@ size_t heat1d_sync_workspace_bytes(heat1d_plan_t p) {
 
 size_t heat1d_async_workspace_bytes(heat1d_plan_t p) {
   if (!p || p->batched) return 0;
-  const int P = plan_nsub(p);
-  return async_ring_bytes(p, P) + align_up((size_t)P * 2 * 4) + align_up(2 * 4);
+  return async_layout(p, plan_nsub(p)).total;
 }
 
 size_t heat1d_adjoint_workspace_bytes(heat1d_plan_t p, int64_t K) {
@@ -765,6 +794,23 @@ namespace {
 // rods are split (the autotuner re-splits them in place).
 size_t batched_queue_off(heat1d_plan_t p, int q) {
   return (size_t)q * align_up(p->Nh.size() * 4 + 4);
+}
+// Behind the queues and their heads: the tiles, rods and weight offsets of the
+// band passes, their flag, records and weights.
+struct BatchedBandLayout {
+  size_t items, rods, woff, flag, rec, w, total;
+};
+BatchedBandLayout batched_band_layout(heat1d_plan_t p) {
+  BatchedBandLayout L{};
+  L.items = batched_queue_off(p, 3) + align_up(3 * 4);
+  L.rods = L.items + align_up(p->band_items.size() * sizeof(BandItem));
+  L.woff = L.rods + align_up(p->band_rods.size() * 4);
+  L.flag = L.woff + align_up(p->band_woff.size() * 4);
+  L.rec = L.flag + align_up(4);
+  L.w = L.rec + align_up(p->band_items.size() * 8);
+  L.total = L.w + align_up((p->band_woff.empty() ? 0 : (size_t)p->band_woff.back()) *
+                           esize(p->dtype));
+  return L;
 }
 }  // namespace
 
@@ -785,7 +831,6 @@ double heat1d_last_kernel_ms(heat1d_plan_t plan, int64_t* launches) {
   if (!plan || plan->ev_used == 0) return -1.0;
   double total = 0.0;
   for (size_t i = 0; i < plan->ev_used; ++i) {
-  batched_split_band(p);
     if (hipEventSynchronize(plan->ev[i].b) != hipSuccess) return -1.0;
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, plan->ev[i].a, plan->ev[i].b) != hipSuccess) return -1.0;
@@ -830,23 +875,6 @@ int heat1d_run_sync_observed(heat1d_plan_t p, const void* u0, void* uK, double r
   if (K > INT32_MAX || p->nrods > 65535) return HEAT1D_EUNSUPPORTED;
   const int64_t N = p->N, B = p->nrods;
   const size_t bytes = (size_t)N * B * esize(p->dtype);
-// Behind the queues and their heads: the tiles, rods and weight offsets of the
-// band passes, their flag, records and weights.
-struct BatchedBandLayout {
-  size_t items, rods, woff, flag, rec, w, total;
-};
-BatchedBandLayout batched_band_layout(heat1d_plan_t p) {
-  BatchedBandLayout L{};
-  L.items = batched_queue_off(p, 3) + align_up(3 * 4);
-  L.rods = L.items + align_up(p->band_items.size() * sizeof(BandItem));
-  L.woff = L.rods + align_up(p->band_rods.size() * 4);
-  L.flag = L.woff + align_up(p->band_woff.size() * 4);
-  L.rec = L.flag + align_up(4);
-  L.w = L.rec + align_up(p->band_items.size() * 8);
-  L.total = L.w + align_up((p->band_woff.empty() ? 0 : (size_t)p->band_woff.back()) *
-                           esize(p->dtype));
-  return L;
-}
   const int64_t nobs = K / every + 1;
   const size_t nbytes = (size_t)B * nobs * 8;
   const size_t wsb = heat1d_observed_workspace_bytes(p);
@@ -1014,6 +1042,72 @@ int check_async(heat1d_plan_t p, const void* u0, const void* uK, double r, int64
   return HEAT1D_OK;
 }
 
+// How an asynchronous run goes by strips (stages = 0: it does not).  Emulated
+// runs without statistics only, of kBatchBandFrom steps or more.
+StripPlan strips_of(heat1d_plan_t p, int P, double r, double c1, double cN, int64_t K, int32_t d,
+                    int32_t mode, const int64_t* stats) {
+  StripPlan none;
+  const AsyncLayout L = async_layout(p, P);
+  if (!L.strips || mode != HEAT1D_ASYNC_EMULATED || stats || K < kBatchBandFrom ||
+      !std::isfinite(c1) || !std::isfinite(cN))
+    return none;
+  return strip_plan(p->dtype, p->N, P, r, K, d, L.ping ? K : 1, !fp32_drifts(p->dtype, r, K));
+}
+
+int run_strips(heat1d_plan_t p, const StripPlan& sp, const void* u0, void* uK, double r, double c1,
+               double cN, int64_t K, int32_t d, uint64_t seed, int P, char* ws,
+               const AsyncLayout& L, bool timed, hipStream_t s) {
+  BandPass b;
+  b.dtype = p->dtype;
+  b.N = p->N;
+  b.r = p->dtype == HEAT1D_F32 ? (double)(float)r : r;
+  b.c1 = c1;
+  b.cN = cN;
+  b.ring = periodic(p);
+  b.scratch = ws + L.w_off;
+  b.flag = (int32_t*)(ws + L.flag_off);
+  StripStage a;
+  a.dtype = p->dtype;
+  a.N = p->N;
+  a.P = P;
+  a.d = d;
+  a.sched = p->opts.delay_schedule;
+  a.ring = b.ring;
+  a.seed = seed;
+  a.r = r;
+  a.c1 = c1;
+  a.cN = cN;
+  a.M = sp.M;
+  a.cut = sp.cut;
+  a.history = ws + L.hist_off;
+  a.flag = b.flag;
+  for (int64_t i = 0; i < sp.stages; ++i) {
+    const int64_t T = std::min<int64_t>(sp.T, K - i * sp.T);
+    a.in = i == 0 ? u0 : a.out;
+    a.out = (sp.stages - 1 - i) % 2 == 0 ? uK : (void*)(ws + L.ping_off);
+    a.k0 = i * sp.T;
+    a.T = T;
+    hipError_t e = hipSuccess;
+    if (sp.cut > 0) {
+      // the points away from the edges
+      b.in = a.in;
+      b.out = a.out;
+      if (b.T != T) {
+        b.T = T;
+        e = launch_band_weights(b, s);
+        if (e != hipSuccess) return hip_status(e);
+      }
+      e = launch_band_pass(b, s);
+      if (e != hipSuccess) return hip_status(e);
+    }
+    EventPair* ev = timed ? timing_begin(p, s) : nullptr;
+    e = launch_strips(a, s);
+    timing_end(ev, s);
+    if (e != hipSuccess) return hip_status(e);
+  }
+  return HEAT1D_OK;
+}
+
 // Enqueue one asynchronous run whose ring, hints and status words sit in `ws`
 // (heat1d_async_workspace_bytes(p) bytes, laid out as that call describes).
 int run_async_impl(heat1d_plan_t p, const void* u0, void* uK, double r, double c1, double cN,
@@ -1037,9 +1131,10 @@ int run_async_impl(heat1d_plan_t p, const void* u0, void* uK, double r, double c
   a.r = r;
   a.c1 = c1;
   a.cN = cN;
+  const AsyncLayout L = async_layout(p, P);
   a.ring = ws;
-  a.prog = (int32_t*)(ws + async_ring_bytes(p, P));
-  a.err = (int32_t*)(ws + async_ring_bytes(p, P) + align_up((size_t)P * 2 * 4));
+  a.prog = (int32_t*)(ws + L.hint_off);
+  a.err = (int32_t*)(ws + L.err_off);
   a.stats = stats;
   a.watchdog = p->watchdog;
   a.remap = (P % 8 == 0 && P >= 16) ? 1 : 0;
@@ -1051,8 +1146,22 @@ int run_async_impl(heat1d_plan_t p, const void* u0, void* uK, double r, double c
                 (long long)p->N, P, waves, M, d, mode == 0 ? "emulated" : "hardware",
                 a.periodic ? " ring" : "");
   p->desc = buf;
+  const StripPlan sp = strips_of(p, P, r, c1, cN, K, d, mode, stats);
+  if (sp.stages > 0) {
+    p->desc += " strips=" + std::to_string(sp.stages) + "x" + std::to_string(sp.T) +
+               " M=" + std::to_string(sp.M) + " cut=" + std::to_string(sp.cut);
+    a.only_if = (int32_t*)(ws + L.flag_off);
+  }
   hipError_t e = launch_async_prepare(a, s);
   if (e != hipSuccess) return hip_status(e);
+  if (sp.stages > 0) {
+    const int rc = run_strips(p, sp, u0, uK, r, c1, cN, K, d, seed, P, ws, L, timed, s);
+    if (rc != HEAT1D_OK) return rc;
+    // points that are not finite: the whole run again, step by step (the
+    // workgroups leave at once where there were none)
+    e = launch_async(a, s);
+    return e == hipErrorCooperativeLaunchTooLarge ? HEAT1D_EOCCUPANCY : hip_status(e);
+  }
   EventPair* ev = timed ? timing_begin(p, s) : nullptr;
   e = launch_async(a, s);
   timing_end(ev, s);
@@ -1085,7 +1194,7 @@ int heat1d_run_async_noalloc(heat1d_plan_t p, const void* u0, void* uK, double r
   int P = 0, waves = 0, M = 0;
   const int st = check_async(p, u0, uK, r, K, d, mode, &P, &waves, &M);
   if (st != HEAT1D_OK) return st;
-  if (heat1d_async_workspace_bytes(p) > kNoAllocScratchBytes) return HEAT1D_ESCRATCH;
+  if (async_layout(p, P).total > kNoAllocScratchBytes) return HEAT1D_ESCRATCH;
   if (status && (overlaps(status, 4, u0, (size_t)p->N * esize(p->dtype)) ||
                  overlaps(status, 4, uK, (size_t)p->N * esize(p->dtype))))
     return HEAT1D_EINVAL;
@@ -1095,8 +1204,7 @@ int heat1d_run_async_noalloc(heat1d_plan_t p, const void* u0, void* uK, double r
   const int rc = run_async_impl(p, u0, uK, r, c1, cN, K, d, seed, mode, (char*)ws, stats, P,
                                 waves, M, false, s);
   if (rc != HEAT1D_OK || !status) return rc;
-  const int32_t* err =
-      (const int32_t*)((char*)ws + async_ring_bytes(p, P) + align_up((size_t)P * 2 * 4));
+  const int32_t* err = (const int32_t*)((char*)ws + async_layout(p, P).err_off);
   return hip_status(launch_copy_status(err, status, s));
 }
 
@@ -1104,7 +1212,7 @@ int heat1d_async_status(heat1d_plan_t p, void* workspace, void* stream) {
   if (!p || !workspace) return HEAT1D_EINVAL;
   const int P = plan_nsub(p);
   const char* ws = (const char*)workspace;
-  const int32_t* err = (const int32_t*)(ws + async_ring_bytes(p, P) + align_up((size_t)P * 2 * 4));
+  const int32_t* err = (const int32_t*)(ws + async_layout(p, P).err_off);
   int32_t h = 0;
   hipStream_t s = (hipStream_t)stream;
   if (hipMemcpyAsync(&h, err, sizeof h, hipMemcpyDeviceToHost, s) != hipSuccess) return HEAT1D_EHIP;
@@ -1464,6 +1572,16 @@ int heat1d_batched_prepare(heat1d_plan_t p, void* workspace, void* stream) {
                        hipMemcpyHostToDevice, s) != hipSuccess)
       return HEAT1D_EHIP;
   }
+  if (!p->band_items.empty()) {
+    const BatchedBandLayout L = batched_band_layout(p);
+    if (hipMemcpyAsync(ws + L.items, p->band_items.data(), p->band_items.size() * sizeof(BandItem),
+                       hipMemcpyHostToDevice, s) != hipSuccess ||
+        hipMemcpyAsync(ws + L.rods, p->band_rods.data(), p->band_rods.size() * 4,
+                       hipMemcpyHostToDevice, s) != hipSuccess ||
+        hipMemcpyAsync(ws + L.woff, p->band_woff.data(), p->band_woff.size() * 4,
+                       hipMemcpyHostToDevice, s) != hipSuccess)
+      return HEAT1D_EHIP;
+  }
   // the host vectors must stay valid until the copies finish
   if (hipStreamSynchronize(s) != hipSuccess) return HEAT1D_EHIP;
   return HEAT1D_OK;
@@ -1507,6 +1625,40 @@ BatchedLaunch batched_args(heat1d_plan_t p, const void* u0, void* uK, const int6
   b.groups = p->groups;
   b.small_first = p->small_first;
   return b;
+}
+
+// The whole batch: the queues' rods in the persistent kernel, the others as
+// band passes.
+hipError_t launch_batch(heat1d_plan_t p, const void* u0, void* uK, const int64_t* offsets,
+                        const double* r, const double* c1, const double* cN, const int32_t* K,
+                        void* workspace, hipStream_t s) {
+  char* ws = (char*)workspace;
+  hipError_t e = hipSuccess;
+  if (!p->band_items.empty()) {
+    const BatchedBandLayout L = batched_band_layout(p);
+    BandBatch b;
+    b.dtype = p->dtype;
+    b.in = u0;
+    b.out = uK;
+    b.offsets = offsets;
+    b.r = r;
+    b.c1 = c1;
+    b.cN = cN;
+    b.K = K;
+    b.items = (const BandItem*)(ws + L.items);
+    b.rods = (const int32_t*)(ws + L.rods);
+    b.woff = (const int32_t*)(ws + L.woff);
+    b.w = ws + L.w;
+    b.flag = (int32_t*)(ws + L.flag);
+    b.rec = ws + L.rec;
+    b.nitems = (int32_t)p->band_items.size();
+    b.nslots = (int32_t)p->band_rods.size();
+    b.hmax = p->band_hmax;
+    e = launch_band_batch(b, s);
+  }
+  if (e == hipSuccess && !p->by_work.empty())
+    e = launch_batched(batched_args(p, u0, uK, offsets, r, c1, cN, K, workspace), s);
+  return e;
 }
 
 }  // namespace
@@ -1606,16 +1758,6 @@ int heat1d_autotune_batched(heat1d_plan_t p, const void* u0, void* uK, const int
   const int up = heat1d_batched_prepare(p, workspace, stream);
   if (rc == HEAT1D_OK) rc = up;
   hipEventDestroy(ev[0]);
-  if (!p->band_items.empty()) {
-    const BatchedBandLayout L = batched_band_layout(p);
-    if (hipMemcpyAsync(ws + L.items, p->band_items.data(), p->band_items.size() * sizeof(BandItem),
-                       hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(ws + L.rods, p->band_rods.data(), p->band_rods.size() * 4,
-                       hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(ws + L.woff, p->band_woff.data(), p->band_woff.size() * 4,
-                       hipMemcpyHostToDevice, s) != hipSuccess)
-      return HEAT1D_EHIP;
-  }
   hipEventDestroy(ev[1]);
   describe(p);
   if (best_ms) *best_ms = best;
@@ -1646,55 +1788,30 @@ int heat1d_forward_checkpointed(heat1d_plan_t p, const void* u0, void* uK, doubl
   if (!p || p->batched || !u0 || !workspace || !r_ok(r) || K < 0) return HEAT1D_EINVAL;
   if (periodic(p)) return HEAT1D_EUNSUPPORTED;
   if (K > INT32_MAX) return HEAT1D_EUNSUPPORTED;
+  const bool band = band_adjoint(p);
   const AdjLayout L = adjoint_layout(p, K);
   if (!band && L.g.tiles_per_rod <= 0) return HEAT1D_EUNSUPPORTED;
   const size_t bytes = (size_t)p->N * p->nrods * esize(p->dtype);
+  const size_t wsb = heat1d_adjoint_workspace_bytes(p, K);
   char* ws = (char*)workspace;
   if (overlaps(ws, wsb, u0, bytes) ||
       (uK && (overlaps(ws, wsb, uK, bytes) || overlaps(u0, uK, bytes))))
     return HEAT1D_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   const int64_t N = p->N, B = p->nrods;
+  if (band && K > 0) {
+    const BandAdjLayout Z = band_adjoint_layout(p, K);
+    const bool one = band_run(p->dtype, r, K).passes <= 1;
+    return run_band(p, B, u0, uK || one ? uK : ws + Z.spare_off, r, c1, cN, K, ws + Z.ping_off,
+                    ws + Z.scr_off, ws + Z.z_off, nullptr, nullptr, s);
+  }
+  if (band) return uK ? hip_status(launch_impose_ends(p->dtype, u0, uK, N, B, c1, cN, s)) : HEAT1D_OK;
   hipError_t e = launch_impose_ends(p->dtype, u0, ws + L.ckpt_off, N, B, c1, cN, s);
   if (e != hipSuccess) return hip_status(e);
   if (K == 0) {
     if (uK) return hip_status(launch_impose_ends(p->dtype, u0, uK, N, B, c1, cN, s));
     return HEAT1D_OK;
   }
-// The whole batch: the queues' rods in the persistent kernel, the others as
-// band passes.
-hipError_t launch_batch(heat1d_plan_t p, const void* u0, void* uK, const int64_t* offsets,
-                        const double* r, const double* c1, const double* cN, const int32_t* K,
-                        void* workspace, hipStream_t s) {
-  char* ws = (char*)workspace;
-  hipError_t e = hipSuccess;
-  if (!p->band_items.empty()) {
-    const BatchedBandLayout L = batched_band_layout(p);
-    BandBatch b;
-    b.dtype = p->dtype;
-    b.in = u0;
-    b.out = uK;
-    b.offsets = offsets;
-    b.r = r;
-    b.c1 = c1;
-    b.cN = cN;
-    b.K = K;
-    b.items = (const BandItem*)(ws + L.items);
-    b.rods = (const int32_t*)(ws + L.rods);
-    b.woff = (const int32_t*)(ws + L.woff);
-    b.w = ws + L.w;
-    b.flag = (int32_t*)(ws + L.flag);
-    b.rec = ws + L.rec;
-    b.nitems = (int32_t)p->band_items.size();
-    b.nslots = (int32_t)p->band_rods.size();
-    b.hmax = p->band_hmax;
-    e = launch_band_batch(b, s);
-  }
-  if (e == hipSuccess && !p->by_work.empty())
-    e = launch_batched(batched_args(p, u0, uK, offsets, r, c1, cN, K, workspace), s);
-  return e;
-}
-
   for (int64_t j = 0; j < L.nseg; ++j) {
     const int steps = (int)std::min<int64_t>(L.S, K - j * L.S);
     const void* in = ws + L.ckpt_off + j * L.state_bytes;
@@ -1715,11 +1832,13 @@ int heat1d_backward_checkpointed(heat1d_plan_t p, const void* gK, double r, doub
     return HEAT1D_EINVAL;
   if (periodic(p)) return HEAT1D_EUNSUPPORTED;
   if (K > INT32_MAX) return HEAT1D_EUNSUPPORTED;
+  const bool band = band_adjoint(p);
   const AdjLayout L = adjoint_layout(p, K);
   if (!band &&
       (L.g.tiles_per_rod <= 0 || L.gs.tiles_per_rod <= 0 || L.gsub.tiles_per_rod <= 0))
     return HEAT1D_EUNSUPPORTED;
   const size_t bytes = (size_t)p->N * p->nrods * esize(p->dtype);
+  const size_t wsb = heat1d_adjoint_workspace_bytes(p, K);
   char* ws = (char*)workspace;
   const size_t gb = (size_t)(p->opts.grad_sum ? 1 : p->nrods) * 8;
   if (overlaps(gK, grad_u0, bytes) || overlaps(ws, wsb, gK, bytes) ||
@@ -1800,11 +1919,9 @@ struct EndsLayout {
 EndsLayout ends_layout(heat1d_plan_t p) {
   EndsLayout L{};
   const size_t st = align_up((size_t)p->N * esize(p->dtype));
-  const bool band = band_adjoint(p);
   L.w_off = 0;
   L.z_off = st;
   L.ping_off = 2 * st;
-  const size_t wsb = heat1d_adjoint_workspace_bytes(p, K);
   L.part_off = 3 * st;
   L.rod_off = L.part_off + align_up((size_t)2 * norm_partials(p->N, p->nrods) * 8);
   // per-rod dL/dc1 and dL/dcN when the plan reports their sums (opts.grad_sum)
@@ -1812,13 +1929,6 @@ EndsLayout ends_layout(heat1d_plan_t p) {
   L.total = L.scr_off + band_scratch_bytes(p->N, 1);
   return L;
 }
-  if (band && K > 0) {
-    const BandAdjLayout Z = band_adjoint_layout(p, K);
-    const bool one = band_run(p->dtype, r, K).passes <= 1;
-    return run_band(p, B, u0, uK || one ? uK : ws + Z.spare_off, r, c1, cN, K, ws + Z.ping_off,
-                    ws + Z.scr_off, ws + Z.z_off, nullptr, nullptr, s);
-  }
-  if (band) return uK ? hip_status(launch_impose_ends(p->dtype, u0, uK, N, B, c1, cN, s)) : HEAT1D_OK;
 }  // namespace
 
 size_t heat1d_adjoint_ends_workspace_bytes(heat1d_plan_t p) {
@@ -1845,12 +1955,10 @@ int heat1d_adjoint_ends(heat1d_plan_t p, const void* gK, double r, int64_t K, do
   // of Eq.3 in (u0, c1, cN) it is du(K)/dc1, and its mirror image is du(K)/dcN
   hipError_t e = launch_zero(ws + L.z_off, L.ping_off - L.z_off, s);
   if (e != hipSuccess) return hip_status(e);
-  const bool band = band_adjoint(p);
   heat1d_plan_s one = *p;
   one.nrods = 1;
   one.timing = false;
   // one rod fills few CUs, so the run is bound by launches and per-step
-  const size_t wsb = heat1d_adjoint_workspace_bytes(p, K);
   // latency: 64-step passes over short (8 points per lane) tiles measured
   // fastest for a 2^16-point rod; smaller tiles for short rods, else steps
   int kern = HEAT1D_SYNC_STEP, T = 1, M = 4;

@@ -105,6 +105,9 @@ struct AsyncLaunch {
   int32_t jitter;  // seeded pause per step: 0..jitter short sleeps (0 = none)
   int32_t periodic;  // 1: ring of Section 5.3, subdomains 0 and P-1 neighbours (P >= 2)
   int32_t sched;     // emulated mode: delay schedule (sched_delay in heat1d_delays.h)
+  int32_t* only_if = nullptr;  // not NULL: launch_async_prepare clears it, and
+                               // launch_async's run happens only if it has been
+                               // raised since
 };
 bool async_supports(int dtype, int M);
 hipError_t launch_async_prepare(const AsyncLaunch& a, hipStream_t s);

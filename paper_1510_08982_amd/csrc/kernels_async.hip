@@ -53,6 +53,7 @@ struct AsyncDev {
   int32_t jitter;
   int32_t periodic;  // 1: the rod is a ring and subdomains 0 and P-1 are neighbours
   int32_t sched;     // emulated mode: the delay schedule
+  const int32_t* only_if;  // not NULL: the run is wanted only where this is not 0
 };
 
 template <typename F> struct SlotWords;
@@ -222,6 +223,7 @@ __device__ __forceinline__ bool halo_resolve(const AsyncDev& a, int k, int p, in
 // carries no register-indexed writes or reads of it.
 template <typename F, int M, int kMode, bool kStats, bool kRagged>
 __global__ __launch_bounds__(1024) void async_kernel(const AsyncDev a) {
+  if (a.only_if != nullptr && *a.only_if == 0) return;  // every workgroup alike
   __shared__ F lds[4 * 16];
   __shared__ int s_abort_at;
   __shared__ unsigned long long s_stats[kMaxStatDelay + 3];
@@ -395,13 +397,14 @@ __global__ __launch_bounds__(1024) void async_kernel(const AsyncDev a) {
 }
 
 __global__ void async_prepare_kernel(uint64_t* ring, int64_t nwords, int32_t* hint, int64_t nhint,
-                                     int32_t* err) {
+                                     int32_t* err, int32_t* flag) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nwords; i += stride)
     ring[i] = ~0ull;  // tag 0xffffffff: no step published yet
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nhint; i += stride)
     hint[i] = -1;
   if (blockIdx.x == 0 && threadIdx.x < 2) err[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && flag != nullptr) *flag = 0;
 }
 
 __global__ void delay_schedule_kernel(int32_t P, int64_t K, int32_t d, uint64_t seed,
@@ -530,7 +533,8 @@ hipError_t launch_async_prepare(const AsyncLaunch& a, hipStream_t s) {
   if (blocks > 4096) blocks = 4096;
   if (blocks < 1) blocks = 1;
   hipLaunchKernelGGL(async_prepare_kernel, dim3((unsigned)blocks), dim3(256), 0, s,
-                     reinterpret_cast<uint64_t*>(a.ring), words, a.prog, (int64_t)a.P * 2, a.err);
+                     reinterpret_cast<uint64_t*>(a.ring), words, a.prog, (int64_t)a.P * 2, a.err,
+                     a.only_if);
   return hipGetLastError();
 }
 
@@ -560,6 +564,7 @@ hipError_t launch_async(const AsyncLaunch& a, hipStream_t s) {
   d.jitter = a.jitter;
   d.periodic = a.periodic;
   d.sched = a.sched;
+  d.only_if = a.only_if;
   void* args[] = {&d};
   return hipLaunchCooperativeKernel(fn, dim3((unsigned)a.P), dim3((unsigned)(a.waves * kWave)),
                                     args, 0, s);

@@ -10,7 +10,7 @@ import torch
 import oracle
 import workloads
 from paper_1510_08982_amd import abi
-from paper_1510_08982_amd.heat import AdjointPlan, BatchedPlan, SyncPlan
+from paper_1510_08982_amd.heat import AdjointPlan, AsyncPlan, BatchedPlan, SyncPlan
 from _helpers import normwise, tol_for, torch_dtype, np_dtype, print_case
 
 pytestmark = pytest.mark.gpu
@@ -185,3 +185,71 @@ def test_band_adjoint_matches_oracle(N, B, K, r):
         print(f"  rod {b}: dL/dr {gr[b]:.6e}, off {abs(gr[b] - rgr) / scale:.3e}")
         assert abs(gr[b] - rgr) <= tol_for(dt) * scale
         assert gu[sl][0] == 0 and gu[sl][-1] == 0
+
+
+STRIP_CASES = [  # (dt, N, P, d, K, r): one stage and several, with band passes and without
+    ("f64", 4096, 16, 3, 2000, 0.4), ("f32", 4096, 16, 3, 2000, 0.4),
+    ("f32", 1 << 18, 16, 16, 5000, 0.45), ("f64", 70001, 13, 4, 900, 0.5),
+    ("f32", 70001, 2, 63, 448, 0.3), ("f64", 30011, 9, 1, 3000, 0.45),
+    ("f32", 100003, 300, 5, 448, 0.05), ("f64", 20000, 4, 7, 6000, 0.5),
+]
+
+
+@pytest.mark.parametrize("ring", [False, True])
+@pytest.mark.parametrize("dt,N,P,d,K,r", STRIP_CASES)
+def test_strips_match_oracle(dt, N, P, d, K, r, ring):
+    """The emulated asynchronous run as strips about the subdomain edges, every
+    point against the oracle; the allocation-free entry point bit for bit."""
+    f = np_dtype(dt)
+    u0 = workloads.as_dtype(np.random.default_rng(N + K).uniform(-1, 1, N), f)
+    r, c1, cN = (workloads.as_dtype(x, f) for x in (r, 1.0, -1.0))
+    x = dev(u0, dt)
+    with AsyncPlan(N, P, torch_dtype(dt), max_delay=d, periodic=ring) as plan:
+        out = plan.run(x, r, c1, cN, K, d, 42)
+        print_case(test="strips", dt=dt, N=N, P=P, d=d, K=K, ring=ring, plan=plan.describe())
+        assert "strips=" in plan.describe()
+        assert plan.status() == abi.HEAT1D_OK
+        same = torch.empty_like(out)
+        abi.heat1d_run_async_noalloc(plan.handle, x.data_ptr(), same.data_ptr(), r, c1, cN, K, d,
+                                     42, abi.HEAT1D_ASYNC_EMULATED, None, None,
+                                     torch.cuda.current_stream().cuda_stream)
+        assert torch.equal(out, same)
+    got = out.cpu().numpy()
+    if ring:
+        ref = oracle.async_ensemble(u0, r, 0.0, 0.0, K, P, d, [42], every=K, periodic=True)[0][0]
+    else:
+        ref = oracle.async_emulated(u0, r, c1, cN, K, P, d, 42)
+        assert got[0] == f(c1) and got[-1] == f(cN)
+    err = normwise(got, ref)
+    print(f"  normwise error {err:.3e}")
+    assert err <= tol_for(dt)
+
+
+@pytest.mark.parametrize("dt", ["f32", "f64"])
+@pytest.mark.parametrize("sched", [1, 2])
+def test_strips_under_fixed_schedules_match_oracle(sched, dt):
+    N, P, d, K = 50000, 20, 9, 1500
+    f = np_dtype(dt)
+    u0 = workloads.as_dtype(np.random.default_rng(3).uniform(-1, 1, N), f)
+    r = workloads.as_dtype(0.45, f)
+    with AsyncPlan(N, P, torch_dtype(dt), max_delay=d, delay_schedule=sched) as plan:
+        got = plan.run(dev(u0, dt), r, 1.0, -1.0, K, d, 42).cpu().numpy()
+        print_case(test="strips_sched", dt=dt, sched=sched, plan=plan.describe())
+        assert "strips=" in plan.describe()
+    ref = oracle.async_emulated(u0, r, 1.0, -1.0, K, P, d, 42, schedule=sched)
+    assert normwise(got, ref) <= tol_for(dt)
+
+
+def test_strips_leave_points_that_are_not_finite_to_the_stepping_run():
+    N, P, d, K = 50000, 20, 4, 700
+    u0 = np.random.default_rng(3).uniform(-1, 1, N)
+    for i in (26000, 30000):   # near an edge (2500-point subdomains) and on one
+        u0[i] = np.inf
+    x = dev(u0, "f32")
+    with AsyncPlan(N, P, torch.float32, max_delay=d) as plan:
+        got = plan.run(x, 0.4, 1.0, -1.0, K, d, 42)
+        assert "strips=" in plan.describe()
+        st = torch.zeros(d + 3, dtype=torch.int64, device=DEV)
+        ref = plan.run(x, 0.4, 1.0, -1.0, K, d, 42, stats=st)   # statistics: stepped
+        assert "strips=" not in plan.describe()
+    assert torch.equal(got.view(torch.int32), ref.view(torch.int32))

@@ -522,6 +522,517 @@ __global__ __launch_bounds__(kAdjThreads) void ensemble_adjoint_kernel(EnsAdjDev
                   ((wpart[4] + wpart[5]) + (wpart[6] + wpart[7]));
 }
 
+// ---------------------------------------------------------------------------
+// Short rods: one wavefront steps, seven prepare its reads.
+//
+// The kernels above spend their time on one workgroup barrier per step and on
+// the delay draws (a dozen quarter-rate multiplies each) that every wavefront
+// makes before it.  Where the rod fits one wavefront (M points per lane), the
+// steps need no barrier at all: wavefront 0 steps, and the other seven work a
+// chunk of kChunk steps ahead of it -- drawing the delays, which do not depend
+// on the state, and turning each into what the stepping wavefront uses directly
+// (forward: the LDS address of the value to read) -- and a chunk behind it,
+// taking norms and snapshots from the states it left in LDS.  One barrier per
+// chunk.  The values are those of the kernels above bit for bit; norms and
+// dL/dr are summed in another order, in double as there.
+//
+// What bounds it: the chain of a step (an LDS read at a prepared address, two
+// adds and two multiply-adds, the LDS write that the next step reads), about
+// 330 clocks of one wavefront, of which 690 us are made at K = 5000 and up to
+// 256 members, a member a compute unit.  300 members of N = 100, d = 3,
+// K = 5000, one point a subdomain, FP64, a norm a step: 3530 -> 1190 us (two
+// members on 44 of the compute units, whose prepared draws share its vector
+// units); the adjoint's two passes 6455 -> 2590 us.  With twelve wavefronts the
+// draws came sooner (690 -> 650 us alone) but two members on a compute unit got in
+// each other's way (1190 -> 1710 us).  The adjoint kernel is held to 128
+// registers up to two points a lane, so that two members fit a compute unit:
+// with its second differences prefetched into the stepping wavefront's own
+// registers (148 of them) the two ran one after the other (1500 -> 1875 us).
+// ---------------------------------------------------------------------------
+constexpr int kChunk = 8;
+constexpr int kHist = 2 * kChunk;  // states in LDS: this chunk's and the last one's
+constexpr int kWaveWaves = 8;
+constexpr int kWaveThreads = kWaveWaves * kWave;
+constexpr int kHelpers = kWaveWaves - 1;
+constexpr int kWaveMaxM = 4;
+
+template <int M>
+struct WaveShape {
+  static constexpr int kPoints = kWave * M;
+  static constexpr int kPitch = kPoints + 2;   // elements of a state in LDS
+  static constexpr int kEntries = 2 * kPoints;  // reads of a step
+};
+
+// Points per lane with which a rod runs on one stepping wavefront, 0: it does
+// not.  The delays must end inside the chunk before (kHist states are kept).  At
+// kWaveMaxM points a lane the adjoint's tables take 109 KiB of LDS, and what a
+// lane steps by itself catches up with a barrier a step: 512 members, N = P =
+// 258, d = 3, K = 1000, FP64: 730 -> 623 us, both passes 1797 -> 1552 us, where
+// 8 members of N = P = 20 go from 390 to 98 and from 966 to 217 us.
+static int ensemble_wave_m(int64_t N, int d, bool ring) {
+  const int64_t count = ring ? N : N - 2;
+  if (d >= kChunk || count < 1) return 0;
+  // the ring's adjoint keeps a copy of point 0 behind point N-1
+  const int64_t m = (count + (ring ? 1 : 0) + kWave - 1) / kWave;
+  return m <= kWaveMaxM ? (int)m : 0;
+}
+
+// A thread's way through the (step, item) pairs t, t + nt, ... of a chunk with m
+// items a step; the two divisions are made once per launch.
+struct Walk {
+  int s, x, ds, dx, m;
+  __device__ __forceinline__ Walk(int t, int nt, int m_) {
+    m = m_ > 0 ? m_ : 1;
+    s = t / m;
+    x = t - s * m;
+    ds = nt / m;
+    dx = nt - ds * m;
+  }
+  __device__ __forceinline__ void next() {
+    s += ds;
+    x += dx;
+    if (x >= m) {
+      x -= m;
+      ++s;
+    }
+  }
+};
+
+template <typename F, int M, bool kRing>
+__global__ __launch_bounds__(kWaveThreads)
+__attribute__((amdgpu_waves_per_eu(4))) void ensemble_wave_kernel(EnsDev a) {
+  using S = WaveShape<M>;
+  constexpr int kRow = S::kPitch * (int)sizeof(F);  // bytes of a state
+  __shared__ __align__(16) F hist[kHist * S::kPitch];
+  __shared__ __align__(16) uint32_t s_table[2][kChunk][S::kEntries];  // byte offsets into hist
+  __shared__ uint32_t s_read[S::kEntries];
+  __shared__ uint16_t s_draw[S::kEntries + 4];
+  constexpr uint32_t kAcross = 0x80000000u;
+  constexpr uint16_t kNoRead = 0xffff;
+  const int N = a.N, P = a.P, K = a.K;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid / kWave);
+  const int64_t e = blockIdx.x;
+  const uint64_t seed = a.seeds[e];
+  const F* __restrict__ u0 = static_cast<const F*>(a.u0) + e * N;
+  const F c1 = (F)a.c1, cN = (F)a.cN;
+  constexpr int first = kRing ? 0 : 1;
+  const int last = kRing ? N : N - 1;  // updated points [first, last)
+  const int count = last - first;
+  // reads with a delay: none with d = 0 or one subdomain
+  const int ndraw = a.d > 0 && P > 1 ? 2 * P : 0;
+  const uint32_t dp1 = (uint32_t)a.d + 1;
+
+  // Point t >= count of the stepping wavefront stands still: it reads the cell
+  // behind the last updated point twice, which holds what it holds itself (the
+  // right end, or 0 on the ring).
+  const F still = kRing ? F(0) : cN;
+  for (int i = tid; i < kHist * S::kPitch; i += kWaveThreads) {
+    const int q = i % S::kPitch;
+    hist[i] = q >= last ? still : (q < first ? c1 : F(0));
+  }
+  for (int i = tid; i < 2 * kChunk * S::kEntries; i += kWaveThreads)
+    (&s_table[0][0][0])[i] = (uint32_t)(last * (int)sizeof(F));
+  __syncthreads();
+  if (tid < S::kPoints && tid < count) hist[first + tid] = u0[first + tid];
+
+  // Of each read: the byte offset of its neighbour in a state, and whether it
+  // crosses a subdomain edge; of each draw (2 p + side): its read.
+  for (int y = tid; y < 2 * count; y += kWaveThreads) {
+    const int i = first + (y >> 1), side = y & 1;
+    const int nb = side ? (kRing && i == N - 1 ? 0 : i + 1) : (kRing && i == 0 ? N - 1 : i - 1);
+    const bool edge = ndraw && (point_meta<kRing>(i, N, P) & (side ? kEdgeRight : kEdgeLeft));
+    s_read[y] = (uint32_t)(nb * (int)sizeof(F)) | (edge ? kAcross : 0u);
+  }
+  for (int q = tid; q < ndraw; q += kWaveThreads) {
+    const int p = q >> 1, i = q & 1 ? (p + 1) * N / P - 1 : p * N / P;
+    s_draw[q] = i < first || i >= last ? kNoRead : (uint16_t)(2 * (i - first) + (q & 1));
+  }
+  __syncthreads();
+
+  // The reads of steps k0 .. k0+n-1, by the threads t, t + nt, ...: across a
+  // subdomain edge the neighbour's value of step max(k - delay, 0), inside a
+  // subdomain that of step k.
+  auto prepare = [&](int k0, const Walk& reads, const Walk& draws) __attribute__((always_inline)) {
+    const int n = min(kChunk, K - k0);
+    uint32_t(*tab)[S::kEntries] = s_table[(k0 / kChunk) & 1];
+    if (ndraw < 2 * N) {
+      for (Walk w = reads; w.s < n; w.next()) {
+        const uint32_t rd = s_read[w.x];
+        if (!(rd & kAcross)) tab[w.s][w.x] = (uint32_t)(((k0 + w.s) & (kHist - 1)) * kRow) + rd;
+      }
+    }
+    if (ndraw) {
+      for (Walk w = draws; w.s < n; w.next()) {
+        const int k = k0 + w.s;
+        const int dl = delay_at(seed, (uint64_t)k * (uint64_t)ndraw + (uint64_t)w.x, dp1);
+        const int y = s_draw[w.x];
+        if (y != kNoRead)
+          tab[w.s][y] = (uint32_t)((max(k - dl, 0) & (kHist - 1)) * kRow) + (s_read[y] & ~kAcross);
+      }
+    }
+  };
+  // Norms of the states s0 .. s1, one helper wavefront each, and snapshots.
+  double* __restrict__ norms = a.norms ? a.norms + e * a.nobs : nullptr;
+  F* __restrict__ snaps =
+      a.snaps ? static_cast<F*>(a.snaps) + e * (int64_t)a.nsnap * N : nullptr;
+  auto report = [&](int s0, int s1, int helper) __attribute__((always_inline)) {
+    if (norms && helper == 0) {
+      constexpr int kLanes = kWave / kChunk;  // lanes of a state: 8
+      const int s = s0 + lane / kLanes;
+      const int o = a.every == 1 ? s : s / a.every;
+      const bool wanted = s <= s1 && o * a.every == s;
+      const F* u = hist + (s & (kHist - 1)) * S::kPitch;
+      // all reads under way at once
+      F v[(S::kPitch + kLanes - 1) / kLanes];
+#pragma unroll
+      for (int x = 0; x < (S::kPitch + kLanes - 1) / kLanes; ++x) {
+        const int i = x * kLanes + lane % kLanes;
+        v[x] = u[min(i, N - 1)];
+        if (i >= N) v[x] = F(0);
+      }
+      double sq = 0.0;
+#pragma unroll
+      for (int x = 0; x < (S::kPitch + kLanes - 1) / kLanes; ++x)
+        sq = __builtin_fma((double)v[x], (double)v[x], sq);
+      sq += dpp<0xB1>(sq);   // quad_perm [1,0,3,2]
+      sq += dpp<0x4E>(sq);   // quad_perm [2,3,0,1]
+      sq += dpp<0x141>(sq);  // row_half_mirror: the other half of the eight lanes
+      if (wanted && lane % kLanes == 0) norms[o] = sqrt(sq);
+    }
+    if (snaps && helper == 1) {
+      for (int j = 0; j < a.nsnap; ++j) {
+        const int s = a.snap_steps[j];
+        if (s < s0 || s > s1) continue;
+        for (int i = lane; i < N; i += kWave)
+          snaps[(int64_t)j * N + i] = hist[(s & (kHist - 1)) * S::kPitch + i];
+      }
+    }
+  };
+
+  prepare(0, Walk(tid, kWaveThreads, 2 * count), Walk(tid, kWaveThreads, ndraw));
+  const Walk reads(tid - kWave, kHelpers * kWave, 2 * count);
+  const Walk draws(tid - kWave, kHelpers * kWave, ndraw);
+  __syncthreads();
+
+  F u[M];
+#pragma unroll
+  for (int j = 0; j < M; ++j) {
+    const int t = lane * M + j;
+    u[j] = t < count ? hist[first + t] : still;
+  }
+  F r = (F)a.r;
+  asm("" : "+v"(r));
+  // the trajectory holds, for the adjoint, the second difference each step saw
+  F* __restrict__ traj = a.traj ? static_cast<F*>(a.traj) + e * (int64_t)(K + 1) * N : nullptr;
+  uint32_t at[2 * M];  // where the coming step reads
+  auto step = [&](int c, int k0, int s) __attribute__((always_inline)) {
+    if (s == 0) {
+#pragma unroll
+      for (int j = 0; j < 2 * M; ++j) at[j] = s_table[c & 1][0][lane * 2 * M + j];
+    }
+    F l[M], rr[M];
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      l[j] = *reinterpret_cast<const F*>(reinterpret_cast<const char*>(hist) + at[2 * j]);
+      rr[j] = *reinterpret_cast<const F*>(reinterpret_cast<const char*>(hist) + at[2 * j + 1]);
+    }
+    if (s + 1 < kChunk) {
+#pragma unroll
+      for (int j = 0; j < 2 * M; ++j) at[j] = s_table[c & 1][s + 1][lane * 2 * M + j];
+    }
+    F* row = hist + ((k0 + s + 1) & (kHist - 1)) * S::kPitch + first + lane * M;
+    F* tr = traj ? traj + (int64_t)(k0 + s) * N + first + lane * M : nullptr;
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      const F lap = fma_of(F(-2), u[j], l[j] + rr[j]);
+      u[j] = fma_of(r, lap, u[j]);
+      // (the cell of the right end keeps its value, finite or not)
+      row[j] = lane * M + j < count ? u[j] : still;
+      if (tr && lane * M + j < count) tr[j] = lap;
+    }
+  };
+  const int chunks = (K + kChunk - 1) / kChunk;
+  for (int c = 0; c <= chunks; ++c) {
+    const int k0 = c * kChunk;
+    if (wave == 0) {
+      __builtin_amdgcn_s_setprio(3);
+      if (K - k0 >= kChunk) {
+#pragma unroll
+        for (int s = 0; s < kChunk; ++s) step(c, k0, s);
+      } else {
+        for (int s = 0; s < K - k0; ++s) step(c, k0, s);
+      }
+      __builtin_amdgcn_s_setprio(0);
+    } else {
+      const int helper = wave - 1;
+      if (c + 1 < chunks) prepare(k0 + kChunk, reads, draws);
+      report(c == 0 ? 0 : k0 - kChunk + 1, min(k0, K), kHelpers - 1 - helper);
+    }
+    __syncthreads();
+  }
+  if (a.uK) {
+    F* __restrict__ out = static_cast<F*>(a.uK) + e * N;
+    const F* fin = hist + (K & (kHist - 1)) * S::kPitch;
+    for (int i = tid; i < N; i += kWaveThreads) out[i] = fin[i];
+  }
+}
+
+// s_acc[to[y]] += v[y / 2], 2 M cells of LDS that differ.  FP64 by the LDS
+// itself; its FP32 addition takes some 250 clocks, so those are read, added and
+// written (8 members, N = 100, P = 7, d = 4, K = 1000, both passes: 545 -> 304 us).
+template <int M>
+__device__ __forceinline__ void lds_add(double* s_acc, const uint32_t (&to)[2 * M],
+                                        const double (&v)[M]) {
+#pragma unroll
+  for (int y = 0; y < 2 * M; ++y)
+    __builtin_amdgcn_ds_atomic_fadd_f64(
+        (__attribute__((address_space(3))) double*)(s_acc + to[y]), v[y >> 1]);
+}
+template <int M>
+__device__ __forceinline__ void lds_add(float* s_acc, const uint32_t (&to)[2 * M],
+                                        const float (&v)[M]) {
+  float x[2 * M];
+#pragma unroll
+  for (int y = 0; y < 2 * M; ++y) x[y] = s_acc[to[y]];
+#pragma unroll
+  for (int y = 0; y < 2 * M; ++y) s_acc[to[y]] = x[y] + v[y >> 1];
+}
+
+// The adjoint of the above (the recurrence stated for ensemble_adjoint_kernel).
+// A read of step k that landed on step k is reversed by the neighbour's
+// lambda(k+1), which a lane shift brings, where the helpers have set its flag; a
+// delayed one by an LDS addition of the reader's lambda(k+1) to the accumulator
+// of (landing step, point read, side), at the address that the helpers prepared,
+// and the accumulators of a step are read one step before they are used: the
+// last additions to them came from the step before that.  Every accumulator has
+// one reader that adds to it, one addition a step, so the order is fixed.  dL/dr
+// is the sum of lambda(k+1) times the second difference the forward step saw,
+// which the forward pass left in the workspace.
+struct EnsWaveAdjDev {
+  const void* lap;  // member e: second differences of step k at (e (K+1) + k) N
+  const void* gK;
+  const uint64_t* seeds;
+  void* grad_u0;
+  double* grad_r;
+  double* grad_c1;
+  double* grad_cN;
+  int32_t N, P, K, d;
+  double r;
+};
+
+template <typename F, int M, bool kRing>
+__global__ __launch_bounds__(kWaveThreads)
+__attribute__((amdgpu_waves_per_eu(M <= 2 ? 4 : 2))) void ensemble_wave_adjoint_kernel(EnsWaveAdjDev a) {
+  using S = WaveShape<M>;
+  constexpr int kLand = kChunk;  // accumulator rows: landing steps k-d .. k, d < kChunk
+  // [step][point][side]: side 0 what point j+1 read of j, side 1 what j-1 read; behind
+  // them the cells where additions that nothing asked for go, one for each read
+  __shared__ __align__(16) F s_acc[(kLand + 1) * S::kEntries];
+  __shared__ __align__(16) uint32_t s_to[2][kChunk][S::kEntries];  // indexes into s_acc
+  __shared__ __align__(16) uint8_t s_now[2][kChunk][S::kEntries];  // [point][side]: landed at once
+  __shared__ __align__(16) F s_lap[2][kChunk][S::kPoints];  // second differences
+  __shared__ uint16_t s_draw[S::kEntries + 4];  // of each draw (2 p + side) the read it is for
+  constexpr uint16_t kNoRead = 0xffff;
+  const int N = a.N, P = a.P, K = a.K;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid / kWave);
+  const int64_t e = blockIdx.x;
+  const uint64_t seed = a.seeds[e];
+  const F* __restrict__ gK = static_cast<const F*>(a.gK) + e * N;
+  const F* __restrict__ lap = static_cast<const F*>(a.lap) + e * (int64_t)(K + 1) * N;
+  constexpr int first = kRing ? 0 : 1;
+  const int last = kRing ? N : N - 1;
+  const int count = last - first;
+  const int ndraw = a.d > 0 && P > 1 ? 2 * P : 0;
+  const uint32_t dp1 = (uint32_t)a.d + 1;
+  // the point (counted from the first updated one) that read y reads, -1: an end
+  auto target = [&](int y) __attribute__((always_inline)) {
+    const int t = (y >> 1) + (y & 1 ? 1 : -1);
+    if (kRing) return t < 0 ? count - 1 : (t == count ? 0 : t);
+    return t < 0 || t >= count ? -1 : t;
+  };
+
+  for (int i = tid; i < (kLand + 1) * S::kEntries; i += kWaveThreads) s_acc[i] = F(0);
+  for (int i = tid; i < 2 * kChunk * S::kEntries; i += kWaveThreads) {
+    (&s_to[0][0][0])[i] = (uint32_t)(kLand * S::kEntries + i % S::kEntries);
+    (&s_now[0][0][0])[i] = 0;
+  }
+  for (int q = tid; q < ndraw; q += kWaveThreads) {
+    const int p = q >> 1, i = q & 1 ? (p + 1) * N / P - 1 : p * N / P;
+    const int y = 2 * (i - first) + (q & 1);
+    s_draw[q] = i < first || i >= last || target(y) < 0 ? kNoRead : (uint16_t)y;
+  }
+  __syncthreads();
+  // reads inside a subdomain land at once at every step
+  for (int y = tid; y < 2 * count; y += kWaveThreads) {
+    const int t = target(y);
+    const bool edge =
+        ndraw && (point_meta<kRing>(first + (y >> 1), N, P) & (y & 1 ? kEdgeRight : kEdgeLeft));
+    if (t >= 0 && !edge)
+      for (int x = 0; x < 2 * kChunk; ++x) (&s_now[0][0][0])[x * S::kEntries + 2 * t + (y & 1)] = 1;
+  }
+  auto prepare = [&](int c, const Walk& draws) __attribute__((always_inline)) {
+    const int k0 = c * kChunk, n = min(kChunk, K - k0);
+    if (!ndraw) return;
+    for (Walk w = draws; w.s < n; w.next()) {
+      const int k = k0 + w.s, y = s_draw[w.x];
+      const int dl = delay_at(seed, (uint64_t)k * (uint64_t)ndraw + (uint64_t)w.x, dp1);
+      if (y == kNoRead) continue;
+      const int at = max(k - dl, 0), to = 2 * target(y) + (y & 1);
+      s_to[c & 1][w.s][y] =
+          (uint32_t)((at == k ? kLand : at & (kLand - 1)) * S::kEntries + (at == k ? y : to));
+      s_now[c & 1][w.s][to] = at == k;
+    }
+  };
+  const int chunks = (K + kChunk - 1) / kChunk;
+  const Walk draws(tid - kWave, kHelpers * kWave, ndraw);
+  __syncthreads();
+
+  F h[M], hl, hr;  // lambda(k+1) of the lane's points and of those beside them
+  // the neighbour lanes' points; on the ring the cell behind point N-1 holds
+  // point 0's, and lane 0 has point N-1 on its left
+  auto trade = [&]() __attribute__((always_inline)) {
+    hl = from_lower_lane(h[M - 1]);
+    hr = from_upper_lane(h[0]);
+    if constexpr (kRing) {
+      F end = F(0);
+#pragma unroll
+      for (int j = 0; j < M; ++j)
+        if ((N - 1) % M == j) end = read_lane(h[j], (N - 1) / M);
+      hl = lane == 0 ? end : hl;
+      const F zero = read_lane(h[0], 0);
+      const bool here = lane == N / M;
+#pragma unroll
+      for (int j = 0; j < M; ++j)
+        if (N % M == j) h[j] = here ? zero : h[j];
+      if (N % M == 0) hr = lane == N / M - 1 ? zero : hr;
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < M; ++j) h[j] = lane * M + j < count ? gK[first + lane * M + j] : F(0);
+  trade();
+  F r = (F)a.r;
+  asm("" : "+v"(r));
+  double gr = 0.0, sum[M] = {};
+  // The second differences of a chunk, from memory on their way while the
+  // thread does what comes between the two calls.
+  constexpr int kLoads = (kChunk * S::kPoints + kHelpers * kWave - 1) / (kHelpers * kWave);
+  auto load = [&](F(&v)[kLoads], int c, int t, int nt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int x = t + i * nt, s = x / S::kPoints, j = x % S::kPoints;
+      const int k = c * kChunk + s;
+      v[i] = s < kChunk && j < count && k < K ? lap[(int64_t)k * N + first + j] : F(0);
+    }
+  };
+  auto keep = [&](const F(&v)[kLoads], int c, int t, int nt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int x = t + i * nt, s = x / S::kPoints;
+      if (s < kChunk) s_lap[c & 1][s][x % S::kPoints] = v[i];
+    }
+  };
+  F got[M][2];  // the accumulators of the coming step
+  uint32_t to[2 * M];
+  uint16_t now[M];
+  F lp[M];
+#pragma unroll
+  for (int j = 0; j < M; ++j) got[j][0] = got[j][1] = F(0);
+  auto fetch = [&](int c, int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int y = 0; y < 2 * M; ++y) to[y] = s_to[c & 1][s][lane * 2 * M + y];
+#pragma unroll
+    for (int j = 0; j < M; ++j)
+      now[j] = *reinterpret_cast<const uint16_t*>(&s_now[c & 1][s][2 * (lane * M + j)]);
+#pragma unroll
+    for (int j = 0; j < M; ++j) lp[j] = s_lap[c & 1][s][lane * M + j];
+  };
+  auto step = [&](int c, int s) __attribute__((always_inline)) {
+    F out[M];
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      const F lc = h[j];
+      const F right = j + 1 < M ? h[j + 1 < M ? j + 1 : 0] : hr;
+      const F left = j > 0 ? h[j > 0 ? j - 1 : 0] : hl;
+      F nb = (now[j] & 1 ? right : F(0)) + (now[j] & 0x100 ? left : F(0));
+      nb += got[j][0] + got[j][1];
+      out[j] = fma_of(r, fma_of(F(-2), lc, nb), lc);
+    }
+    // this step's delayed reads; then the accumulators of the next step down,
+    // complete with them, and this step's row cleared for step k - kLand
+    lds_add<M>(s_acc, to, h);
+    F* row = s_acc + (s * S::kEntries + lane * 2 * M);
+    const F* nxt = s_acc + (((s - 1) & (kLand - 1)) * S::kEntries + lane * 2 * M);
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      got[j][0] = nxt[2 * j];
+      got[j][1] = nxt[2 * j + 1];
+    }
+    F lq[M];
+#pragma unroll
+    for (int j = 0; j < M; ++j) lq[j] = lp[j];
+    if (s > 0) fetch(c, s - 1);
+#pragma unroll
+    for (int y = 0; y < 2 * M; ++y) row[y] = F(0);
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      // (on the ring the cell behind point N-1 holds a copy, which is not summed)
+      const F hj = kRing && lane * M + j >= count ? F(0) : h[j];
+      gr = __builtin_fma((double)hj, (double)lq[j], gr);
+      sum[j] = __builtin_fma((double)r, (double)h[j], sum[j]);
+      h[j] = lane * M + j < count ? out[j] : F(0);
+    }
+    trade();
+  };
+  if (chunks > 0 && wave > 0) {
+    F v[kLoads];
+    load(v, chunks - 1, tid - kWave, kHelpers * kWave);
+    prepare(chunks - 1, draws);
+    keep(v, chunks - 1, tid - kWave, kHelpers * kWave);
+  }
+  __syncthreads();
+  for (int c = chunks - 1; c >= 0; --c) {
+    if (wave == 0) {
+      __builtin_amdgcn_s_setprio(3);
+      const int n = min(kChunk, K - c * kChunk);
+      fetch(c, n - 1);
+      if (n == kChunk) {
+#pragma unroll
+        for (int s = kChunk - 1; s >= 0; --s) step(c, s);
+      } else {
+        for (int s = n - 1; s >= 0; --s) step(c, s);
+      }
+      __builtin_amdgcn_s_setprio(0);
+    } else if (c >= 1) {
+      F v[kLoads];
+      load(v, c - 1, tid - kWave, kHelpers * kWave);
+      prepare(c - 1, draws);
+      keep(v, c - 1, tid - kWave, kHelpers * kWave);
+    }
+    __syncthreads();
+  }
+  if (wave != 0) return;
+  F* __restrict__ gu = static_cast<F*>(a.grad_u0) + e * N;
+#pragma unroll
+  for (int j = 0; j < M; ++j) {
+    const int t = lane * M + j;
+    if (t >= count) continue;
+    gu[first + t] = h[j];
+    if (!kRing && t == 0) a.grad_c1[e] = sum[j] + (double)gK[0];
+    if (!kRing && t == count - 1) a.grad_cN[e] = sum[j] + (double)gK[N - 1];
+  }
+  gr = wave_sum_to_last(gr);
+  if (lane == kWave - 1) a.grad_r[e] = gr;
+  if (lane == 0) {
+    if (kRing) {  // the ring has no end values
+      a.grad_c1[e] = 0.0;
+      a.grad_cN[e] = 0.0;
+    } else {
+      gu[0] = F(0);
+      gu[N - 1] = F(0);
+    }
+  }
+}
+
 // Points per thread the kernel is built for.
 static int ensemble_ppt(int64_t need) {
   for (int p : {1, 2, 4, 8, 12, 16})
@@ -539,6 +1050,19 @@ static hipError_t ensemble_dispatch(int ppt, dim3 grid, dim3 block, size_t lds, 
     case 8: hipLaunchKernelGGL((ensemble_kernel<F, 8, kRing>), grid, block, lds, s, a); break;
     case 12: hipLaunchKernelGGL((ensemble_kernel<F, 12, kRing>), grid, block, lds, s, a); break;
     case 16: hipLaunchKernelGGL((ensemble_kernel<F, 16, kRing>), grid, block, lds, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <typename F, bool kRing>
+static hipError_t ensemble_wave_dispatch(int m, dim3 grid, hipStream_t s, const EnsDev& a) {
+  const dim3 block(kWaveThreads);
+  switch (m) {
+    case 1: hipLaunchKernelGGL((ensemble_wave_kernel<F, 1, kRing>), grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((ensemble_wave_kernel<F, 2, kRing>), grid, block, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((ensemble_wave_kernel<F, 3, kRing>), grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((ensemble_wave_kernel<F, 4, kRing>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -578,6 +1102,15 @@ hipError_t launch_ensemble(const EnsembleLaunch& L, hipStream_t s) {
   a.nsnap = L.nsnap;
   for (int j = 0; j < kEnsembleMaxSnaps; ++j) a.snap_steps[j] = j < L.nsnap ? L.snap_steps[j] : -1;
   const dim3 grid((unsigned)L.E), block((unsigned)kFwdThreads);
+  // a trajectory is written in the form that the adjoint's kernel takes
+  const int wm = ensemble_wave_m(L.N, L.d, L.periodic != 0);
+  if (wm > 0) {
+    if (L.periodic)
+      return L.dtype == 0 ? ensemble_wave_dispatch<float, true>(wm, grid, s, a)
+                          : ensemble_wave_dispatch<double, true>(wm, grid, s, a);
+    return L.dtype == 0 ? ensemble_wave_dispatch<float, false>(wm, grid, s, a)
+                        : ensemble_wave_dispatch<double, false>(wm, grid, s, a);
+  }
   const size_t sh = (size_t)lds;
   if (L.periodic)
     return L.dtype == 0 ? ensemble_dispatch<float, true>(ppt, grid, block, sh, s, a)
@@ -600,12 +1133,46 @@ static hipError_t ensemble_adjoint_dispatch(int ppt, dim3 grid, size_t lds, hipS
   return hipGetLastError();
 }
 
+template <typename F, bool kRing>
+static hipError_t ensemble_wave_adjoint_launch(const EnsembleAdjointLaunch& L, int m,
+                                               hipStream_t s) {
+  EnsWaveAdjDev a;
+  a.lap = L.traj;
+  a.gK = L.gK;
+  a.seeds = L.seeds;
+  a.grad_u0 = L.grad_u0;
+  a.grad_r = L.grad_r;
+  a.grad_c1 = L.grad_c1;
+  a.grad_cN = L.grad_cN;
+  a.N = L.N;
+  a.P = L.P;
+  a.K = L.K;
+  a.d = L.d;
+  a.r = L.r;
+  const dim3 grid((unsigned)L.E), b(kWaveThreads);
+  switch (m) {
+    case 1: hipLaunchKernelGGL((ensemble_wave_adjoint_kernel<F, 1, kRing>), grid, b, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((ensemble_wave_adjoint_kernel<F, 2, kRing>), grid, b, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((ensemble_wave_adjoint_kernel<F, 3, kRing>), grid, b, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((ensemble_wave_adjoint_kernel<F, 4, kRing>), grid, b, 0, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_ensemble_adjoint(const EnsembleAdjointLaunch& L, hipStream_t s) {
   if (L.E < 1 || L.E > 0x7fffffffLL || L.N < 3 || L.P < 1 || L.P > L.N || L.K < 0 || L.d < 0 ||
       !L.traj || !L.gK || !L.seeds || !L.grad_u0 || !L.grad_r || !L.grad_c1 || !L.grad_cN)
     return hipErrorInvalidValue;
   const int64_t lds = ensemble_adjoint_lds_bytes(L.dtype, L.N, L.P, L.d);
   if (lds > kEnsembleMaxLds) return hipErrorInvalidValue;
+  if (const int m = ensemble_wave_m(L.N, L.d, L.periodic != 0); m > 0) {
+    if (L.periodic)
+      return L.dtype == 0 ? ensemble_wave_adjoint_launch<float, true>(L, m, s)
+                          : ensemble_wave_adjoint_launch<double, true>(L, m, s);
+    return L.dtype == 0 ? ensemble_wave_adjoint_launch<float, false>(L, m, s)
+                        : ensemble_wave_adjoint_launch<double, false>(L, m, s);
+  }
   const int64_t count = L.periodic ? L.N : L.N - 2;  // updated points
   const int ppt = ensemble_ppt((count + kAdjThreads - 1) / kAdjThreads);
   if (ppt == 0 || ppt > 8) return hipErrorInvalidValue;

@@ -404,8 +404,12 @@ int heat1d_run_async_ensemble_adjoint(heat1d_plan_t plan, const void *u0, const 
  * wrapping, grad_c1 = grad_cN = 0.  The forward pass
  * keeps u at every S-th step (S = opts.ckpt_stride, default ceil(sqrt(K)))
  * and, for the points next to the P-1 subdomain edges only, every step; the
- * backward pass replays each stretch of S steps from its checkpoint.  Both
- * run in lockstep, one launch per step: in the emulated mode the delays are a
+ * backward pass replays each stretch of S steps from its checkpoint.  Both run
+ * in lockstep, one launch per step, or, where every subdomain has more than
+ * 1024 points (and opts.sync_kernel is not HEAT1D_SYNC_STEP), one per 32 steps,
+ * with the states at as many of those launches' starts kept as the same
+ * workspace holds (all of them up to K = 32 (ceil(K/S) + S - 1)): grad_u0 and uK
+ * are the same bit for bit.  In the emulated mode the delays are a
  * fixed function of the seed, so the forward values equal those of
  * heat1d_run_async bit for bit.  u0, gK: N elements (device, read only; they
  * may alias); uK: NULL or N elements, receives u(K); grad_u0: N elements;

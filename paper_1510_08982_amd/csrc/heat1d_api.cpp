@@ -1471,32 +1471,44 @@ int heat1d_run_async_adjoint(heat1d_plan_t p, const void* u0, const void* gK, do
   // bit for bit.
   const bool tiled = p->opts.sync_kernel != HEAT1D_SYNC_STEP && async_tiled_applies(N, P, d);
   const int T = async_tiled_depth();
-  const int G = async_tiled_store_every();
   if (tiled)
     HEAT1D_TRY(launch_async_tiled_order(A, (int*)A.ord_lock, (int*)A.ord_adj, s));
-  const int64_t sstride = (int64_t)(L.state_bytes / es);
-  for (int64_t c = 0; c < L.nck && K > 0; ++c) {
-    const int64_t k0 = c * S, len = std::min<int64_t>(S, K - k0);
-    const bool last = c + 1 == L.nck;
-    const void* cur = ck(c);
-    if (tiled) {
-      // launches of T steps from the stretch start; the last stretch keeps
-      // every G-th state for the backward sweep (T is a multiple of G, so each
-      // launch starts from a kept state); earlier stretches pass through the
-      // two lambda buffers, unused until then
-      int ping = 0;
-      for (int64_t done = 0; done < len;) {
-        const int steps = (int)std::min<int64_t>(T, len - done);
-        const bool end = done + steps == len;
-        void* out = end ? (last ? fin : ck(c + 1)) : (last ? nullptr : lam[ping]);
-        ping ^= 1;
-        HEAT1D_TRY(launch_async_lockstep_tiled(A, cur, out, last ? st(0) : nullptr, sstride,
-                                               (int)k0, (int)(k0 + done), steps, 1, s));
-        cur = out ? out : st((done + steps) / G - 1);
-        done += steps;
-      }
-      continue;
+  // Tiled runs go in segments of T steps, whose transpose needs the state at the
+  // segment's start alone.  The places of the checkpoints and of a stretch's
+  // states (ck and st are one array) hold those of all segments up to
+  // K = T (nck + S - 1), 4096 steps with the default S; beyond that the segments
+  // form nst stretches of at most m, the starts of a stretch's later segments
+  // replayed from its first.
+  const int64_t nseg = (K + T - 1) / T, places = L.nck + S - 1;
+  int64_t m = 1;
+  while ((nseg + m - 1) / m + m - 1 > places) ++m;
+  const int64_t nst = std::max<int64_t>(1, std::min(nseg, places - (m - 1)));
+  auto first_seg = [&](int64_t c) { return c * (nseg / nst) + std::min(c, nseg % nst); };
+  // the segments [a, b) forward from u(a T) = cur: the state after segment g goes
+  // to where(g)
+  auto forward = [&](const void* cur, int64_t a, int64_t b, int record, auto where) {
+    for (int64_t g = a; g < b; ++g) {
+      void* out = where(g);
+      const hipError_t f = launch_async_lockstep_tiled(
+          A, cur, out, (int)(g * T), (int)std::min<int64_t>(T, K - g * T), record, s);
+      if (f != hipSuccess) return f;
+      cur = out;
     }
+    return hipSuccess;
+  };
+  for (int64_t c = 0; tiled && c < nst && K > 0; ++c) {
+    // earlier stretches pass through the two lambda buffers, unused until the
+    // backward sweep; the last one's states stay for it
+    const int64_t a = first_seg(c), b = first_seg(c + 1);
+    const bool last = c + 1 == nst;
+    HEAT1D_TRY(forward(ck(c), a, b, 1, [&](int64_t g) {
+      if (g + 1 == b) return last ? fin : ck(c + 1);
+      return last ? ck(nst + (g - a)) : lam[g & 1];
+    }));
+  }
+  for (int64_t c = 0; !tiled && c < L.nck && K > 0; ++c) {
+    const int64_t k0 = c * S, len = std::min<int64_t>(S, K - k0);
+    const void* cur = ck(c);
     for (int64_t j = 1; j <= len; ++j) {
       void* nxt = j < len ? st(j - 1) : (c + 1 < L.nck ? ck(c + 1) : fin);
       HEAT1D_TRY(launch_async_lockstep(A, cur, nxt, (int)(k0 + j - 1), 1, s));
@@ -1511,41 +1523,29 @@ int heat1d_run_async_adjoint(heat1d_plan_t p, const void* u0, const void* gK, do
                   : launch_impose_ends(p->dtype, gK, lK, N, 1, 0.0, 0.0, s));
   HEAT1D_TRY(launch_async_edges(p->dtype, lK, rec(A.LE, K), A.lo, P, N, A.ring, s));
   const void* lcur = lK;
-  for (int64_t c = L.nck - 1; c >= 0 && K > 0; --c) {
+  for (int64_t c = nst - 1; tiled && c >= 0 && K > 0; --c) {
+    const int64_t a = first_seg(c), b = first_seg(c + 1);
+    if (c + 1 < nst)
+      HEAT1D_TRY(forward(ck(c), a, b - 1, 0, [&](int64_t g) { return ck(nst + (g - a)); }));
+    for (int64_t g = b - 1; g >= a; --g) {
+      const void* u = g == a ? ck(c) : ck(nst + (g - a) - 1);
+      void* lout = g == 0 ? grad_u0 : (lcur == lam[0] ? lam[1] : lam[0]);
+      EventPair* ev = timing_begin(p, s);
+      e = launch_async_adjoint_tiled(A, lcur, lout, u, (int)(g * T),
+                                     (int)std::min<int64_t>(T, K - g * T), s);
+      timing_end(ev, s);
+      if (e != hipSuccess) return hip_status(e);
+      lcur = lout;
+    }
+  }
+  for (int64_t c = L.nck - 1; !tiled && c >= 0 && K > 0; --c) {
     const int64_t k0 = c * S, len = std::min<int64_t>(S, K - k0);
     if (c + 1 < L.nck) {
       const void* cur = ck(c);
-      if (tiled) {
-        // every G-th state of the stretch (u(k0) is its checkpoint)
-        for (int64_t done = 0; done < len - 1;) {
-          const int steps = (int)std::min<int64_t>(T, len - 1 - done);
-          HEAT1D_TRY(launch_async_lockstep_tiled(A, cur, nullptr, st(0), sstride, (int)k0,
-                                                 (int)(k0 + done), steps, 0, s));
-          if (done + steps < len - 1) cur = st((done + steps) / G - 1);
-          done += steps;
-        }
-      } else {
-        for (int64_t j = 1; j < len; ++j) {
-          HEAT1D_TRY(launch_async_lockstep(A, cur, st(j - 1), (int)(k0 + j - 1), 0, s));
-          cur = st(j - 1);
-        }
+      for (int64_t j = 1; j < len; ++j) {
+        HEAT1D_TRY(launch_async_lockstep(A, cur, st(j - 1), (int)(k0 + j - 1), 0, s));
+        cur = st(j - 1);
       }
-    }
-    if (tiled) {
-      // lambda in registers for up to T steps per launch, segments starting
-      // at k0 + iT (the launches' lowest steps fall on kept states)
-      for (int64_t i = (len - 1) / T; i >= 0; --i) {
-        const int64_t kb = k0 + i * T;
-        const int steps = (int)std::min<int64_t>(T, k0 + len - kb);
-        void* lout = kb == 0 ? grad_u0 : (lcur == lam[0] ? lam[1] : lam[0]);
-        EventPair* ev = timing_begin(p, s);
-        e = launch_async_adjoint_tiled(A, lcur, lout, ck(c), st(0), sstride, (int)k0, (int)kb,
-                                       steps, s);
-        timing_end(ev, s);
-        if (e != hipSuccess) return hip_status(e);
-        lcur = lout;
-      }
-      continue;
     }
     for (int64_t k = k0 + len - 1; k >= k0; --k) {
       const void* uk = k == k0 ? ck(c) : st(k - k0 - 1);

@@ -155,21 +155,15 @@ hipError_t launch_async_lockstep(const AsyncAdjStep& a, const void* cur, void* n
                                  int record, hipStream_t s);
 // The same steps on register tiles, at most async_tiled_depth() per launch,
 // for rods (or rings, P >= 2) whose subdomains are longer than one tile (bit
-// for bit the per-step launches): from the state `in` of step k0, `steps` steps; when
-// states is not NULL, every state u(k) with k - kc a positive multiple of
-// async_tiled_store_every() goes to states + ((k-kc)/every - 1)*stride; the
-// last state to `out` unless it is NULL.
+// for bit the per-step launches): from the state `in` of step k0, `steps` steps,
+// the last state to `out`.
 bool async_tiled_applies(int64_t N, int P, int d);
 int async_tiled_depth();
-int async_tiled_store_every();
-hipError_t launch_async_lockstep_tiled(const AsyncAdjStep& a, const void* in, void* out,
-                                       void* states, int64_t stride, int kc, int k0, int steps,
-                                       int record, hipStream_t s);
-// The transpose steps k0+steps-1 .. k0 on register tiles, lambda in registers;
-// u from the sparse states of the replay (u_first for k == kc, st_base +
-// ((k-kc)/every - 1)*stride for the other multiples of every above kc) and
-// recomputed between them; k0 - kc a multiple of every; lambda bit for bit
-// that of the per-step kernel; dL/dr summed per tile into part[t]
+hipError_t launch_async_lockstep_tiled(const AsyncAdjStep& a, const void* in, void* out, int k0,
+                                       int steps, int record, hipStream_t s);
+// The transpose steps k0+steps-1 .. k0 (at most async_tiled_depth() of them) on
+// register tiles, lambda in registers; u = u(k0), from which each tile steps
+// forward itself; lambda bit for bit that of the per-step kernel; dL/dr summed per tile into part[t]
 // (async_tiled_tiles slots), dL/dc1 and dL/dcN into ends.
 int64_t async_tiled_tiles(int dtype, int64_t N);
 // The order in which the tiled launches take their tiles: those holding a
@@ -178,8 +172,7 @@ int64_t async_tiled_tiles(int dtype, int64_t N);
 hipError_t launch_async_tiled_order(const AsyncAdjStep& a, int* ord_lock, int* ord_adj,
                                     hipStream_t s);
 hipError_t launch_async_adjoint_tiled(const AsyncAdjStep& a, const void* lam_in, void* lam_out,
-                                      const void* u_first, const void* st_base, int64_t stride,
-                                      int kc, int k0, int steps, hipStream_t s);
+                                      const void* u, int k0, int steps, hipStream_t s);
 // lambda(k) from lambda(k+1) and u(k), LE[k] and the step's dL/dr, dL/dc1,
 // dL/dcN terms (added to part and ends).
 hipError_t launch_async_adjoint_step(const AsyncAdjStep& a, const void* lam1, void* lam0,

@@ -20,9 +20,10 @@
 // edge 0 is the wrap between subdomain P-1 and subdomain 0: E[k][0] =
 // (u_{N-1}(k), u_0(k)), and subdomain p's right edge is edge (p+1) mod P.
 //
-// Steps are HBM-bound: a forward step reads and writes the state (2 s bytes
-// per point), a backward step reads lambda(k+1) and u(k) and writes lambda(k)
-// (3 s bytes per point); the edge records add 2 values per edge and step.
+// The per-step launches are HBM-bound: a forward step reads and writes the state
+// (2 s bytes per point), a backward step reads lambda(k+1) and u(k) and writes
+// lambda(k) (3 s bytes per point); the edge records add 2 values per edge and
+// step.  The tiled launches read and write that once in 32 steps.
 #include <algorithm>
 
 #include "heat1d_delays.h"
@@ -189,25 +190,28 @@ __global__ __launch_bounds__(kThreads) void async_lockstep_kernel(
 // recomputed with their delayed reads, from a history of their last d+2
 // values kept in LDS (filled from the edge record E for the steps before the
 // launch, by the tile itself after).  A tile whose output range holds an edge
-// point records its values in E (record != 0).  With `states` not NULL every
-// state u(k) the launch computes with k - kc a positive multiple of kStoreEvery
-// is stored at states + ((k - kc) / kStoreEvery - 1) * stride (the sparse
-// replay of a stretch that starts at step kc); the last state goes to `out`
-// unless it is NULL.
+// point records its values in E (record != 0).
 constexpr int kTileM = 16;
 constexpr int kTileT = 32;
 constexpr int kHistQ = 258;  // d + 2 slots for d <= 255
-// The replay of a stretch stores every kStoreEvery-th state; the transpose
-// recomputes the kStoreEvery-1 states between them in registers, so its tiles
-// carry kStoreEvery-1 more halo points (kAdjT).
-constexpr int kStoreEvery = 4;
-constexpr int kAdjT = kTileT + kStoreEvery;
+// The transpose of a segment of up to kTileT steps steps its tiles forward from
+// the state at the segment's start, keeps every kGroup-th of its states in LDS
+// and the second differences of one group in registers.  Its tiles have points enough beside
+// their own for that.
+constexpr int kGroup = 8;
+constexpr int kAdjT = kTileT + 4;
+constexpr int kAdjH = kAdjT;   // a multiple of both vector lengths
+constexpr int kAdjHist = 512;  // d + 2 slots for d <= 255, a power of two
+static_assert(kAdjT % 4 == 0, "the tiles' halo is kAdjT itself");
+template <typename F>
+constexpr int kAdjM = sizeof(F) == 4 ? 16 : 8;  // points per lane: a group takes kGroup of them
+static int adjoint_m(int dtype) { return dtype == 0 ? kAdjM<float> : kAdjM<double>; }
 // Tiles per workgroup of the lockstep and transpose kernels.  A workgroup's
 // tiles finish at different times (the one holding a subdomain edge runs
 // longest), and its wavefront slots are refilled only once all of them are
 // done, so one tile per workgroup keeps the CU's slots busy.
 constexpr int kAdjWaves = 1;
-static_assert(kTileT % kStoreEvery == 0, "launches start on kept states");
+static_assert(kTileT % kGroup == 0, "whole groups but the last");
 
 // Where a tile sits and what it holds.  Dirichlet rods: the tiles of the
 // synchronous tiled pass (tile t from point t*Wout, the rod ends pinned by the
@@ -333,9 +337,8 @@ __global__ __launch_bounds__(256) void tile_order_kernel(int* __restrict__ order
 
 template <typename F, bool kRing>
 __global__ __launch_bounds__(kAdjWaves * kWave) void async_lockstep_tiled_kernel(
-    const F* __restrict__ in, F* __restrict__ out, F* __restrict__ states, int64_t stride,
-    int kc, F* __restrict__ E, const int* __restrict__ order, int64_t N, int P, int k0,
-    int steps, int d,
+    const F* __restrict__ in, F* __restrict__ out, F* __restrict__ E,
+    const int* __restrict__ order, int64_t N, int P, int k0, int steps, int d,
     uint64_t seed, int sched, F r, F c1, F cN, int64_t tiles, int H, double pscale, int record,
     int aligned) {
   constexpr int M = kTileM;
@@ -390,6 +393,7 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_lockstep_tiled_kernel
   const bool own_a = qa >= lo_t && qa < hi_t, own_b = qb >= lo_t && qb < hi_t;
   if (left_end) u[0] = (lane == 0) ? c1 : u[0];
   if (right_end) set_point<F, M>(u, jN, lane == lN, cN);
+  asm("" : "+v"(r));
   for (int s = 0; s < steps; ++s) {
     const int k = k0 + s;
     F ua = F(0), ual = F(0), ub = F(0), ubr = F(0);
@@ -422,46 +426,52 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_lockstep_tiled_kernel
     }
     if (left_end) u[0] = (lane == 0) ? c1 : u[0];
     if (right_end) set_point<F, M>(u, jN, lane == lN, cN);
-    if (states && (k + 1 - kc) % kStoreEvery == 0)
-      store_points<F, M>(u, states + (int64_t)((k + 1 - kc) / kStoreEvery - 1) * stride,
-                         base + q0, q0, lo_t, hi_t, st_aligned);
   }
-  if (out) store_points<F, M>(u, out, base + q0, q0, lo_t, hi_t, st_aligned);
+  store_points<F, M>(u, out, base + q0, q0, lo_t, hi_t, st_aligned);
 }
 
 // The transpose steps k0+steps-1 down to k0 on register tiles: lambda of the
-// tile's points stays in registers across the launch's steps.  The states come
-// from the sparse replay: u(k) is stored for k - kc a multiple of kStoreEvery
-// (u_first for k == kc, the stretch's checkpoint; st_base + ((k-kc)/kStoreEvery - 1)
-// * stride above it), and the up to kStoreEvery-1 states above each stored one
-// are recomputed in registers (Eq.4 with the delayed edge reads taken from the
-// edge record E) before the transpose steps that use them; the next stored
-// state is loaded while the current group is computed.  k0 - kc is a multiple
-// of kStoreEvery.  Every point takes the plain transpose step (lambda_i(k)
-// from lambda_{i+-1}(k+1), neighbours by DPP); the two edge points are then
-// recomputed with the contributions gathered from the later steps whose
-// delayed reads landed on them, from an LDS history of their lambda (filled
-// from LE for the steps above the launch), in the order of the per-step
-// kernel, so lambda is bit for bit the same.  dL/dr over the tile's own
+// tile's points stays in registers across the launch's steps.  Of the states
+// only u(k0) is read: the tile steps forward from it (Eq.4 with the delayed edge
+// reads taken from the edge record E), keeps every kGroup-th state in LDS, and
+// goes back group by group, the second differences of a group's states
+// recomputed into registers before the transpose steps that use them.  Every point takes the plain
+// transpose step (lambda_i(k) from lambda_{i+-1}(k+1), neighbours by DPP); the
+// two edge points are then recomputed with the contributions gathered from the
+// later steps whose delayed reads landed on them, from an LDS history of their
+// lambda (filled from LE for the steps above the launch), in the order of the
+// per-step kernel, so lambda is bit for bit the same.  dL/dr over the tile's own
 // output points (the edge points' delayed Laplacians as a correction of the
 // plain ones), each step's terms of a lane summed in the state precision and
 // those sums in double, into part[t]; dL/dc1 and dL/dcN by the tiles that own
-// points 1 and N-2.  The tiles carry kStoreEvery-1 halo points more
-// than the steps need (the recomputed states lose one valid point per step at
-// each tile end).
+// points 1 and N-2.  The tiles carry kAdjT points beside their own at each end:
+// lambda and the recomputed states lose one valid point per step there.
+//
+// Vector arithmetic bounds it: about ten instructions a point and step (three for
+// each of 52/32 forward steps, four for the transpose and dL/dr) where every
+// fourth state through memory cost eight and 32 bytes a point and step.
+// N = 2^24, 1024 subdomains, d = 4, K = 5000, FP32: 78.2 -> 49.4 ms, a launch of
+// 32 steps 242 us; two wavefronts a SIMD (209 registers).  The tiles that hold
+// an edge are the longest chain: with the edge points' states taken from the
+// record instead of computed again a launch went from 336 to 269 us (59 us where
+// those tiles are alone, N = 2^18); with the second differences kept instead of
+// the states, from 269 to 242 us.  FP64 takes 8 points a lane, so that a group
+// fits the same registers: N = 2^22, K = 1000: 7.91 -> 5.76 ms.
 template <typename F, bool kRing>
 __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
-    const F* __restrict__ lam_in, F* __restrict__ lam_out, const F* __restrict__ u_first,
-    const F* __restrict__ st_base, int64_t stride, int kc, const F* __restrict__ E,
-    F* __restrict__ LE, const int* __restrict__ order, int64_t N, int P, int k0, int steps,
+    const F* __restrict__ lam_in, F* __restrict__ lam_out, const F* __restrict__ u0,
+    const F* __restrict__ E, F* __restrict__ LE, const int* __restrict__ order, int64_t N, int P, int k0, int steps,
     int K, int d, uint64_t seed, int sched, F r, F c1, F cN, int64_t tiles, int H, double pscale,
     double* __restrict__ part, double* __restrict__ ends, int aligned) {
-  constexpr int M = kTileM;
+  constexpr int M = kAdjM<F>;
   constexpr int L = kWave * M;
-  constexpr int G = kStoreEvery;
-  __shared__ F hist[kAdjWaves][2][kHistQ];
-  // per edge tile, for the launch's steps: the delayed edge values its steps
-  // read, and the step whose read each later step's delay lands on
+  constexpr int G = kGroup;
+  __shared__ F kept[kAdjWaves][kTileT / G - 1][M][kWave];
+  __shared__ F hist[kAdjWaves][2][kAdjHist];
+  // per edge tile, for the launch's steps: the edge points' values and the
+  // delayed ones that its steps read, and the step whose read each later step's
+  // delay lands on
+  __shared__ F eval[kAdjWaves][2][kTileT];
   __shared__ F edly[kAdjWaves][2][kTileT];
   __shared__ int pull[kAdjWaves][2][kTileT + kHistQ];
   const int lane = threadIdx.x & (kWave - 1);
@@ -471,10 +481,11 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
   const int64_t t = order[v];
   const int64_t base = kRing ? t * (L - 2 * H) - H : t * (L - 2 * H);
   const int q0 = lane * M;
+  F c[M];
   F l[M];
+  load_tile<F, M, kRing>(c, u0, base, q0, L, N, aligned != 0);
   load_tile<F, M, kRing>(l, lam_in, base, q0, L, N, aligned != 0);
   const TileSetup ts = tile_setup<kRing>(t, tiles, L, H, N, P, pscale);
-  auto stored = [&](int k) { return k == kc ? u_first : st_base + (int64_t)((k - kc) / G - 1) * stride; };
   const bool left_end = ts.left_end, right_end = ts.right_end;
   const int lo_t = ts.lo_t, hi_t = ts.hi_t;
   const int qN = ts.qN;
@@ -490,9 +501,11 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
   const int b = ts.b, qa = ts.qa;
   const int pa = kRing ? ts.pa : b - 1;
   const int qb = qa + 1;
-  const int Q = d + 2;
+  // slots of the lambda history: the power of two from d + 2 on
+  const int Q = (1 << (32 - __builtin_clz(d + 1))) - 1;
   F* ha = hist[w][0];
   F* hb = hist[w][1];
+  // eval[w][.][k - k0]: u_a(k) and u_b(k);
   // edly[w][0][k - k0]: u_{lo(b)}(k - dR), the right read of a's last point;
   // edly[w][1][k - k0]: u_{lo(b)-1}(k - dL), the left read of b's first point;
   // pull[w][0][k - k0], pull[w][1][k - k0]: max(k - dL, 0), max(k - dR, 0)
@@ -501,8 +514,8 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
     // of its steps can reach (k+1 .. k+d+1, at most K)
     const int s1 = k0 + steps + d < K ? k0 + steps + d : K;
     for (int s = k0 + steps + lane; s <= s1; s += kWave) {
-      ha[s % Q] = LE[((int64_t)s * P + b) * 2];
-      hb[s % Q] = LE[((int64_t)s * P + b) * 2 + 1];
+      ha[s & Q] = LE[((int64_t)s * P + b) * 2];
+      hb[s & Q] = LE[((int64_t)s * P + b) * 2 + 1];
     }
     // the delays of the launch's steps and of the d steps above it (whose
     // reads can land on them), and the record values the steps read
@@ -514,6 +527,8 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
       pull[w][0][j] = k - dL > 0 ? k - dL : 0;
       pull[w][1][j] = k - dR > 0 ? k - dR : 0;
       if (j < steps) {
+        eval[w][0][j] = E[((int64_t)k * P + b) * 2];
+        eval[w][1][j] = E[((int64_t)k * P + b) * 2 + 1];
         edly[w][0][j] = E[((int64_t)pull[w][1][j] * P + b) * 2 + 1];
         edly[w][1][j] = E[((int64_t)pull[w][0][j] * P + b) * 2];
       }
@@ -523,6 +538,8 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
   const bool own_a = qa >= lo_t && qa < hi_t, own_b = qb >= lo_t && qb < hi_t;
+  // a tile between others: its own points are those from kAdjH to L - kAdjH
+  const bool inner = lo_t == kAdjH && hi_t == L - kAdjH && !left_end && !right_end;
   double g = 0.0, e1 = 0.0, eN = 0.0;
   const double rd = (double)r;
   // the lane's points whose dL/dr terms this tile sums: its own output
@@ -535,35 +552,41 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
       own_mask |= 1u << j;
   }
 
-  // u(k+1) from u(k) = x, as the forward launches compute it
-  auto fwd_step = [&](const F (&x)[M], F (&y)[M], int k) {
+  asm("" : "+v"(r));
+  // u(k+1) from u(k), in c, and the second differences of u(k) (across a
+  // subdomain edge the plain ones); the edge points' values are the record's
+  auto fwd_step = [&](F (&lap)[M], int k, bool step) __attribute__((always_inline)) {
+    const F left = from_lower_lane(c[M - 1]);
+    const F right = from_upper_lane(c[0]);
+    F prev = left;
 #pragma unroll
-    for (int j = 0; j < M; ++j) y[j] = x[j];
-    lane_step<F, M>(y, from_lower_lane(x[M - 1]), from_upper_lane(x[0]), r);
-    if (has_edge) {
-      const F ua = read_lane(get_point<F, M>(x, qa % M), qa / M);
-      const F ual = qa >= 1 ? read_lane(get_point<F, M>(x, (qa - 1) % M), (qa - 1) / M) : F(0);
-      const F ub = qb < L ? read_lane(get_point<F, M>(x, qb % M), qb / M) : F(0);
-      const F ubr = qb + 1 < L ? read_lane(get_point<F, M>(x, (qb + 1) % M), (qb + 1) / M) : F(0);
-      const F rb = edly[w][0][k - k0], la = edly[w][1][k - k0];
-      set_point<F, M>(y, qa % M, lane == qa / M, eq3_step(ual, ua, rb, r));
-      if (qb < L) set_point<F, M>(y, qb % M, lane == qb / M, eq3_step(la, ub, ubr, r));
+    for (int j = 0; j < M; ++j) {
+      const F x = c[j];
+      const F nx = j + 1 < M ? c[j + 1] : right;
+      lap[j] = fma_of(F(-2), x, prev + nx);
+      c[j] = fma_of(r, lap[j], x);
+      prev = x;
     }
-    if (left_end) y[0] = (lane == 0) ? c1 : y[0];
-    if (right_end) set_point<F, M>(y, jN, lane == lN, cN);
+    if (!step) return;
+    if (has_edge) {
+      set_point<F, M>(c, qa % M, lane == qa / M, eval[w][0][k + 1 - k0]);
+      if (qb < L) set_point<F, M>(c, qb % M, lane == qb / M, eval[w][1][k + 1 - k0]);
+    }
+    if (left_end) c[0] = (lane == 0) ? c1 : c[0];
+    if (right_end) set_point<F, M>(c, jN, lane == lN, cN);
   };
 
-  // lambda(k) from lambda(k+1) (in l) and u(k) = uc
-  auto bwd_step = [&](const F (&uc)[M], int k) {
-    F la1 = F(0), lal1 = F(0), lb1 = F(0), lbr1 = F(0), ua = F(0), ub = F(0);
+  // lambda(k+1) of the edge points
+  F la1 = F(0), lb1 = F(0);
+  if (has_edge) {
+    la1 = read_lane(get_point<F, M>(l, qa % M), qa / M);
+    if (qb < L) lb1 = read_lane(get_point<F, M>(l, qb % M), qb / M);
+  }
+  // lambda(k) from lambda(k+1), in l; lap: the second differences of u(k)
+  auto bwd_step = [&](const F (&lap)[M], int k) __attribute__((always_inline)) {
+    F lal1 = F(0), lbr1 = F(0);
     if (has_edge) {
-      la1 = read_lane(get_point<F, M>(l, qa % M), qa / M);
-      ua = read_lane(get_point<F, M>(uc, qa % M), qa / M);
       if (qa >= 1) lal1 = read_lane(get_point<F, M>(l, (qa - 1) % M), (qa - 1) / M);
-      if (qb < L) {
-        lb1 = read_lane(get_point<F, M>(l, qb % M), qb / M);
-        ub = read_lane(get_point<F, M>(uc, qb % M), qb / M);
-      }
       if (qb + 1 < L) lbr1 = read_lane(get_point<F, M>(l, (qb + 1) % M), (qb + 1) / M);
     }
     if (own_1) e1 += rd * (double)read_lane(l[1 % M], 1 / M);
@@ -571,14 +594,26 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
     // dL/dr with the plain Laplacians over the tile's own points: the lane's
     // terms of this step summed in the state precision (two chains), then
     // added to the double total
-    const F ul = from_lower_lane(uc[M - 1]), ur = from_upper_lane(uc[0]);
-    {
+    if (inner) {
+      // the lanes that hold the tile's first and last own point start and stop there
+      F acc[2] = {F(0), F(0)}, sum = F(0);
+#pragma unroll
+      for (int j = 0; j < M; ++j) {
+        if (j > 0 && j == kAdjH % M) {
+          acc[0] = lane == kAdjH / M ? F(0) : acc[0];
+          acc[1] = lane == kAdjH / M ? F(0) : acc[1];
+        }
+        if (j == (L - kAdjH) % M) sum = acc[0] + acc[1];
+        acc[j & 1] = fma_of(l[j], lap[j], acc[j & 1]);
+      }
+      sum = lane == (L - kAdjH) / M ? sum : acc[0] + acc[1];
+      g += (double)(lane >= kAdjH / M && lane <= (L - kAdjH) / M ? sum : F(0));
+    } else {
       F acc[2] = {F(0), F(0)};
 #pragma unroll
       for (int j = 0; j < M; ++j) {
-        const F uL = j > 0 ? uc[j - 1] : ul, uR = j + 1 < M ? uc[j + 1] : ur;
         const F lm = ((own_mask >> j) & 1u) ? l[j] : F(0);
-        acc[j & 1] = fma_of(lm, fma_of(F(-2), uc[j], uL + uR), acc[j & 1]);
+        acc[j & 1] = fma_of(lm, lap[j], acc[j & 1]);
       }
       g += (double)(acc[0] + acc[1]);
     }
@@ -599,6 +634,7 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
       const int kmax = k + d < K - 1 ? k + d : K - 1;
       // the delayed Laplacians of the edge points, as corrections of the plain ones
       const F uRd = edly[w][0][k - k0], uLd = edly[w][1][k - k0];
+      const F ua = eval[w][0][k - k0], ub = eval[w][1][k - k0];
       if (lane == 0) {
         if (own_a) g += (double)la1 * ((double)uRd - (double)ub);
         if (own_b) g += (double)lb1 * ((double)uLd - (double)ua);
@@ -615,8 +651,8 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
         const bool in = kk <= kmax;
         const bool hit_a = in && pull[w][0][kk - k0] == k;
         const bool hit_b = in && pull[w][1][kk - k0] == k;
-        const F vb = (in && kk > k) ? hb[(kk + 1) % Q] : lb1;  // lambda_b(kk+1)
-        const F va = (in && kk > k) ? ha[(kk + 1) % Q] : la1;  // lambda_a(kk+1)
+        const F vb = (in && kk > k) ? hb[(kk + 1) & Q] : lb1;  // lambda_b(kk+1)
+        const F va = (in && kk > k) ? ha[(kk + 1) & Q] : la1;  // lambda_a(kk+1)
         for (uint64_t m = __ballot(hit_a); m; m &= m - 1)
           nba += read_lane(vb, __builtin_ctzll(m));
         for (uint64_t m = __ballot(hit_b); m; m &= m - 1)
@@ -627,9 +663,11 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
       const F nb = fma_of(r, fma_of(F(-2), lb1, nbb), lb1);
       set_point<F, M>(l, qa % M, lane == qa / M, na);
       if (qb < L) set_point<F, M>(l, qb % M, lane == qb / M, nb);
+      la1 = na;
+      lb1 = nb;
       if (lane == 0) {
-        ha[k % Q] = na;
-        hb[k % Q] = nb;
+        ha[k & Q] = na;
+        hb[k & Q] = nb;
         if (own_a) LE[((int64_t)k * P + b) * 2] = na;
         if (own_b) LE[((int64_t)k * P + b) * 2 + 1] = nb;
       }
@@ -642,32 +680,26 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
     if (right_end) set_point<F, M>(l, jN, lane == lN, F(0));
   };
 
-  // groups of up to G steps from the top: the stored state at the group's
-  // bottom, the states above it recomputed, then the transpose steps
-  // downwards; the next group's stored state is loaded into the top state's
-  // registers once its step is done (three steps of work hide the load)
-  const int ktop = k0 + steps - 1;
-  int k4 = kc + (ktop - kc) / G * G;
-  F s0[M], s1[M], s2[M], s3[M];
-  load_tile<F, M, kRing>(s0, stored(k4), base, q0, L, N, aligned != 0);
-  for (int k = ktop; k >= k0;) {
-    const int k4n = k4 - G;
-    const int n = k - k4 + 1;
-    static_assert(G == 4, "the group is written out for four states");
-    if (n >= 2) fwd_step(s0, s1, k4);
-    if (n >= 3) fwd_step(s1, s2, k4 + 1);
-    if (n >= 4) fwd_step(s2, s3, k4 + 2);
-    if (n >= 4) bwd_step(s3, k4 + 3);
-    if (k4n >= k0) load_tile<F, M, kRing>(s3, stored(k4n), base, q0, L, N, aligned != 0);
-    if (n >= 3) bwd_step(s2, k4 + 2);
-    if (n >= 2) bwd_step(s1, k4 + 1);
-    bwd_step(s0, k4);
-    k = k4 - 1;
-    k4 = k4n;
-    if (k >= k0) {
+  // forward to the bottom of the top group, then the groups from the top
+  F lap[G][M];
+  const int groups = (steps + G - 1) / G;
+  for (int g0 = 0; g0 + 1 < groups; ++g0) {
 #pragma unroll
-      for (int j = 0; j < M; ++j) s0[j] = s3[j];
+    for (int j = 0; j < M; ++j) kept[w][g0][j][lane] = c[j];
+    for (int i = 0; i < G; ++i) fwd_step(lap[0], k0 + g0 * G + i, true);
+  }
+  for (int g0 = groups - 1; g0 >= 0; --g0) {
+    const int kb = k0 + g0 * G, n = min(G, steps - g0 * G);
+    if (g0 != groups - 1) {
+#pragma unroll
+      for (int j = 0; j < M; ++j) c[j] = kept[w][g0][j][lane];
     }
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+      if (i < n) fwd_step(lap[i], kb + i, i + 1 < n);
+#pragma unroll
+    for (int i = G - 1; i >= 0; --i)
+      if (i < n) bwd_step(lap[i], kb + i);
   }
   store_points<F, M>(l, lam_out, base + q0, q0, lo_t, hi_t, aligned != 0 && base >= 0);
   for (int off = kWave / 2; off > 0; off >>= 1) g += __shfl_xor(g, off, kWave);
@@ -855,100 +887,85 @@ int async_tiled_depth() { return kTileT; }
 
 template <typename F, bool kRing>
 static void lockstep_tiled_launch(const AsyncAdjStep& a, const TileGeom& g, const void* in,
-                                  void* out, void* states, int64_t stride, int kc, int k0,
-                                  int steps, int record, int aligned, hipStream_t s) {
+                                  void* out, int k0, int steps, int record, int aligned,
+                                  hipStream_t s) {
   hipLaunchKernelGGL((async_lockstep_tiled_kernel<F, kRing>),
                      dim3((unsigned)((g.tiles_per_rod + kAdjWaves - 1) / kAdjWaves)),
-                     dim3(kAdjWaves * kWave), 0, s, (const F*)in, (F*)out, (F*)states, stride,
-                     kc, (F*)a.E, a.ord_lock, a.N, a.P, k0, steps, a.d, a.seed, a.sched, (F)a.r, (F)a.c1,
+                     dim3(kAdjWaves * kWave), 0, s, (const F*)in, (F*)out, (F*)a.E,
+                     a.ord_lock, a.N, a.P, k0, steps, a.d, a.seed, a.sched, (F)a.r, (F)a.c1,
                      (F)a.cN, g.tiles_per_rod, g.H, (double)a.P / (double)a.N, record, aligned);
 }
 
-hipError_t launch_async_lockstep_tiled(const AsyncAdjStep& a, const void* in, void* out,
-                                       void* states, int64_t stride, int kc, int k0, int steps,
-                                       int record, hipStream_t s) {
+hipError_t launch_async_lockstep_tiled(const AsyncAdjStep& a, const void* in, void* out, int k0,
+                                       int steps, int record, hipStream_t s) {
   const TileGeom g = a.ring ? ring_geometry(a.dtype, kTileM, kTileT, a.N)
                             : tile_geometry(a.dtype, kTileM, kTileT, a.N);
   if (steps < 1 || steps > g.H || steps > kTileT || g.tiles_per_rod <= 0 || g.Wout <= 0 ||
-      !async_tiled_applies(a.N, a.P, a.d) || (a.ring && a.P < 2) || (states && k0 < kc))
+      !async_tiled_applies(a.N, a.P, a.d) || (a.ring && a.P < 2))
     return hipErrorInvalidValue;
-  const int aligned = is_aligned16(in) && (!out || is_aligned16(out)) &&
-                      (!states || is_aligned16(states)) && stride % 4 == 0;
+  const int aligned = is_aligned16(in) && is_aligned16(out);
   if (a.dtype == 0)
-    a.ring ? lockstep_tiled_launch<float, true>(a, g, in, out, states, stride, kc, k0, steps,
-                                                record, aligned, s)
-           : lockstep_tiled_launch<float, false>(a, g, in, out, states, stride, kc, k0, steps,
-                                                 record, aligned, s);
+    a.ring ? lockstep_tiled_launch<float, true>(a, g, in, out, k0, steps, record, aligned, s)
+           : lockstep_tiled_launch<float, false>(a, g, in, out, k0, steps, record, aligned, s);
   else
-    a.ring ? lockstep_tiled_launch<double, true>(a, g, in, out, states, stride, kc, k0, steps,
-                                                 record, aligned, s)
-           : lockstep_tiled_launch<double, false>(a, g, in, out, states, stride, kc, k0, steps,
-                                                  record, aligned, s);
+    a.ring ? lockstep_tiled_launch<double, true>(a, g, in, out, k0, steps, record, aligned, s)
+           : lockstep_tiled_launch<double, false>(a, g, in, out, k0, steps, record, aligned, s);
   return hipGetLastError();
 }
-
-int async_tiled_store_every() { return kStoreEvery; }
 
 hipError_t launch_async_tiled_order(const AsyncAdjStep& a, int* ord_lock, int* ord_adj,
                                     hipStream_t s) {
   if (!async_tiled_applies(a.N, a.P, a.d) || (a.ring && a.P < 2)) return hipErrorInvalidValue;
   const double pscale = (double)a.P / (double)a.N;
   for (int which = 0; which < 2; ++which) {
-    const int T = which == 0 ? kTileT : kAdjT;
-    const TileGeom g = a.ring ? ring_geometry(a.dtype, kTileM, T, a.N)
-                              : tile_geometry(a.dtype, kTileM, T, a.N);
+    const int T = which == 0 ? kTileT : kAdjT, M = which == 0 ? kTileM : adjoint_m(a.dtype);
+    const TileGeom g = a.ring ? ring_geometry(a.dtype, M, T, a.N)
+                              : tile_geometry(a.dtype, M, T, a.N);
     if (g.tiles_per_rod <= 0 || g.Wout <= 0) return hipErrorInvalidValue;
     int* ord = which == 0 ? ord_lock : ord_adj;
     if (a.ring)
       hipLaunchKernelGGL(tile_order_kernel<true>, dim3(1), dim3(256), 0, s, ord, g.tiles_per_rod,
-                         kWave * kTileM, g.H, a.N, a.P, pscale);
+                         kWave * M, g.H, a.N, a.P, pscale);
     else
       hipLaunchKernelGGL(tile_order_kernel<false>, dim3(1), dim3(256), 0, s, ord, g.tiles_per_rod,
-                         kWave * kTileM, g.H, a.N, a.P, pscale);
+                         kWave * M, g.H, a.N, a.P, pscale);
   }
   return hipGetLastError();
 }
 
 int64_t async_tiled_tiles(int dtype, int64_t N) {
-  return std::max(tile_geometry(dtype, kTileM, kAdjT, N).tiles_per_rod,
-                  ring_geometry(dtype, kTileM, kAdjT, N).tiles_per_rod);
+  const int M = adjoint_m(dtype);  // no larger a tile than the lockstep's, with a wider halo
+  return std::max(tile_geometry(dtype, M, kAdjT, N).tiles_per_rod,
+                  ring_geometry(dtype, M, kAdjT, N).tiles_per_rod);
 }
 
 template <typename F, bool kRing>
 static void adjoint_tiled_launch(const AsyncAdjStep& a, const TileGeom& g, const void* lam_in,
-                                 void* lam_out, const void* u_first, const void* st_base,
-                                 int64_t stride, int kc, int k0, int steps, int aligned,
+                                 void* lam_out, const void* u, int k0, int steps, int aligned,
                                  hipStream_t s) {
   hipLaunchKernelGGL((async_adjoint_tiled_kernel<F, kRing>),
                      dim3((unsigned)((g.tiles_per_rod + kAdjWaves - 1) / kAdjWaves)),
                      dim3(kAdjWaves * kWave), 0, s, (const F*)lam_in, (F*)lam_out,
-                     (const F*)u_first, (const F*)st_base, stride, kc, (const F*)a.E,
-                     (F*)a.LE, a.ord_adj, a.N, a.P, k0, steps, a.K, a.d, a.seed, a.sched, (F)a.r, (F)a.c1,
+                     (const F*)u, (const F*)a.E, (F*)a.LE, a.ord_adj, a.N, a.P, k0, steps, a.K, a.d, a.seed, a.sched, (F)a.r, (F)a.c1,
                      (F)a.cN, g.tiles_per_rod, g.H, (double)a.P / (double)a.N, a.part, a.ends,
                      aligned);
 }
 
 hipError_t launch_async_adjoint_tiled(const AsyncAdjStep& a, const void* lam_in, void* lam_out,
-                                      const void* u_first, const void* st_base, int64_t stride,
-                                      int kc, int k0, int steps, hipStream_t s) {
-  const TileGeom g = a.ring ? ring_geometry(a.dtype, kTileM, kAdjT, a.N)
-                            : tile_geometry(a.dtype, kTileM, kAdjT, a.N);
-  if (steps < 1 || steps > kTileT || steps + kStoreEvery - 1 > g.H || g.tiles_per_rod <= 0 ||
-      g.Wout <= 0 || !async_tiled_applies(a.N, a.P, a.d) || (a.ring && a.P < 2) || k0 < kc ||
-      (k0 - kc) % kStoreEvery != 0)
+                                      const void* u, int k0, int steps, hipStream_t s) {
+  const int M = adjoint_m(a.dtype);
+  const TileGeom g = a.ring ? ring_geometry(a.dtype, M, kAdjT, a.N)
+                            : tile_geometry(a.dtype, M, kAdjT, a.N);
+  if (steps < 1 || steps > kTileT || steps + 3 > g.H || g.tiles_per_rod <= 0 || g.Wout <= 0 ||
+      !async_tiled_applies(a.N, a.P, a.d) || (a.ring && a.P < 2))
     return hipErrorInvalidValue;
-  const int aligned = is_aligned16(lam_in) && is_aligned16(lam_out) && is_aligned16(u_first) &&
-                      is_aligned16(st_base) && stride % 4 == 0;
+  const int aligned = is_aligned16(lam_in) && is_aligned16(lam_out) && is_aligned16(u);
   if (a.dtype == 0)
-    a.ring ? adjoint_tiled_launch<float, true>(a, g, lam_in, lam_out, u_first, st_base, stride,
-                                               kc, k0, steps, aligned, s)
-           : adjoint_tiled_launch<float, false>(a, g, lam_in, lam_out, u_first, st_base, stride,
-                                                kc, k0, steps, aligned, s);
+    a.ring ? adjoint_tiled_launch<float, true>(a, g, lam_in, lam_out, u, k0, steps, aligned, s)
+           : adjoint_tiled_launch<float, false>(a, g, lam_in, lam_out, u, k0, steps, aligned, s);
   else
-    a.ring ? adjoint_tiled_launch<double, true>(a, g, lam_in, lam_out, u_first, st_base, stride,
-                                                kc, k0, steps, aligned, s)
-           : adjoint_tiled_launch<double, false>(a, g, lam_in, lam_out, u_first, st_base, stride,
-                                                 kc, k0, steps, aligned, s);
+    a.ring ? adjoint_tiled_launch<double, true>(a, g, lam_in, lam_out, u, k0, steps, aligned, s)
+           : adjoint_tiled_launch<double, false>(a, g, lam_in, lam_out, u, k0, steps, aligned, s);
   return hipGetLastError();
 }
 

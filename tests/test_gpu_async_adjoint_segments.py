@@ -1,0 +1,59 @@
+"""Gradients through the emulated asynchronous run in segments of 32 steps
+(subdomains longer than a tile): u(K) and dL/du0 bit for bit those of one launch
+per step, with subdomain edges at every kind of place in a tile, runs that end
+inside a group of 8 steps or with a segment of one step, and runs of more
+segments than the workspace keeps states for (the others replayed).  The scalar
+gradients, whose terms the two sum in another grouping (a lane's terms of a step
+in the state precision), agree to the state tolerance times the oracle's
+magnitude of each sum."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from paper_1510_08982_amd import abi
+from paper_1510_08982_amd.heat import AsyncPlan
+from _helpers import np_dtype, print_case, tol_for, torch_dtype
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # (dt, N, P, d, K, checkpoint stride)
+    ("f32", 40000, 37, 7, 97, 0), ("f64", 40000, 37, 7, 105, 0),   # edges all over the tiles
+    ("f32", 66600, 64, 255, 70, 0), ("f64", 3100, 2, 1, 33, 0),
+    ("f64", 9999, 1, 3, 40, 0), ("f32", 2049, 2, 0, 31, 0),
+    ("f32", 2100, 2, 5, 4500, 0), ("f64", 2100, 2, 3, 4500, 0),    # stretches of two segments
+    ("f64", 2100, 2, 3, 20000, 0),                                 # and of three
+    ("f32", 5000, 2, 2, 300, 1), ("f64", 5000, 2, 2, 300, 300),    # any checkpoint stride
+]
+
+
+@pytest.mark.parametrize("ring", [False, True])
+@pytest.mark.parametrize("dt,N,P,d,K,stride", CASES)
+def test_segments_are_the_per_step_launches(dt, N, P, d, K, stride, ring):
+    if ring and P < 2:
+        pytest.skip("a ring has two subdomains or more")
+    f = np_dtype(dt)
+    rng = np.random.default_rng(N + K)
+    u0, gK = (torch.from_numpy(workloads.as_dtype(rng.uniform(-1, 1, N), f).astype(f)).to("cuda")
+              for _ in range(2))
+    print_case(test="async_adjoint_segments", dt=dt, N=N, P=P, d=d, K=K, stride=stride, ring=ring)
+    c1, cN = (0.0, 0.0) if ring else (0.25, -0.5)
+    got = []
+    for kernel in (abi.HEAT1D_SYNC_AUTO, abi.HEAT1D_SYNC_STEP):
+        opts = dict(sync_kernel=kernel)
+        if stride:
+            opts["ckpt_stride"] = stride
+        with AsyncPlan(N, P, torch_dtype(dt), max_delay=max(d, 1), periodic=ring,
+                       **opts) as plan:
+            got.append([x.cpu() for x in plan.adjoint(u0, gK, 0.37, c1, cN, K, d, 3)])
+    (gu, gr, g1, gN, uK), (hu, hr, h1, hN, vK) = got
+    assert torch.equal(gu, hu) and torch.equal(uK, vK)
+    u, g = (x.cpu().numpy().astype(np.float64) for x in (u0, gK))
+    r, a, b = (workloads.as_dtype(x, f) for x in (0.37, c1, cN))
+    if ring:
+        scales = [oracle.async_adjoint_periodic(u, g, r, K, P, d, 3, with_scale=True)[2], 0, 0]
+    else:
+        scales = oracle.async_adjoint(u, g, r, a, b, K, P, d, 3, with_scales=True)[4]
+    for x, y, sc in zip((gr, g1, gN), (hr, h1, hN), scales):
+        assert abs(float(x) - float(y)) <= tol_for(dt) * sc, (float(x), float(y), sc)

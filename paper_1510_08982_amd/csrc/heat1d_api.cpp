@@ -388,10 +388,10 @@ AsyncAdjLayout async_adjoint_layout(heat1d_plan_t p, int64_t K, int P) {
   a.LE_off = a.E_off + a.rec_bytes;
   a.lo_off = a.LE_off + a.rec_bytes;
   a.part_off = a.lo_off + align_up((size_t)(P + 1) * 8);
-  a.nparts = std::max<int64_t>(async_adjoint_blocks(p->N), async_tiled_tiles(p->dtype, p->N));
+  a.nparts = std::max<int64_t>(async_adjoint_blocks(p->N), async_tiled_tiles(p->dtype, p->N, P));
   a.ends_off = a.part_off + align_up((size_t)a.nparts * 8);
   a.ord_off = a.ends_off + align_up(16);
-  a.ord_bytes = align_up((size_t)std::max<int64_t>(async_tiled_tiles(p->dtype, p->N), 0) * 4);
+  a.ord_bytes = align_up((size_t)std::max<int64_t>(async_tiled_tiles(p->dtype, p->N, P), 0) * 4);
   a.total = a.ord_off + 2 * a.ord_bytes;
   return a;
 }
@@ -1466,7 +1466,7 @@ int heat1d_run_async_adjoint(heat1d_plan_t p, const void* u0, const void* gK, do
                   : launch_impose_ends(p->dtype, u0, u0s, N, 1, c1, cN, s));
   HEAT1D_TRY(launch_async_edges(p->dtype, u0s, A.E, A.lo, P, N, A.ring, s));
   // Register tiles of up to T steps per launch where every subdomain is
-  // longer than a tile (ring tiles on a ring; opts.sync_kernel =
+  // long enough (ring tiles on a ring; opts.sync_kernel =
   // HEAT1D_SYNC_STEP asks for one launch per step); both give the same values
   // bit for bit.
   const bool tiled = p->opts.sync_kernel != HEAT1D_SYNC_STEP && async_tiled_applies(N, P, d);

@@ -154,7 +154,7 @@ hipError_t launch_async_edges(int dtype, const void* u, void* Ek, const int64_t*
 hipError_t launch_async_lockstep(const AsyncAdjStep& a, const void* cur, void* nxt, int k,
                                  int record, hipStream_t s);
 // The same steps on register tiles, at most async_tiled_depth() per launch,
-// for rods (or rings, P >= 2) whose subdomains are longer than one tile (bit
+// for rods (or rings, P >= 2) whose subdomains have 144 points or more (bit
 // for bit the per-step launches): from the state `in` of step k0, `steps` steps,
 // the last state to `out`.
 bool async_tiled_applies(int64_t N, int P, int d);
@@ -165,10 +165,10 @@ hipError_t launch_async_lockstep_tiled(const AsyncAdjStep& a, const void* in, vo
 // register tiles, lambda in registers; u = u(k0), from which each tile steps
 // forward itself; lambda bit for bit that of the per-step kernel; dL/dr summed per tile into part[t]
 // (async_tiled_tiles slots), dL/dc1 and dL/dcN into ends.
-int64_t async_tiled_tiles(int dtype, int64_t N);
+int64_t async_tiled_tiles(int dtype, int64_t N, int P);
 // The order in which the tiled launches take their tiles: those holding a
 // subdomain edge (the longest-running) first, then the rest, each in tile
-// order.  ord_lock and ord_adj hold async_tiled_tiles(dtype, N) ints each.
+// order.  ord_lock and ord_adj hold async_tiled_tiles ints each.
 hipError_t launch_async_tiled_order(const AsyncAdjStep& a, int* ord_lock, int* ord_adj,
                                     hipStream_t s);
 hipError_t launch_async_adjoint_tiled(const AsyncAdjStep& a, const void* lam_in, void* lam_out,

@@ -25,6 +25,7 @@
 // lambda(k) (3 s bytes per point); the edge records add 2 values per edge and
 // step.  The tiled launches read and write that once in 32 steps.
 #include <algorithm>
+#include <type_traits>
 
 #include "heat1d_delays.h"
 #include "heat1d_device.h"
@@ -275,6 +276,67 @@ __device__ __forceinline__ TileSetup tile_setup(int64_t t, int64_t tiles, int L,
   return s;
 }
 
+// Tiles of rods and rings whose subdomains are no longer than a tile: the rod is
+// cut at the subdomains' middles into P + 1 pieces (the first and last half as
+// long), so that a piece holds one edge at most, about its middle, and each piece
+// into `parts` tiles of kFitOwn own points at most.  With kAdjH points more at
+// each end a tile still reaches no second edge (kFitMin); what lies beyond them
+// up to L is not used.  Cuts are multiples of 4, for whole vectors.
+// A launch of 32 steps is bound by the chain of a tile's edge where the tiles fit
+// the chip at once (52 us), by its vector arithmetic in larger rods.  FP64, d = 14,
+// N = 231586 in 843 subdomains, K = 500: 19.8 -> 1.33 ms against a launch a step
+// (which waits for each delayed value in turn); FP32, N = 2^24 in subdomains of
+// 300, d = 4, K = 128: 21.0 -> 8.4 ms.
+constexpr int kFitM = 8;
+constexpr int kFitOwn = kWave * kFitM - 2 * kAdjH;
+// Shortest subdomain: a piece's ends are at least (144 - 4) / 2 points from the
+// edges before and behind it, more than kAdjH.  Three and a half times its own
+// points are work there: N = 2^24, K = 128, FP32 takes 17.2 ms against 18.3.
+constexpr int kFitMin = 144;
+
+__device__ __forceinline__ int64_t fit_cut(int64_t j, int64_t N, int P) {
+  return j <= 0 ? 0 : j > P ? N : ((part_lo(j - 1, N, P) + part_lo(j, N, P)) / 2) & ~(int64_t)3;
+}
+
+template <bool kRing>
+__device__ __forceinline__ TileSetup fit_setup(int64_t t, int parts, int64_t N, int P) {
+  TileSetup s;
+  constexpr int L = kWave * kFitM;
+  const int64_t j = t / parts;
+  const int64_t c0 = fit_cut(j, N, P), c1 = fit_cut(j + 1, N, P);
+  const int64_t len = ((c1 - c0 + parts - 1) / parts + 3) & ~(int64_t)3;
+  const int64_t first = c0 + (t - j * parts) * len, last = min(first + len, c1);
+  s.base = first - kAdjH;
+  if (!kRing && s.base < 0) s.base = 0;
+  s.lo_t = (int)(first - s.base);
+  s.hi_t = (int)(last - s.base);  // <= lo_t: a part with no points of its own
+  s.left_end = !kRing && s.base == 0;
+  const int64_t qN64 = N - 1 - s.base;
+  s.right_end = !kRing && qN64 < L;
+  s.qN = s.right_end ? (int)qN64 : 0;
+  s.has_edge = false;
+  s.b = s.pa = s.qa = 0;
+  // the edge of piece j is that of subdomains j-1 and j; the pieces at the
+  // ring's seam both have edge 0
+  const bool seam = j == 0 || j == P;
+  if (P > 1 && (kRing || !seam)) {
+    const int64_t at = (j == P ? N : j == 0 ? 0 : part_lo(j, N, P)) - 1 - s.base;
+    if (at >= s.lo_t - kAdjH - 1 && at >= 0 && at < s.hi_t + kAdjH) {
+      s.has_edge = true;
+      s.b = seam ? 0 : (int)j;
+      s.pa = seam ? P - 1 : (int)j - 1;
+      s.qa = (int)at;
+    }
+  }
+  s.b = uniform(s.b);
+  s.pa = uniform(s.pa);
+  s.qa = uniform(s.qa);
+  s.lo_t = uniform(s.lo_t);
+  s.hi_t = uniform(s.hi_t);
+  s.qN = uniform(s.qN);
+  return s;
+}
+
 // The lane's M points of a tile from local point 0 at index `base`: whole
 // vectors inside the rod, taken modulo N on a ring tile that crosses the seam.
 template <typename F, int M, bool kRing>
@@ -335,13 +397,12 @@ __global__ __launch_bounds__(256) void tile_order_kernel(int* __restrict__ order
   }
 }
 
-template <typename F, bool kRing>
+template <typename F, int M, bool kRing, bool kFit>
 __global__ __launch_bounds__(kAdjWaves * kWave) void async_lockstep_tiled_kernel(
     const F* __restrict__ in, F* __restrict__ out, F* __restrict__ E,
     const int* __restrict__ order, int64_t N, int P, int k0, int steps, int d,
-    uint64_t seed, int sched, F r, F c1, F cN, int64_t tiles, int H, double pscale, int record,
-    int aligned) {
-  constexpr int M = kTileM;
+    uint64_t seed, int sched, F r, F c1, F cN, int64_t tiles, int H, int parts, double pscale,
+    int record, int aligned) {
   constexpr int L = kWave * M;
   __shared__ F hist[kAdjWaves][2][kHistQ];
   __shared__ int pull[kAdjWaves][2][kTileT];  // max(k - dL, 0), max(k - dR, 0)
@@ -349,14 +410,19 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_lockstep_tiled_kernel
   const int w = threadIdx.x / kWave;
   const int64_t v = (int64_t)blockIdx.x * kAdjWaves + w;
   if (v >= tiles) return;
-  const int64_t t = order[v];
+  const int64_t t = kFit ? v : order[v];
+  TileSetup ts;
+  if constexpr (kFit) {
+    ts = fit_setup<kRing>(t, parts, N, P);
+    if (ts.lo_t >= ts.hi_t) return;
+  }
   // the tile's first point (as tile_setup places it), so the loads go out first
-  const int64_t base = kRing ? t * (L - 2 * H) - H : t * (L - 2 * H);
+  const int64_t base = kFit ? ts.base : kRing ? t * (L - 2 * H) - H : t * (L - 2 * H);
   const int q0 = lane * M;
   const bool st_aligned = aligned != 0 && base >= 0;
   F u[M];
   load_tile<F, M, kRing>(u, in, base, q0, L, N, aligned != 0);
-  const TileSetup ts = tile_setup<kRing>(t, tiles, L, H, N, P, pscale);
+  if constexpr (!kFit) ts = tile_setup<kRing>(t, tiles, L, H, N, P, pscale);
   const bool left_end = ts.left_end, right_end = ts.right_end;
   const int lo_t = ts.lo_t, hi_t = ts.hi_t;
   const int qN = ts.qN;
@@ -457,15 +523,17 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_lockstep_tiled_kernel
 // those tiles are alone, N = 2^18); with the second differences kept instead of
 // the states, from 269 to 242 us.  FP64 takes 8 points a lane, so that a group
 // fits the same registers: N = 2^22, K = 1000: 7.91 -> 5.76 ms.
-template <typename F, bool kRing>
+template <typename F, int M, bool kRing, bool kFit>
 __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
     const F* __restrict__ lam_in, F* __restrict__ lam_out, const F* __restrict__ u0,
-    const F* __restrict__ E, F* __restrict__ LE, const int* __restrict__ order, int64_t N, int P, int k0, int steps,
-    int K, int d, uint64_t seed, int sched, F r, F c1, F cN, int64_t tiles, int H, double pscale,
-    double* __restrict__ part, double* __restrict__ ends, int aligned) {
-  constexpr int M = kAdjM<F>;
+    const F* __restrict__ E, F* __restrict__ LE, const int* __restrict__ order, int64_t N,
+    int P, int k0, int steps, int K, int d, uint64_t seed, int sched, F r, F c1, F cN,
+    int64_t tiles, int H, int parts, double pscale, double* __restrict__ part, double* __restrict__ ends, int aligned) {
   constexpr int L = kWave * M;
   constexpr int G = kGroup;
+  // dL/dr of the fitted tiles is summed as the per-step kernel sums it, every
+  // term in double from a second difference in double
+  using Lap = std::conditional_t<kFit, double, F>;
   __shared__ F kept[kAdjWaves][kTileT / G - 1][M][kWave];
   __shared__ F hist[kAdjWaves][2][kAdjHist];
   // per edge tile, for the launch's steps: the edge points' values and the
@@ -478,14 +546,19 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
   const int w = threadIdx.x / kWave;
   const int64_t v = (int64_t)blockIdx.x * kAdjWaves + w;
   if (v >= tiles) return;
-  const int64_t t = order[v];
-  const int64_t base = kRing ? t * (L - 2 * H) - H : t * (L - 2 * H);
+  const int64_t t = kFit ? v : order[v];
+  TileSetup ts;
+  if constexpr (kFit) {
+    ts = fit_setup<kRing>(t, parts, N, P);
+    if (ts.lo_t >= ts.hi_t) return;
+  }
+  const int64_t base = kFit ? ts.base : kRing ? t * (L - 2 * H) - H : t * (L - 2 * H);
   const int q0 = lane * M;
   F c[M];
   F l[M];
   load_tile<F, M, kRing>(c, u0, base, q0, L, N, aligned != 0);
   load_tile<F, M, kRing>(l, lam_in, base, q0, L, N, aligned != 0);
-  const TileSetup ts = tile_setup<kRing>(t, tiles, L, H, N, P, pscale);
+  if constexpr (!kFit) ts = tile_setup<kRing>(t, tiles, L, H, N, P, pscale);
   const bool left_end = ts.left_end, right_end = ts.right_end;
   const int lo_t = ts.lo_t, hi_t = ts.hi_t;
   const int qN = ts.qN;
@@ -539,7 +612,7 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
   }
   const bool own_a = qa >= lo_t && qa < hi_t, own_b = qb >= lo_t && qb < hi_t;
   // a tile between others: its own points are those from kAdjH to L - kAdjH
-  const bool inner = lo_t == kAdjH && hi_t == L - kAdjH && !left_end && !right_end;
+  const bool inner = !kFit && lo_t == kAdjH && hi_t == L - kAdjH && !left_end && !right_end;
   double g = 0.0, e1 = 0.0, eN = 0.0;
   const double rd = (double)r;
   // the lane's points whose dL/dr terms this tile sums: its own output
@@ -555,7 +628,7 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
   asm("" : "+v"(r));
   // u(k+1) from u(k), in c, and the second differences of u(k) (across a
   // subdomain edge the plain ones); the edge points' values are the record's
-  auto fwd_step = [&](F (&lap)[M], int k, bool step) __attribute__((always_inline)) {
+  auto fwd_step = [&](Lap (&lap)[M], int k, bool step) __attribute__((always_inline)) {
     const F left = from_lower_lane(c[M - 1]);
     const F right = from_upper_lane(c[0]);
     F prev = left;
@@ -563,8 +636,9 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
     for (int j = 0; j < M; ++j) {
       const F x = c[j];
       const F nx = j + 1 < M ? c[j + 1] : right;
-      lap[j] = fma_of(F(-2), x, prev + nx);
-      c[j] = fma_of(r, lap[j], x);
+      const F second = fma_of(F(-2), x, prev + nx);
+      lap[j] = kFit ? (Lap)prev + (Lap)nx - Lap(2) * (Lap)x : (Lap)second;
+      c[j] = fma_of(r, second, x);
       prev = x;
     }
     if (!step) return;
@@ -583,7 +657,7 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
     if (qb < L) lb1 = read_lane(get_point<F, M>(l, qb % M), qb / M);
   }
   // lambda(k) from lambda(k+1), in l; lap: the second differences of u(k)
-  auto bwd_step = [&](const F (&lap)[M], int k) __attribute__((always_inline)) {
+  auto bwd_step = [&](const Lap (&lap)[M], int k) __attribute__((always_inline)) {
     F lal1 = F(0), lbr1 = F(0);
     if (has_edge) {
       if (qa >= 1) lal1 = read_lane(get_point<F, M>(l, (qa - 1) % M), (qa - 1) / M);
@@ -594,7 +668,13 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
     // dL/dr with the plain Laplacians over the tile's own points: the lane's
     // terms of this step summed in the state precision (two chains), then
     // added to the double total
-    if (inner) {
+    if constexpr (kFit) {
+#pragma unroll
+      for (int j = 0; j < M; ++j) {
+        const F lm = ((own_mask >> j) & 1u) ? l[j] : F(0);
+        g += (double)lm * (double)lap[j];
+      }
+    } else if (inner) {
       // the lanes that hold the tile's first and last own point start and stop there
       F acc[2] = {F(0), F(0)}, sum = F(0);
 #pragma unroll
@@ -681,7 +761,7 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
   };
 
   // forward to the bottom of the top group, then the groups from the top
-  F lap[G][M];
+  Lap lap[G][M];
   const int groups = (steps + G - 1) / G;
   for (int g0 = 0; g0 + 1 < groups; ++g0) {
 #pragma unroll
@@ -879,21 +959,46 @@ hipError_t launch_async_lockstep(const AsyncAdjStep& a, const void* cur, void* n
   return hipGetLastError();
 }
 
+// Longer subdomains than a tile: tiles of one length; else, down to kFitMin, the
+// tiles fitted to them.  Shorter ones take a launch a step: a tile would hold
+// several edges.
+static bool fitted(int64_t N, int P) { return P > 1 && N / P <= (int64_t)kWave * kTileM; }
+
 bool async_tiled_applies(int64_t N, int P, int d) {
-  return d + 2 <= kHistQ && (P == 1 || N / P > (int64_t)kWave * kTileM);
+  return d + 2 <= kHistQ && (P == 1 || N / P >= kFitMin);
 }
+
+// Tiles of a piece (of at most N/P + 1 + 4 points), in whole vectors.
+static int fit_parts(int64_t N, int P) { return (int)((N / P + 5 + kFitOwn - 5) / (kFitOwn - 4)); }
 
 int async_tiled_depth() { return kTileT; }
 
-template <typename F, bool kRing>
-static void lockstep_tiled_launch(const AsyncAdjStep& a, const TileGeom& g, const void* in,
+template <typename F, int M, bool kRing, bool kFit>
+static void lockstep_tiled_launch(const AsyncAdjStep& a, int64_t tiles, int H, const void* in,
                                   void* out, int k0, int steps, int record, int aligned,
                                   hipStream_t s) {
-  hipLaunchKernelGGL((async_lockstep_tiled_kernel<F, kRing>),
-                     dim3((unsigned)((g.tiles_per_rod + kAdjWaves - 1) / kAdjWaves)),
-                     dim3(kAdjWaves * kWave), 0, s, (const F*)in, (F*)out, (F*)a.E,
-                     a.ord_lock, a.N, a.P, k0, steps, a.d, a.seed, a.sched, (F)a.r, (F)a.c1,
-                     (F)a.cN, g.tiles_per_rod, g.H, (double)a.P / (double)a.N, record, aligned);
+  hipLaunchKernelGGL((async_lockstep_tiled_kernel<F, M, kRing, kFit>),
+                     dim3((unsigned)((tiles + kAdjWaves - 1) / kAdjWaves)),
+                     dim3(kAdjWaves * kWave), 0, s, (const F*)in, (F*)out, (F*)a.E, a.ord_lock,
+                     a.N, a.P, k0, steps, a.d, a.seed, a.sched, (F)a.r, (F)a.c1, (F)a.cN, tiles, H,
+                     fit_parts(a.N, a.P), (double)a.P / (double)a.N, record, aligned);
+}
+
+template <typename F>
+static void lockstep_tiled_pick(const AsyncAdjStep& a, const TileGeom& g, const void* in, void* out,
+                                int k0, int steps, int record, int aligned, hipStream_t s) {
+  if (fitted(a.N, a.P)) {
+    const int64_t tiles = (int64_t)(a.P + 1) * fit_parts(a.N, a.P);
+    a.ring ? lockstep_tiled_launch<F, kFitM, true, true>(a, tiles, kAdjH, in, out, k0, steps,
+                                                         record, aligned, s)
+           : lockstep_tiled_launch<F, kFitM, false, true>(a, tiles, kAdjH, in, out, k0, steps,
+                                                          record, aligned, s);
+  } else {
+    a.ring ? lockstep_tiled_launch<F, kTileM, true, false>(a, g.tiles_per_rod, g.H, in, out, k0,
+                                                           steps, record, aligned, s)
+           : lockstep_tiled_launch<F, kTileM, false, false>(a, g.tiles_per_rod, g.H, in, out, k0,
+                                                            steps, record, aligned, s);
+  }
 }
 
 hipError_t launch_async_lockstep_tiled(const AsyncAdjStep& a, const void* in, void* out, int k0,
@@ -905,17 +1010,16 @@ hipError_t launch_async_lockstep_tiled(const AsyncAdjStep& a, const void* in, vo
     return hipErrorInvalidValue;
   const int aligned = is_aligned16(in) && is_aligned16(out);
   if (a.dtype == 0)
-    a.ring ? lockstep_tiled_launch<float, true>(a, g, in, out, k0, steps, record, aligned, s)
-           : lockstep_tiled_launch<float, false>(a, g, in, out, k0, steps, record, aligned, s);
+    lockstep_tiled_pick<float>(a, g, in, out, k0, steps, record, aligned, s);
   else
-    a.ring ? lockstep_tiled_launch<double, true>(a, g, in, out, k0, steps, record, aligned, s)
-           : lockstep_tiled_launch<double, false>(a, g, in, out, k0, steps, record, aligned, s);
+    lockstep_tiled_pick<double>(a, g, in, out, k0, steps, record, aligned, s);
   return hipGetLastError();
 }
 
 hipError_t launch_async_tiled_order(const AsyncAdjStep& a, int* ord_lock, int* ord_adj,
                                     hipStream_t s) {
   if (!async_tiled_applies(a.N, a.P, a.d) || (a.ring && a.P < 2)) return hipErrorInvalidValue;
+  if (fitted(a.N, a.P)) return hipSuccess;  // taken in order: nearly all hold an edge
   const double pscale = (double)a.P / (double)a.N;
   for (int which = 0; which < 2; ++which) {
     const int T = which == 0 ? kTileT : kAdjT, M = which == 0 ? kTileM : adjoint_m(a.dtype);
@@ -933,22 +1037,41 @@ hipError_t launch_async_tiled_order(const AsyncAdjStep& a, int* ord_lock, int* o
   return hipGetLastError();
 }
 
-int64_t async_tiled_tiles(int dtype, int64_t N) {
+int64_t async_tiled_tiles(int dtype, int64_t N, int P) {
+  if (fitted(N, P)) return (int64_t)(P + 1) * fit_parts(N, P);
   const int M = adjoint_m(dtype);  // no larger a tile than the lockstep's, with a wider halo
   return std::max(tile_geometry(dtype, M, kAdjT, N).tiles_per_rod,
                   ring_geometry(dtype, M, kAdjT, N).tiles_per_rod);
 }
 
-template <typename F, bool kRing>
-static void adjoint_tiled_launch(const AsyncAdjStep& a, const TileGeom& g, const void* lam_in,
+template <typename F, int M, bool kRing, bool kFit>
+static void adjoint_tiled_launch(const AsyncAdjStep& a, int64_t tiles, int H, const void* lam_in,
                                  void* lam_out, const void* u, int k0, int steps, int aligned,
                                  hipStream_t s) {
-  hipLaunchKernelGGL((async_adjoint_tiled_kernel<F, kRing>),
-                     dim3((unsigned)((g.tiles_per_rod + kAdjWaves - 1) / kAdjWaves)),
-                     dim3(kAdjWaves * kWave), 0, s, (const F*)lam_in, (F*)lam_out,
-                     (const F*)u, (const F*)a.E, (F*)a.LE, a.ord_adj, a.N, a.P, k0, steps, a.K, a.d, a.seed, a.sched, (F)a.r, (F)a.c1,
-                     (F)a.cN, g.tiles_per_rod, g.H, (double)a.P / (double)a.N, a.part, a.ends,
-                     aligned);
+  hipLaunchKernelGGL((async_adjoint_tiled_kernel<F, M, kRing, kFit>),
+                     dim3((unsigned)((tiles + kAdjWaves - 1) / kAdjWaves)),
+                     dim3(kAdjWaves * kWave), 0, s, (const F*)lam_in, (F*)lam_out, (const F*)u,
+                     (const F*)a.E, (F*)a.LE, a.ord_adj, a.N, a.P, k0, steps, a.K, a.d, a.seed,
+                     a.sched, (F)a.r, (F)a.c1, (F)a.cN, tiles, H, fit_parts(a.N, a.P),
+                     (double)a.P / (double)a.N, a.part, a.ends, aligned);
+}
+
+template <typename F>
+static void adjoint_tiled_pick(const AsyncAdjStep& a, const TileGeom& g, const void* lam_in,
+                               void* lam_out, const void* u, int k0, int steps, int aligned,
+                               hipStream_t s) {
+  if (fitted(a.N, a.P)) {
+    const int64_t tiles = (int64_t)(a.P + 1) * fit_parts(a.N, a.P);
+    a.ring ? adjoint_tiled_launch<F, kFitM, true, true>(a, tiles, kAdjH, lam_in, lam_out, u, k0,
+                                                        steps, aligned, s)
+           : adjoint_tiled_launch<F, kFitM, false, true>(a, tiles, kAdjH, lam_in, lam_out, u, k0,
+                                                         steps, aligned, s);
+  } else {
+    a.ring ? adjoint_tiled_launch<F, kAdjM<F>, true, false>(a, g.tiles_per_rod, g.H, lam_in,
+                                                            lam_out, u, k0, steps, aligned, s)
+           : adjoint_tiled_launch<F, kAdjM<F>, false, false>(a, g.tiles_per_rod, g.H, lam_in,
+                                                             lam_out, u, k0, steps, aligned, s);
+  }
 }
 
 hipError_t launch_async_adjoint_tiled(const AsyncAdjStep& a, const void* lam_in, void* lam_out,
@@ -961,11 +1084,9 @@ hipError_t launch_async_adjoint_tiled(const AsyncAdjStep& a, const void* lam_in,
     return hipErrorInvalidValue;
   const int aligned = is_aligned16(lam_in) && is_aligned16(lam_out) && is_aligned16(u);
   if (a.dtype == 0)
-    a.ring ? adjoint_tiled_launch<float, true>(a, g, lam_in, lam_out, u, k0, steps, aligned, s)
-           : adjoint_tiled_launch<float, false>(a, g, lam_in, lam_out, u, k0, steps, aligned, s);
+    adjoint_tiled_pick<float>(a, g, lam_in, lam_out, u, k0, steps, aligned, s);
   else
-    a.ring ? adjoint_tiled_launch<double, true>(a, g, lam_in, lam_out, u, k0, steps, aligned, s)
-           : adjoint_tiled_launch<double, false>(a, g, lam_in, lam_out, u, k0, steps, aligned, s);
+    adjoint_tiled_pick<double>(a, g, lam_in, lam_out, u, k0, steps, aligned, s);
   return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
 """Gradients through the emulated asynchronous run in segments of 32 steps
-(subdomains longer than a tile): u(K) and dL/du0 bit for bit those of one launch
+(subdomains of 144 points or more): u(K) and dL/du0 bit for bit those of one launch
 per step, with subdomain edges at every kind of place in a tile, runs that end
 inside a group of 8 steps or with a segment of one step, and runs of more
 segments than the workspace keeps states for (the others replayed).  The scalar
@@ -25,6 +25,13 @@ CASES = [  # (dt, N, P, d, K, checkpoint stride)
     ("f32", 2100, 2, 5, 4500, 0), ("f64", 2100, 2, 3, 4500, 0),    # stretches of two segments
     ("f64", 2100, 2, 3, 20000, 0),                                 # and of three
     ("f32", 5000, 2, 2, 300, 1), ("f64", 5000, 2, 2, 300, 300),    # any checkpoint stride
+    # short subdomains, a tile about each edge: the shortest, one tile a piece,
+    # two and three, lengths that are no multiple of 4
+    ("f32", 145 * 7 - 1, 7, 5, 97, 0), ("f64", 144 * 2, 2, 9, 105, 0),
+    ("f32", 431 * 5 + 3, 5, 255, 70, 0), ("f64", 437 * 6 - 2, 6, 3, 64, 0),
+    ("f32", 1024 * 3, 3, 1, 33, 0), ("f64", 868 * 9 + 5, 9, 40, 40, 7),
+    ("f32", 231587, 843, 14, 40, 0), ("f64", 1001 * 2, 2, 3, 4500, 0),
+    ("f32", 143 * 3 + 1, 3, 2, 35, 0),                             # too short for one
 ]
 
 

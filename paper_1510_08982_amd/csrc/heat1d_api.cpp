@@ -574,7 +574,7 @@ void batched_split_band(heat1d_plan_t p) {
   std::vector<int32_t> rest;
   int64_t tiles = 0, w = 0;
   for (int32_t b : p->by_work) {
-    const int h = band_reach(p->dtype, 0.5, std::max(p->Kh[b], 1));
+    const int h = band_reach_bound(p->dtype, 0.5, std::max(p->Kh[b], 1));
     const int64_t nt = (p->Nh[b] + kBandBatchTile - 1) / kBandBatchTile;
     // r is known to the run only; 1/2 drifts least
     if (p->Kh[b] < kBatchBandFrom || fp32_drifts(p->dtype, 0.5, p->Kh[b]) || h > kBandMaxReach || tiles + nt > (1 << 22) ||

@@ -26,6 +26,10 @@ constexpr int kBandMaxReach = 2048;
 // Points beyond which the weights of T steps are dropped (at most T): the
 // dropped weights sum to at most 2^-28 (FP32) / 2^-57 (FP64).
 int band_reach(int dtype, double r, int64_t T);
+// The same from a bound that grows with r and with T, and which band_reach never
+// exceeds: what room for any r has to be sized for.  (It drops less, 2^-33 and
+// 2^-64 at most: runs of many short passes use it.)
+int band_reach_bound(int dtype, double r, int64_t T);
 
 // How a run of K steps is cut into passes of at most T steps each.
 struct BandRun {

@@ -330,12 +330,12 @@ StripPlan strip_plan(int dtype, int64_t N, int P, double r, int64_t K, int d, in
       int64_t lo = 0, hi = K + 1;  // reach of lo steps fits, of hi steps does not (or is not asked)
       while (hi - lo > 1) {
         const int64_t mid = lo + (hi - lo) / 2;
-        (band_reach(dtype, r, mid) <= reach ? lo : hi) = mid;
+        (band_reach_bound(dtype, r, mid) <= reach ? lo : hi) = mid;
       }
       if (lo < 1) continue;
       const int64_t stages = (K + lo - 1) / lo, T = (K + stages - 1) / stages;
       if (stages > most) continue;
-      const int64_t R = band_reach(dtype, r, T);
+      const int64_t R = band_reach_bound(dtype, r, T);
       double c = (double)K * per_simd * (step0 + step1 * m) + (double)stages * 10.0;
       if (!cover)
         c += (double)stages * (10.0 + (double)N * (2.0 * R + 200.0) * (dtype == 0 ? 1.5e-8 : 3e-8));

@@ -798,14 +798,15 @@ size_t batched_queue_off(heat1d_plan_t p, int q) {
 // Behind the queues and their heads: the tiles, rods and weight offsets of the
 // band passes, their flag, records and weights.
 struct BatchedBandLayout {
-  size_t items, rods, woff, flag, rec, w, total;
+  size_t items, rods, woff, slot, flag, rec, w, total;
 };
 BatchedBandLayout batched_band_layout(heat1d_plan_t p) {
   BatchedBandLayout L{};
   L.items = batched_queue_off(p, 3) + align_up(3 * 4);
   L.rods = L.items + align_up(p->band_items.size() * sizeof(BandItem));
   L.woff = L.rods + align_up(p->band_rods.size() * 4);
-  L.flag = L.woff + align_up(p->band_woff.size() * 4);
+  L.slot = L.woff + align_up(p->band_woff.size() * 4);
+  L.flag = L.slot + align_up(p->band_rods.size() * kBandSlotBytes);
   L.rec = L.flag + align_up(4);
   L.w = L.rec + align_up(p->band_items.size() * 8);
   L.total = L.w + align_up((p->band_woff.empty() ? 0 : (size_t)p->band_woff.back()) *
@@ -1648,6 +1649,7 @@ hipError_t launch_batch(heat1d_plan_t p, const void* u0, void* uK, const int64_t
     b.items = (const BandItem*)(ws + L.items);
     b.rods = (const int32_t*)(ws + L.rods);
     b.woff = (const int32_t*)(ws + L.woff);
+    b.slot = ws + L.slot;
     b.w = ws + L.w;
     b.flag = (int32_t*)(ws + L.flag);
     b.rec = ws + L.rec;

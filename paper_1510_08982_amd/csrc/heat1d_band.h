@@ -73,6 +73,15 @@ hipError_t launch_band_weights(const BandPass& p, hipStream_t s);
 hipError_t launch_band_pass(const BandPass& p, hipStream_t s);
 hipError_t launch_band_cones(const BandPass& p, hipStream_t s);
 
+// What the tiles of a rod need of it, gathered by the workgroup that computes its
+// weights: a tile then waits for two loads in turn before its first point, not five.
+struct BandSlot {
+  int64_t off, N;
+  double c1, cN;
+  int32_t H, woff;
+};
+constexpr size_t kBandSlotBytes = sizeof(BandSlot);
+
 // Rods of uneven length, step count and r: tiles of kBandBatchTile points, one
 // workgroup each.  All pointers are device memory.
 constexpr int kBandBatchTile = 2048;
@@ -91,6 +100,7 @@ struct BandBatch {
   const int32_t* K = nullptr;
   const BandItem* items = nullptr;  // a rod's tiles one after the other
   const int32_t* rods = nullptr;    // of each slot
+  void* slot = nullptr;             // slots x kBandSlotBytes, written by the run
   const int32_t* woff = nullptr;    // slots + 1: where a slot's weights start
   void* w = nullptr;
   int32_t* flag = nullptr;

@@ -357,7 +357,7 @@ __device__ __forceinline__ void load_tile(F (&u)[M], const F* __restrict__ src, 
 
 // order[0..tiles): the tiles holding an edge, then the others, each in tile
 // order (one workgroup; a chunk of kOrder tiles per pass, places from ballots;
-// with 256 threads 17.6 thousand tiles took 165 us).
+// 17.6 thousand tiles in 88 us, with 256 threads 165).
 constexpr int kOrder = 1024;
 template <bool kRing>
 __global__ __launch_bounds__(kOrder) void tile_order_kernel(int* __restrict__ order, int64_t tiles,

@@ -465,6 +465,14 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_lockstep_tiled_kernel
   if (left_end) u[0] = (lane == 0) ? c1 : u[0];
   if (right_end) set_point<F, M>(u, jN, lane == lN, cN);
   asm("" : "+v"(r));
+  if (!kFit && !has_edge && !left_end && !right_end) {
+    // most tiles: the bare step (70 -> 65 us a launch in a trace)
+#pragma unroll 4
+    for (int s = 0; s < steps; ++s)
+      lane_step<F, M>(u, from_lower_lane(u[M - 1]), from_upper_lane(u[0]), r);
+    store_points<F, M>(u, out, base + q0, q0, lo_t, hi_t, st_aligned);
+    return;
+  }
   for (int s = 0; s < steps; ++s) {
     const int k = k0 + s;
     F ua = F(0), ual = F(0), ub = F(0), ubr = F(0);
@@ -521,13 +529,14 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_lockstep_tiled_kernel
 // Vector arithmetic bounds it: about ten instructions a point and step (three for
 // each of 52/32 forward steps, four for the transpose and dL/dr) where every
 // fourth state through memory cost eight and 32 bytes a point and step.
-// N = 2^24, 1024 subdomains, d = 4, K = 5000, FP32: 78.2 -> 49.4 ms, a launch of
-// 32 steps 242 us; two wavefronts a SIMD (209 registers).  The tiles that hold
+// N = 2^24, 1024 subdomains, d = 4, K = 5000, FP32: 78.2 -> 40.6 ms, a launch of
+// 32 steps 193 us; two wavefronts a SIMD (209 registers).  The tiles that hold
 // an edge are the longest chain: with the edge points' states taken from the
 // record instead of computed again a launch went from 336 to 269 us (59 us where
 // those tiles are alone, N = 2^18); with the second differences kept instead of
-// the states, from 269 to 242 us.  FP64 takes 8 points a lane, so that a group
-// fits the same registers: N = 2^22, K = 1000: 7.91 -> 5.76 ms.
+// the states, from 269 to 242 us; with a sweep of their own for tiles without an
+// edge or end, to 193 us.  FP64 takes 8 points a lane, so that a group fits the
+// same registers: N = 2^22, K = 1000: 7.91 -> 4.6 ms.
 template <typename F, int M, bool kRing, bool kFit>
 __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
     const F* __restrict__ lam_in, F* __restrict__ lam_out, const F* __restrict__ u0,
@@ -569,9 +578,9 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
   const int qN = ts.qN;
   const int lN = qN / M, jN = uniform(qN % M);
   // points 1 and N-2 (dL/dc1, dL/dcN) when this tile owns them
-  const bool own_1 = left_end && 1 < hi_t;
+  const bool owns_1 = left_end && 1 < hi_t;
   const int qM = qN - 1;
-  const bool own_m = right_end && qM >= lo_t && qM < hi_t && qM >= 1;
+  const bool owns_m = right_end && qM >= lo_t && qM < hi_t && qM >= 1;
   const bool has_edge = ts.has_edge;
   // a tile holding an edge has the longest chain of the launch: its wavefront
   // issues ahead of the plain tiles sharing its SIMD
@@ -617,7 +626,7 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
   }
   const bool own_a = qa >= lo_t && qa < hi_t, own_b = qb >= lo_t && qb < hi_t;
   // a tile between others: its own points are those from kAdjH to L - kAdjH
-  const bool inner = !kFit && lo_t == kAdjH && hi_t == L - kAdjH && !left_end && !right_end;
+  const bool between = lo_t == kAdjH && hi_t == L - kAdjH && !left_end && !right_end;
   double g = 0.0, e1 = 0.0, eN = 0.0;
   const double rd = (double)r;
   // the lane's points whose dL/dr terms this tile sums: its own output
@@ -631,167 +640,182 @@ __global__ __launch_bounds__(kAdjWaves * kWave) void async_adjoint_tiled_kernel(
   }
 
   asm("" : "+v"(r));
-  // u(k+1) from u(k), in c, and the second differences of u(k) (across a
-  // subdomain edge the plain ones); the edge points' values are the record's
-  auto fwd_step = [&](Lap (&lap)[M], int k, bool step) __attribute__((always_inline)) {
-    const F left = from_lower_lane(c[M - 1]);
-    const F right = from_upper_lane(c[0]);
-    F prev = left;
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-      const F x = c[j];
-      const F nx = j + 1 < M ? c[j + 1] : right;
-      const F second = fma_of(F(-2), x, prev + nx);
-      lap[j] = kFit ? (Lap)prev + (Lap)nx - Lap(2) * (Lap)x : (Lap)second;
-      c[j] = fma_of(r, second, x);
-      prev = x;
-    }
-    if (!step) return;
-    if (has_edge) {
-      set_point<F, M>(c, qa % M, lane == qa / M, eval[w][0][k + 1 - k0]);
-      if (qb < L) set_point<F, M>(c, qb % M, lane == qb / M, eval[w][1][k + 1 - k0]);
-    }
-    if (left_end) c[0] = (lane == 0) ? c1 : c[0];
-    if (right_end) set_point<F, M>(c, jN, lane == lN, cN);
-  };
+  // Most tiles hold neither an edge nor an end: they take a copy of the sweep
+  // without the conditions (whose scalars had to be kept in vector registers):
+  // 242 -> 194 us a launch.  (Fitted tiles nearly all hold an edge.)
+  auto sweep = [&](auto tag) __attribute__((always_inline)) {
+    constexpr bool kPlain = decltype(tag)::value;
+    const bool has_edge = !kPlain && ts.has_edge;
+    const bool left_end = !kPlain && ts.left_end, right_end = !kPlain && ts.right_end;
+    const bool own_1 = !kPlain && owns_1, own_m = !kPlain && owns_m;
+    const bool inner = kPlain || (!kFit && between);
 
-  // lambda(k+1) of the edge points
-  F la1 = F(0), lb1 = F(0);
-  if (has_edge) {
-    la1 = read_lane(get_point<F, M>(l, qa % M), qa / M);
-    if (qb < L) lb1 = read_lane(get_point<F, M>(l, qb % M), qb / M);
-  }
-  // lambda(k) from lambda(k+1), in l; lap: the second differences of u(k)
-  auto bwd_step = [&](const Lap (&lap)[M], int k) __attribute__((always_inline)) {
-    F lal1 = F(0), lbr1 = F(0);
-    if (has_edge) {
-      if (qa >= 1) lal1 = read_lane(get_point<F, M>(l, (qa - 1) % M), (qa - 1) / M);
-      if (qb + 1 < L) lbr1 = read_lane(get_point<F, M>(l, (qb + 1) % M), (qb + 1) / M);
-    }
-    if (own_1) e1 += rd * (double)read_lane(l[1 % M], 1 / M);
-    if (own_m) eN += rd * (double)read_lane(get_point<F, M>(l, qM % M), qM / M);
-    // dL/dr with the plain Laplacians over the tile's own points: the lane's
-    // terms of this step summed in the state precision (two chains), then
-    // added to the double total
-    if constexpr (kFit) {
-#pragma unroll
-      for (int j = 0; j < M; ++j) {
-        const F lm = ((own_mask >> j) & 1u) ? l[j] : F(0);
-        g += (double)lm * (double)lap[j];
-      }
-    } else if (inner) {
-      // the lanes that hold the tile's first and last own point start and stop there
-      F acc[2] = {F(0), F(0)}, sum = F(0);
-#pragma unroll
-      for (int j = 0; j < M; ++j) {
-        if (j > 0 && j == kAdjH % M) {
-          acc[0] = lane == kAdjH / M ? F(0) : acc[0];
-          acc[1] = lane == kAdjH / M ? F(0) : acc[1];
-        }
-        if (j == (L - kAdjH) % M) sum = acc[0] + acc[1];
-        acc[j & 1] = fma_of(l[j], lap[j], acc[j & 1]);
-      }
-      sum = lane == (L - kAdjH) / M ? sum : acc[0] + acc[1];
-      g += (double)(lane >= kAdjH / M && lane <= (L - kAdjH) / M ? sum : F(0));
-    } else {
-      F acc[2] = {F(0), F(0)};
-#pragma unroll
-      for (int j = 0; j < M; ++j) {
-        const F lm = ((own_mask >> j) & 1u) ? l[j] : F(0);
-        acc[j & 1] = fma_of(lm, lap[j], acc[j & 1]);
-      }
-      g += (double)(acc[0] + acc[1]);
-    }
-    // the plain transpose step of every point
-    {
-      const F left = from_lower_lane(l[M - 1]);
-      const F right = from_upper_lane(l[0]);
+    // u(k+1) from u(k), in c, and the second differences of u(k) (across a
+    // subdomain edge the plain ones); the edge points' values are the record's
+    auto fwd_step = [&](Lap (&lap)[M], int k, bool step) __attribute__((always_inline)) {
+      const F left = from_lower_lane(c[M - 1]);
+      const F right = from_upper_lane(c[0]);
       F prev = left;
 #pragma unroll
       for (int j = 0; j < M; ++j) {
-        const F c = l[j];
-        const F nx = j + 1 < M ? l[j + 1] : right;
-        l[j] = fma_of(r, fma_of(F(-2), c, prev + nx), c);
-        prev = c;
+        const F x = c[j];
+        const F nx = j + 1 < M ? c[j + 1] : right;
+        const F second = fma_of(F(-2), x, prev + nx);
+        lap[j] = kFit ? (Lap)prev + (Lap)nx - Lap(2) * (Lap)x : (Lap)second;
+        c[j] = fma_of(r, second, x);
+        prev = x;
       }
-    }
-    if (has_edge) {
-      const int kmax = k + d < K - 1 ? k + d : K - 1;
-      // the delayed Laplacians of the edge points, as corrections of the plain ones
-      const F uRd = edly[w][0][k - k0], uLd = edly[w][1][k - k0];
-      const F ua = eval[w][0][k - k0], ub = eval[w][1][k - k0];
-      if (lane == 0) {
-        if (own_a) g += (double)la1 * ((double)uRd - (double)ub);
-        if (own_b) g += (double)lb1 * ((double)uLd - (double)ua);
+      if (!step) return;
+      if (has_edge) {
+        set_point<F, M>(c, qa % M, lane == qa / M, eval[w][0][k + 1 - k0]);
+        if (qb < L) set_point<F, M>(c, qb % M, lane == qb / M, eval[w][1][k + 1 - k0]);
       }
-      // point a: the pulls of b's left reads first, then its left neighbour;
-      // point b: its right neighbour first, then the pulls of a's right reads.
-      // Lane j looks at step kk = k + j (a chunk of up to 64 steps at a time);
-      // the hits are added in order of kk.
-      F nba = F(0);
-      F nbb = F(0);
-      nbb += lbr1;
-      for (int c = k; c <= kmax; c += kWave) {
-        const int kk = c + lane;
-        const bool in = kk <= kmax;
-        const bool hit_a = in && pull[w][0][kk - k0] == k;
-        const bool hit_b = in && pull[w][1][kk - k0] == k;
-        const F vb = (in && kk > k) ? hb[(kk + 1) & Q] : lb1;  // lambda_b(kk+1)
-        const F va = (in && kk > k) ? ha[(kk + 1) & Q] : la1;  // lambda_a(kk+1)
-        for (uint64_t m = __ballot(hit_a); m; m &= m - 1)
-          nba += read_lane(vb, __builtin_ctzll(m));
-        for (uint64_t m = __ballot(hit_b); m; m &= m - 1)
-          nbb += read_lane(va, __builtin_ctzll(m));
-      }
-      nba += lal1;
-      const F na = fma_of(r, fma_of(F(-2), la1, nba), la1);
-      const F nb = fma_of(r, fma_of(F(-2), lb1, nbb), lb1);
-      set_point<F, M>(l, qa % M, lane == qa / M, na);
-      if (qb < L) set_point<F, M>(l, qb % M, lane == qb / M, nb);
-      la1 = na;
-      lb1 = nb;
-      if (lane == 0) {
-        ha[k & Q] = na;
-        hb[k & Q] = nb;
-        if (own_a) LE[((int64_t)k * P + b) * 2] = na;
-        if (own_b) LE[((int64_t)k * P + b) * 2 + 1] = nb;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    // lambda of the fixed ends stays 0
-    if (left_end) l[0] = (lane == 0) ? F(0) : l[0];
-    if (right_end) set_point<F, M>(l, jN, lane == lN, F(0));
-  };
+      if (left_end) c[0] = (lane == 0) ? c1 : c[0];
+      if (right_end) set_point<F, M>(c, jN, lane == lN, cN);
+    };
 
-  // forward to the bottom of the top group, then the groups from the top
-  Lap lap[G][M];
-  const int groups = (steps + G - 1) / G;
-  for (int g0 = 0; g0 + 1 < groups; ++g0) {
-#pragma unroll
-    for (int j = 0; j < M; ++j) kept[w][g0][j][lane] = c[j];
-    for (int i = 0; i < G; ++i) fwd_step(lap[0], k0 + g0 * G + i, true);
-  }
-  for (int g0 = groups - 1; g0 >= 0; --g0) {
-    const int kb = k0 + g0 * G, n = min(G, steps - g0 * G);
-    if (g0 != groups - 1) {
-#pragma unroll
-      for (int j = 0; j < M; ++j) c[j] = kept[w][g0][j][lane];
+    // lambda(k+1) of the edge points
+    F la1 = F(0), lb1 = F(0);
+    if (has_edge) {
+      la1 = read_lane(get_point<F, M>(l, qa % M), qa / M);
+      if (qb < L) lb1 = read_lane(get_point<F, M>(l, qb % M), qb / M);
     }
+    // lambda(k) from lambda(k+1), in l; lap: the second differences of u(k)
+    auto bwd_step = [&](const Lap (&lap)[M], int k) __attribute__((always_inline)) {
+      F lal1 = F(0), lbr1 = F(0);
+      if (has_edge) {
+        if (qa >= 1) lal1 = read_lane(get_point<F, M>(l, (qa - 1) % M), (qa - 1) / M);
+        if (qb + 1 < L) lbr1 = read_lane(get_point<F, M>(l, (qb + 1) % M), (qb + 1) / M);
+      }
+      if (own_1) e1 += rd * (double)read_lane(l[1 % M], 1 / M);
+      if (own_m) eN += rd * (double)read_lane(get_point<F, M>(l, qM % M), qM / M);
+      // dL/dr with the plain Laplacians over the tile's own points: the lane's
+      // terms of this step summed in the state precision (two chains), then
+      // added to the double total
+      if constexpr (kFit) {
 #pragma unroll
-    for (int i = 0; i < G; ++i)
-      if (i < n) fwd_step(lap[i], kb + i, i + 1 < n);
+        for (int j = 0; j < M; ++j) {
+          const F lm = ((own_mask >> j) & 1u) ? l[j] : F(0);
+          g += (double)lm * (double)lap[j];
+        }
+      } else if (inner) {
+        // the lanes that hold the tile's first and last own point start and stop there
+        F acc[2] = {F(0), F(0)}, sum = F(0);
 #pragma unroll
-    for (int i = G - 1; i >= 0; --i)
-      if (i < n) bwd_step(lap[i], kb + i);
-  }
+        for (int j = 0; j < M; ++j) {
+          if (j > 0 && j == kAdjH % M) {
+            acc[0] = lane == kAdjH / M ? F(0) : acc[0];
+            acc[1] = lane == kAdjH / M ? F(0) : acc[1];
+          }
+          if (j == (L - kAdjH) % M) sum = acc[0] + acc[1];
+          acc[j & 1] = fma_of(l[j], lap[j], acc[j & 1]);
+        }
+        sum = lane == (L - kAdjH) / M ? sum : acc[0] + acc[1];
+        g += (double)(lane >= kAdjH / M && lane <= (L - kAdjH) / M ? sum : F(0));
+      } else {
+        F acc[2] = {F(0), F(0)};
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+          const F lm = ((own_mask >> j) & 1u) ? l[j] : F(0);
+          acc[j & 1] = fma_of(lm, lap[j], acc[j & 1]);
+        }
+        g += (double)(acc[0] + acc[1]);
+      }
+      // the plain transpose step of every point
+      {
+        const F left = from_lower_lane(l[M - 1]);
+        const F right = from_upper_lane(l[0]);
+        F prev = left;
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+          const F c = l[j];
+          const F nx = j + 1 < M ? l[j + 1] : right;
+          l[j] = fma_of(r, fma_of(F(-2), c, prev + nx), c);
+          prev = c;
+        }
+      }
+      if (has_edge) {
+        const int kmax = k + d < K - 1 ? k + d : K - 1;
+        // the delayed Laplacians of the edge points, as corrections of the plain ones
+        const F uRd = edly[w][0][k - k0], uLd = edly[w][1][k - k0];
+        const F ua = eval[w][0][k - k0], ub = eval[w][1][k - k0];
+        if (lane == 0) {
+          if (own_a) g += (double)la1 * ((double)uRd - (double)ub);
+          if (own_b) g += (double)lb1 * ((double)uLd - (double)ua);
+        }
+        // point a: the pulls of b's left reads first, then its left neighbour;
+        // point b: its right neighbour first, then the pulls of a's right reads.
+        // Lane j looks at step kk = k + j (a chunk of up to 64 steps at a time);
+        // the hits are added in order of kk.
+        F nba = F(0);
+        F nbb = F(0);
+        nbb += lbr1;
+        for (int c = k; c <= kmax; c += kWave) {
+          const int kk = c + lane;
+          const bool in = kk <= kmax;
+          const bool hit_a = in && pull[w][0][kk - k0] == k;
+          const bool hit_b = in && pull[w][1][kk - k0] == k;
+          const F vb = (in && kk > k) ? hb[(kk + 1) & Q] : lb1;  // lambda_b(kk+1)
+          const F va = (in && kk > k) ? ha[(kk + 1) & Q] : la1;  // lambda_a(kk+1)
+          for (uint64_t m = __ballot(hit_a); m; m &= m - 1)
+            nba += read_lane(vb, __builtin_ctzll(m));
+          for (uint64_t m = __ballot(hit_b); m; m &= m - 1)
+            nbb += read_lane(va, __builtin_ctzll(m));
+        }
+        nba += lal1;
+        const F na = fma_of(r, fma_of(F(-2), la1, nba), la1);
+        const F nb = fma_of(r, fma_of(F(-2), lb1, nbb), lb1);
+        set_point<F, M>(l, qa % M, lane == qa / M, na);
+        if (qb < L) set_point<F, M>(l, qb % M, lane == qb / M, nb);
+        la1 = na;
+        lb1 = nb;
+        if (lane == 0) {
+          ha[k & Q] = na;
+          hb[k & Q] = nb;
+          if (own_a) LE[((int64_t)k * P + b) * 2] = na;
+          if (own_b) LE[((int64_t)k * P + b) * 2 + 1] = nb;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
+      // lambda of the fixed ends stays 0
+      if (left_end) l[0] = (lane == 0) ? F(0) : l[0];
+      if (right_end) set_point<F, M>(l, jN, lane == lN, F(0));
+    };
+
+    // forward to the bottom of the top group, then the groups from the top
+    Lap lap[G][M];
+    const int groups = (steps + G - 1) / G;
+    for (int g0 = 0; g0 + 1 < groups; ++g0) {
+#pragma unroll
+      for (int j = 0; j < M; ++j) kept[w][g0][j][lane] = c[j];
+      for (int i = 0; i < G; ++i) fwd_step(lap[0], k0 + g0 * G + i, true);
+    }
+    for (int g0 = groups - 1; g0 >= 0; --g0) {
+      const int kb = k0 + g0 * G, n = min(G, steps - g0 * G);
+      if (g0 != groups - 1) {
+#pragma unroll
+        for (int j = 0; j < M; ++j) c[j] = kept[w][g0][j][lane];
+      }
+#pragma unroll
+      for (int i = 0; i < G; ++i)
+        if (i < n) fwd_step(lap[i], kb + i, i + 1 < n);
+#pragma unroll
+      for (int i = G - 1; i >= 0; --i)
+        if (i < n) bwd_step(lap[i], kb + i);
+    }
+  };
+  if (!kFit && !ts.has_edge && between)
+    sweep(std::true_type{});
+  else
+    sweep(std::false_type{});
   store_points<F, M>(l, lam_out, base + q0, q0, lo_t, hi_t, aligned != 0 && base >= 0);
   for (int off = kWave / 2; off > 0; off >>= 1) g += __shfl_xor(g, off, kWave);
   if (lane == 0) {
     part[t] += g;
-    if (own_1) ends[0] += e1;
-    if (own_m) ends[1] += eN;
+    if (owns_1) ends[0] += e1;
+    if (owns_m) ends[1] += eN;
   }
 }
 

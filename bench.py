@@ -3,9 +3,13 @@
 
 A "step" of this benchmark is one complete run of the synchronous large-rod
 workload: N = 2^26 points in FP32, r = 0.25, c1 = cN = 0, u0 = eight sine modes
-plus noise, K = 2000 time steps (depth-T temporal blocking, autotuned).
-`value` is its throughput in GLUP/s (giga lattice-point updates per second,
-(N-2)*K per run) with the input already resident in HBM.
+plus noise, K = 2000 time steps.  `value` is its throughput in GLUP/s (giga
+lattice-point updates per second, (N-2)*K per run) with the input already
+resident in HBM: the updates of the iteration whose result a run delivers.  A
+plan left to itself takes runs of 64 steps or more as band passes (T steps of
+Eq.3 applied at once, as one banded Toeplitz product on the matrix cores), so a
+run does not make those updates one by one; the "T sweep" variant times the
+kernels that do, and the band passes' roofline counts their own operations.
 
 The same invocation also measures, and reports under "variants", the other
 forms of the hot path: the T sweep (1..32) and the FP64 rod (N = 2^25); the
@@ -39,6 +43,8 @@ import numpy as np  # noqa: E402
 PEAK_FP32_TFLOPS = 157.3  # MI355X vector FP32
 PEAK_FP64_TFLOPS = 78.6   # MI355X vector FP64
 PEAK_HBM_GBS = 8000.0
+PEAK_FP32_MATRIX_TFLOPS = 157.3  # MI355X FP32 matrix instructions
+PEAK_FP64_MATRIX_TFLOPS = 78.6   # MI355X FP64 matrix instructions
 FLOPS_PER_LUP = 4         # add, multiply, fused multiply-add (the update c + r((a+b) - 2c))
 ADJ_FLOPS_PER_LUP = 6     # a lambda update (4) and its dL/dr term (one FMA, 2)
 PROFILES = os.path.join(ROOT, "profiles")
@@ -264,6 +270,13 @@ def main():
                 "hbm_bytes_per_launch_algorithmic": round(bytes_per_launch),
                 "hbm_gbs_algorithmic": round(bytes_per_launch / (kern_ms * 1e-3) / 1e9, 1)
                 if kern_ms > 0 else None}
+    if "band_from=" in desc:
+        roofline = band_roofline(N, r, K, max(launches_total // args.steps, 1), kern_ms)
+        roofline["launches_timed"] = launches_total
+        rec = traffic_record("band_kernel<float>", f"N={N} K={K} r={r}")
+        if rec:
+            roofline["traffic"] = rec["bytes_per_launch"]
+            roofline["traffic_unit"] = "bytes per launch (FETCH_SIZE + WRITE_SIZE, copy-scaled)"
     del out
     plan.close()
     roofline["hbm_gbs_nominal"] = 8000.0
@@ -294,7 +307,7 @@ def main():
         "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": "sync large rod: N=2^26 FP32, r=0.25, c1=cN=0, u0 = 8 sine modes "
-                               "(m=8^j) + U[-0.01,0.01] noise, K=2000, temporal blocking autotuned",
+                               "(m=8^j) + U[-0.01,0.01] noise, K=2000, plan autotuned",
                    "N": N, "K": K, "plan": desc, "device": props.name},
         "roofline": roofline,
         "cpu_baseline": cpu,
@@ -392,6 +405,40 @@ def pass_kernel(desc, ftype, ring=False):
     return f"sync_tiled_kernel<{ftype}, {m}, {sf}>"
 
 
+def band_taps(r, T, double):
+    """Weights of T steps of Eq.3, (r, 1-2r, r)^T, without which the rest sums to
+    2^-28 (FP32) or 2^-57 (FP64) at most: what one output of a band pass needs."""
+    w, base, t = np.ones(1), np.array([r, 1 - 2 * r, r]), int(T)
+    while t:
+        if t & 1:
+            w = np.convolve(w, base)
+        t >>= 1
+        if t:
+            base = np.convolve(base, base)
+    c = len(w) // 2
+    tail = 2 * np.cumsum(w[c:][::-1])[::-1]       # what lies at |d| and beyond
+    return 2 * int(np.sum(tail > (2.0 ** -57 if double else 2.0 ** -28))) - 1
+
+
+def band_roofline(points, r, K, passes, kern_ms, double=False):
+    """Roofline record of a run as `passes` equal band passes over `points` points:
+    the multiply-adds that the weights need (work done for the padding of tiles and
+    of the band is not counted) against the peak of the matrix instructions."""
+    if not kern_ms or kern_ms <= 0:
+        return None
+    peak = PEAK_FP64_MATRIX_TFLOPS if double else PEAK_FP32_MATRIX_TFLOPS
+    taps = band_taps(r, -(-K // passes), double)
+    achieved = 2.0 * taps * points / (kern_ms * 1e-3) / 1e12
+    bytes_ = 2 * (8 if double else 4) * points
+    return {"bound": "mfma", "kernel": "band_kernel<double>" if double else "band_kernel<float>",
+            "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
+            "frac": round(achieved / peak, 4), "traffic": None,
+            "kernel_avg_ms": round(kern_ms, 4), "passes": passes, "taps": taps,
+            "hbm_bytes_per_launch_algorithmic": bytes_,
+            "hbm_gbs_algorithmic": round(bytes_ / (kern_ms * 1e-3) / 1e9, 1),
+            "note": "K steps as band passes: 2 operations per weight and point"}
+
+
 def alu_roofline(kernel, flops_per_launch, kern_ms, peak, flops_per_lup, note="", plan=None):
     """Roofline record of one kernel bound by vector ALU work: achieved =
     algorithmic flops per launch / average launch duration (HIP events on the
@@ -427,8 +474,8 @@ def async_adjoint_inputs(torch, dev, workloads):
 
 def run_async_adjoint(torch, dev, workloads, AsyncPlan, variants):
     """Gradients through the emulated asynchronous run of the asynchronous rod
-    (d = 4): lockstep forward keeping checkpoints every ~sqrt(K) steps and the
-    subdomain-edge records, stretch replays, and the transpose steps."""
+    (d = 4): lockstep forward keeping the states at the starts of segments of 32
+    steps and the subdomain-edge records, few replays, and the transpose steps."""
     arod, xa, g, ra = async_adjoint_inputs(torch, dev, workloads)
     N, K = arod.N, arod.K
     reps = 2
@@ -441,20 +488,19 @@ def run_async_adjoint(torch, dev, workloads, AsyncPlan, variants):
         ap.set_timing(False)
         ap._adj_ws = None
     # The subdomains (16384 points) are longer than a register tile, so the
-    # transpose runs on tiles of up to 32 steps per launch, lambda in
-    # registers, every fourth state read and the three between recomputed:
-    # counted as the synchronous adjoint is, 6 flops per backward update (the
+    # transpose runs on tiles of 32 steps per launch, lambda in registers, the
+    # states recomputed from the one at the launch's first step: counted as the synchronous adjoint is, 6 flops per backward update (the
     # lambda step and its dL/dr term; the recompute is work but not counted),
     # K updates of N-2 points over the launches of one run.
     per_run = max(nl // reps, 1)
     res = {"glups_fwd_adj": round(2 * (N - 2) * K / dt / 1e9, 1), "ms": round(dt * 1e3, 3),
            "d": ASYNC_ADJ_D, "P": 1024, "transpose_launches_per_run": per_run,
-           "roofline": alu_roofline("async_adjoint_tiled_kernel<float, false>",
+           "roofline": alu_roofline("async_adjoint_tiled_kernel<float, 16, false, false>",
                                     ADJ_FLOPS_PER_LUP * (N - 2) * K / per_run, kms,
                                     PEAK_FP32_TFLOPS, ADJ_FLOPS_PER_LUP,
-                                    note="one launch reads lambda once, every fourth u(k) of its "
-                                         "steps and writes lambda once: (steps/4 + 2) * 4 * N "
-                                         "bytes, far below the HBM roofline",
+                                    note="one launch reads lambda and the state of its first "
+                                         "step and writes lambda: 12 N bytes, far below the HBM "
+                                         "roofline",
                                     plan=f"N=2^24 P=1024 d={ASYNC_ADJ_D} K={K}")}
     variants["async_adjoint_N2^24_P1024_K5000_d4_f32"] = res
     log(f"[bench] async adjoint: {res}")
@@ -500,9 +546,10 @@ def run_f64(torch, dev, rod, SyncPlan, variants):
         lups = (N64 - 2) * K
         variants["sync_f64_N2^25"] = {
             "glups": round(lups / dt / 1e9, 1), "ms": round(dt * 1e3, 3), "plan": p64.describe(),
-            "roofline": alu_roofline(pass_kernel(p64.describe(), "double"),
-                                     FLOPS_PER_LUP * lups * 3 / nl, kms, PEAK_FP64_TFLOPS,
-                                     FLOPS_PER_LUP)}
+            "roofline": band_roofline(N64, rod.r, K, max(nl // 3, 1), kms, double=True)
+            if "band_from=" in p64.describe() else
+            alu_roofline(pass_kernel(p64.describe(), "double"), FLOPS_PER_LUP * lups * 3 / nl,
+                         kms, PEAK_FP64_TFLOPS, FLOPS_PER_LUP)}
     log(f"[bench] FP64 rod: {variants['sync_f64_N2^25']}")
     del x64
 
@@ -513,7 +560,8 @@ def run_small(torch, dev, workloads, abi, SyncPlan, AsyncPlan, variants):
     lups = (small.N - 2) * small.K
     res = {}
     one_cu = PEAK_FP64_TFLOPS / 256
-    for name, opts in (("step_per_launch", dict(sync_kernel=abi.HEAT1D_SYNC_STEP)),
+    for name, opts in (("auto", {}),
+                       ("step_per_launch", dict(sync_kernel=abi.HEAT1D_SYNC_STEP)),
                        ("resident_16w", dict(sync_kernel=abi.HEAT1D_SYNC_RESIDENT, waves=16)),
                        ("resident_8w", dict(sync_kernel=abi.HEAT1D_SYNC_RESIDENT, waves=8)),
                        ("resident_4w", dict(sync_kernel=abi.HEAT1D_SYNC_RESIDENT, waves=4)),
@@ -530,7 +578,8 @@ def run_small(torch, dev, workloads, abi, SyncPlan, AsyncPlan, variants):
                                                  mode), 2)
             res[f"async_{mname}_P16_d3"] = {"glups": round(lups / dt / 1e9, 3),
                                             "ms": round(dt * 1e3, 3), "plan": ap.describe()}
-    res["note"] = ("one rod of 4096 points occupies one CU (resident) or 16 CUs (async): "
+    res["note"] = ("auto: band passes; one rod of 4096 points occupies one CU (resident), 16 CUs "
+                   "(async hardware) or a workgroup per subdomain edge and stage (async emulated): "
                    "frac_of_one_cu_fp64 is against one CU's share of the FP64 vector peak")
     variants["small_rod_N4096_f64_K20000"] = res
     log(f"[bench] small rod: {res}")
@@ -538,6 +587,11 @@ def run_small(torch, dev, workloads, abi, SyncPlan, AsyncPlan, variants):
 
 STATS_NOTE = ("delay_histogram and polls are counted on an untimed run just before the timed one "
               "(the counting kernel instance is a few percent slower than the timed one)")
+
+
+EMULATED_NOTE = ("strips about the subdomain edges (strip_kernel, kernel_ms their average per "
+                 "launch) and band passes for the points between them; statistics runs step "
+                 "with async_kernel")
 
 
 def run_async_rod(torch, dev, workloads, abi, SyncPlan, AsyncPlan, variants):
@@ -575,11 +629,14 @@ def run_async_rod(torch, dev, workloads, abi, SyncPlan, AsyncPlan, variants):
                 res[key] = {"glups": round(lups / t.dt / 1e9, 1), "ms": round(t.dt * 1e3, 3),
                             "kernel_ms": round(kms, 3), "status": status,
                             "deviation_from_sync": float((outa - sync_ref).abs().max()) / scale,
-                            "delay_histogram": hist[:d + 1], "polls": hist[d + 1],
-                            "roofline": alu_roofline(
-                                f"async_kernel<float, 64, {mode}, false, false>",
-                                FLOPS_PER_LUP * lups, kms, PEAK_FP32_TFLOPS, FLOPS_PER_LUP,
-                                plan=f"N=2^24 P=1024 d={d} {mname}")}
+                            "delay_histogram": hist[:d + 1], "polls": hist[d + 1]}
+                if mode == abi.HEAT1D_ASYNC_EMULATED:
+                    res[key]["note"] = EMULATED_NOTE
+                else:
+                    res[key]["roofline"] = alu_roofline(
+                        f"async_kernel<float, 64, {mode}, false, false>",
+                        FLOPS_PER_LUP * lups, kms, PEAK_FP32_TFLOPS, FLOPS_PER_LUP,
+                        plan=f"N=2^24 P=1024 d={d} {mname}")
                 log(f"[bench] {key}: {res[key]['glups']} GLUP/s "
                     f"dev={res[key]['deviation_from_sync']:.2e}")
         res["plan"] = ap.describe()
@@ -654,8 +711,9 @@ def run_batched(torch, dev, workloads, SyncPlan, BatchedPlan, variants):
         "autotune_best_ms": round(tune_ms, 3),
         "per_rod_sync_estimate_ms": round(est_per_rod_total * 1e3, 1),
         "speedup_vs_per_rod_sync": round(est_per_rod_total / dt_graph, 2),
-        "roofline": alu_roofline("batched_kernel<float>", FLOPS_PER_LUP * blups, kms,
-                                 PEAK_FP32_TFLOPS, FLOPS_PER_LUP, plan="4096 rods")}
+        "kernel_avg_ms": round(kms, 4),
+        "note": "rods of 448 steps or more as band passes (band_batch_kernel), the others in "
+                "batched_kernel's queues"}
     log(f"[bench] batched: {variants['batched_4096_rods_f32']}")
     del bargs, bout, g
     bp.close()
@@ -725,7 +783,8 @@ def run_ring(torch, dev, rod, SyncPlan, abi, variants):
         desc = rp.describe()
         variants["sync_ring_f32_N2^26_K2000"] = {
             "glups": round(lups / dt / 1e9, 1), "ms": round(dt * 1e3, 3), "plan": desc,
-            "roofline": alu_roofline(pass_kernel(desc, "float", ring=True),
+            "roofline": band_roofline(N, r, K, max(nl // 3, 1), kms) if "band_from=" in desc else
+            alu_roofline(pass_kernel(desc, "float", ring=True),
                                      FLOPS_PER_LUP * lups * 3 / max(nl, 1), kms,
                                      PEAK_FP32_TFLOPS, FLOPS_PER_LUP,
                                      plan=" ".join(x for x in desc.split()
@@ -768,10 +827,13 @@ def run_async_ring(torch, dev, workloads, abi, SyncPlan, AsyncPlan, variants):
                 "glups": round(lups / t.dt / 1e9, 1), "ms": round(t.dt * 1e3, 3),
                 "kernel_ms": round(kms, 3), "status": ap.status(),
                 "deviation_from_sync_ring": float((out - ref).abs().max()) / scale,
-                "delay_histogram": hist[:d + 1], "polls": hist[d + 1],
-                "roofline": alu_roofline(f"async_kernel<float, 64, {mode}, false, false>",
-                                         FLOPS_PER_LUP * lups, kms, PEAK_FP32_TFLOPS,
-                                         FLOPS_PER_LUP)}
+                "delay_histogram": hist[:d + 1], "polls": hist[d + 1]}
+            if mode == abi.HEAT1D_ASYNC_EMULATED:
+                res[f"async_{mname}_d{d}"]["note"] = EMULATED_NOTE
+            else:
+                res[f"async_{mname}_d{d}"]["roofline"] = alu_roofline(
+                    f"async_kernel<float, 64, {mode}, false, false>", FLOPS_PER_LUP * lups, kms,
+                    PEAK_FP32_TFLOPS, FLOPS_PER_LUP)
         res["plan"] = ap.describe()
     res["note"] = STATS_NOTE
     variants["async_ring_N2^24_P1024_K5000_f32"] = res
@@ -815,10 +877,10 @@ def run_ensemble(torch, dev, workloads, variants):
                      "final_norm_max": round(float(fin.max()), 6),
                      "initial_norm": round(float(norms[0, 0]), 6),
                      "roofline": alu_roofline(
-                         f"ensemble_kernel<double, 1, {'true' if periodic else 'false'}>",
+                         f"ensemble_wave_kernel<double, 2, {'true' if periodic else 'false'}>",
                          FLOPS_PER_LUP * lups, kms, PEAK_FP64_TFLOPS,
                          FLOPS_PER_LUP, "the run with a norm after every step; latency-bound: "
-                         "one workgroup barrier per step and member, 98-100 points per member",
+                         "the chain of a step on one wavefront per member, 98-100 points",
                          plan=f"300x100 K=5000 d=3 norms every step {name}")}
     # gradients through every member's run (Dirichlet ends)
     plan = EnsemblePlan(N, E, 0, torch.float64)

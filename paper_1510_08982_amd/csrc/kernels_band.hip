@@ -40,7 +40,10 @@ template <> struct Band<float> {
   // hundred times at the size of the result (3.5e-7 of it against 64 bits on
   // the 2^26-point rod, where stepping has 0.9e-7)
   static constexpr int group = 4;
-  static constexpr int nt_large = 8;
+  // tiles of 256 outputs a wavefront: 4 leave room for five wavefronts a SIMD where
+  // 8, which read each weight half as often, leave three (N = 2^26, K = 2000 491 ->
+  // 455 us, on uniform noise 549 -> 538; N = 2^22, K = 300 37.0 -> 35.2 us)
+  static constexpr int nt_large = 4;
   static __device__ __forceinline__ Acc mma(float a, float b, Acc c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }

@@ -221,6 +221,9 @@ __global__ __launch_bounds__(128) void strip_kernel(const StripArgs<F> a) {
     ring[lane][0] = hist[2 * lane];
     ring[lane][1] = hist[2 * lane + 1];
   }
+  // Wavefront 0 replaces the history when it is done, which a stage of few steps is
+  // before any exchange has made it wait for the other one's reads above.
+  __syncthreads();
   if (edge) strip_run<F, M, true>(u, a, b, lane, wave, la, ring, s_table[wave], s_swap);
   else strip_run<F, M, false>(u, a, b, lane, wave, la, ring, s_table[wave], s_swap);
   if (edge && wave == 0) {

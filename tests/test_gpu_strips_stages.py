@@ -1,0 +1,53 @@
+"""GPU parity of emulated asynchronous runs as strips in many stages: stages of
+few steps, which hand the edges' last values on through memory, with delays up
+to the longest that the history serves."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from paper_1510_08982_amd import abi
+from paper_1510_08982_amd.heat import AsyncPlan
+from _helpers import normwise, tol_for, torch_dtype, np_dtype, print_case
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def strips_of(plan):
+    """(stages, steps of a stage, points per lane) from the plan's description."""
+    word = dict(w.split("=", 1) for w in plan.describe().split() if "=" in w)
+    stages, T = word["strips"].split("x")
+    return int(stages), int(T), int(word["M"])
+
+
+def run_against_oracle(dt, N, P, d, K, r, ring, u0, c1, cN, plan):
+    f = np_dtype(dt)
+    x = torch.from_numpy(u0.astype(f)).to(DEV)
+    got = plan.run(x, r, c1, cN, K, d, 42).cpu().numpy()
+    print_case(test="strips_stages", dt=dt, N=N, P=P, d=d, K=K, ring=ring, plan=plan.describe())
+    assert plan.status() == abi.HEAT1D_OK
+    if ring:
+        ref = oracle.async_ensemble(u0, r, 0.0, 0.0, K, P, d, [42], every=K, periodic=True)[0][0]
+    else:
+        ref = oracle.async_emulated(u0, r, c1, cN, K, P, d, 42)
+    err = normwise(got, ref)
+    print(f"  normwise error {err:.3e}")
+    assert err <= tol_for(dt)
+
+
+@pytest.mark.parametrize("ring", [False, True])
+@pytest.mark.parametrize("d", [50, 63])
+@pytest.mark.parametrize("dt,N,P,K,r", [
+    ("f64", 1418, 32, 1000, 0.25), ("f32", 1418, 32, 463, 0.25),  # a last stage of one step
+    ("f64", 3000, 70, 461, 0.5), ("f32", 3000, 70, 900, 0.3),
+])
+def test_short_stages_read_the_history_before_it_is_replaced(dt, N, P, K, r, d, ring):
+    f = np_dtype(dt)
+    u0 = workloads.as_dtype(np.random.default_rng(N + K).uniform(-1, 1, N), f)
+    r = workloads.as_dtype(r, f)
+    with AsyncPlan(N, P, torch_dtype(dt), max_delay=d, periodic=ring) as plan:
+        run_against_oracle(dt, N, P, d, K, r, ring, u0, 1.0, -1.0, plan)
+        stages, T, _ = strips_of(plan)
+        assert stages > 2 and T <= 32

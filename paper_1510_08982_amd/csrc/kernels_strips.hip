@@ -176,11 +176,22 @@ __device__ __forceinline__ void strip_run(F (&u)[M], const StripArgs<F>& a, int 
       }
       __syncthreads();
       since = 0;
-      // the lane shifts again, for the points that changed; the reads across
-      // the edge stand
+      // The handover of this step again, for the points that changed: with M = 4 the
+      // wrong values have just come as far as the edge point of the other side (with r^32
+      // of what lies beyond the cut end), and a delay of 0 and the ring took it.  What a
+      // delayed read of this step brought is older and stands.
       const F l = from_lower_lane(u[M - 1]), rr = from_upper_lane(u[0]);
-      left = kEdge && lane == la + 1 ? left : l;
-      right = kEdge && lane == la ? right : rr;
+      if constexpr (kEdge) {
+        const int now = ((kb + 32) & (kRing - 1)) * kSlot;
+        const bool late = table[(kb + 32) & (kRing - 1)][side] != now + side * (int)sizeof(F);
+        left = late && lane == la + 1 ? left : l;
+        right = late && lane == la ? right : rr;
+        *reinterpret_cast<F*>(rb + now + own) = side ? u[M - 1] : u[0];
+        old = *reinterpret_cast<F*>(rb + slot);
+      } else {
+        left = l;
+        right = rr;
+      }
     }
   }
 }

@@ -1,6 +1,7 @@
 """GPU parity of emulated asynchronous runs as strips in many stages: stages of
 few steps, which hand the edges' last values on through memory, with delays up
-to the longest that the history serves."""
+to the longest that the history serves, and stages in which the two wavefronts
+of a strip trade their points just as the wrong ones reach the edge."""
 import numpy as np
 import pytest
 import torch
@@ -51,3 +52,22 @@ def test_short_stages_read_the_history_before_it_is_replaced(dt, N, P, K, r, d, 
         run_against_oracle(dt, N, P, d, K, r, ring, u0, 1.0, -1.0, plan)
         stages, T, _ = strips_of(plan)
         assert stages > 2 and T <= 32
+
+
+@pytest.mark.parametrize("ring", [False, True])
+@pytest.mark.parametrize("dt,N,P,d,K,r", [
+    ("f64", 20000, 200, 3, 3000, 0.5), ("f64", 12800, 100, 1, 2000, 0.5),
+    ("f64", 20000, 100, 3, 5000, 0.5), ("f64", 23000, 100, 16, 2000, 0.5),
+    ("f64", 3200, 16, 3, 5000, 0.45), ("f32", 20000, 100, 3, 2000, 0.5),
+])
+def test_edge_values_are_right_where_four_points_a_lane_trade(dt, N, P, d, K, r, ring):
+    """With four points a lane the wavefronts overlap by 32 points and trade
+    every 32 steps: at the trade each holds the other's edge point wrong."""
+    f = np_dtype(dt)
+    # values that do not average out beyond the cut ends
+    u0 = workloads.as_dtype(np.random.default_rng(N + K).uniform(0, 1, N), f)
+    r = workloads.as_dtype(r, f)
+    with AsyncPlan(N, P, torch_dtype(dt), max_delay=d, periodic=ring) as plan:
+        run_against_oracle(dt, N, P, d, K, r, ring, u0, 0.0, 1.0, plan)
+        _, T, M = strips_of(plan)
+        assert M == 4 and T > 32

@@ -74,7 +74,8 @@ enum heat1d_sync_kernel {
                                  also leaves depth_t, pts_per_lane, waves and
                                  fuse_steps open (waves and pts_per_lane may shape
                                  an asynchronous kernel, nsub > 0) takes band passes
-                                 for runs of 64 steps or more (FP32 runs of at most
+                                 for runs of 64 steps or more, on short rods 80 to 144
+                                 (heat1d_plan_describe: band_from; FP32 runs of at most
                                  6200 / (1 + 0.1/r): longer ones step, as their
                                  stepping drifts by more than 1e-5): many steps at once as
                                  one banded matrix, the power of Eq.3's stencil

@@ -27,11 +27,25 @@ using namespace heat1d;
 namespace {
 
 // Synchronous runs of at least this many steps take band passes.  A run of K
-// steps is three short launches there, 13 us up to 2^16 points; stepping (AUTO's
-// default kernel) against that, at K = 32 / 64 / 128: 4096 points 11 / 19 / 37
-// us against 11 / 13 / 13; 2^23 points 28 / 54 / 105 us against 36 / 43 / 46;
-// 2^26 points 158 / 330 / 657 us against 200 / 242 / 271 (all FP32).
+// steps is three short launches there, 14 us (18 up to K = 64) on up to 2^18
+// points; stepping with AUTO's default kernel against that, at K = 64 / 80 / 128,
+// in us: 4096 FP32 points 20 / 24 / 37 against 15 / 14 / 14, 2^22 37 / 51 / 73
+// against 29 / 27 / 28, 2^26 331 / 475 / 659 against 221 / 219 / 243.  Where one
+// workgroup steps a short rod, or the ring's tiles a small FP64 ring, as fast as
+// that, the line lies higher: 100 FP32 points 12 / 15 / 23 against 15 / 14 / 14,
+// an FP64 ring of 2^18 16 / 22 / 30 against 18 / 14 / 15.  And where thousands of
+// rods fill the chip with narrow register tiles (plans of more than 4096 rods),
+// FP32 rods of 257 to 1023 points cost a pass a block of eight wavefronts per 256
+// points: 16384 rods of 1000 points take 153 / 197 / 306 us stepped, 382 at
+// K = 160, against 320 at any.
 constexpr int32_t kBandFrom = 64;
+int32_t band_from_steps(int dtype, int64_t N, int64_t nrods, bool ring) {
+  const bool f32 = dtype == HEAT1D_F32;
+  if (f32 && !ring && nrods > 4096 && N > 256 && N < 1024)
+    return 16 + 32 * (int32_t)((N + 255) / 256);
+  const bool fast = ring ? !f32 : N <= (f32 ? 1024 : 512);
+  return fast && N * nrods <= (int64_t(1) << 18) ? 80 : kBandFrom;
+}
 
 // The same for the rods of a batch, and for the long rods of an emulated
 // asynchronous run.  Shorter runs there agree bit for bit with one launch per
@@ -717,7 +731,7 @@ int heat1d_plan_create(heat1d_plan_t* out, int64_t N, int32_t dtype, const heat1
   // the run's length.
   if (o.sync_kernel == HEAT1D_SYNC_AUTO && o.depth_t == 0 && o.pts_per_lane == 0 &&
       o.waves == 0 && o.fuse_steps == 0 && band_applies(dtype, N, p->nrods))
-    p->band_from = kBandFrom;
+    p->band_from = band_from_steps(dtype, N, p->nrods, o.boundary == HEAT1D_BC_PERIODIC);
   describe(p);
   *out = p;
   return HEAT1D_OK;

@@ -1,0 +1,33 @@
+"""Where the lines between two kernels lie, as a plan reports them: each line was
+measured from both sides, and a call must not take the slower one."""
+import pytest
+
+from paper_1510_08982_amd import abi
+
+RING = abi.HEAT1D_BC_PERIODIC
+F32, F64 = abi.HEAT1D_F32, abi.HEAT1D_F64
+
+
+def described(N, dtype, opts):
+    p = abi.heat1d_plan_create(N, dtype, opts)
+    try:
+        return dict(w.split("=", 1) for w in abi.heat1d_plan_describe(p).split() if "=" in w)
+    finally:
+        abi.heat1d_plan_destroy(p)
+
+
+@pytest.mark.parametrize("N,dtype,rods,ring,steps", [
+    # one workgroup, or the ring's tiles, step these as fast up to about 80 steps
+    (3, F32, 1, False, 80), (1024, F32, 256, False, 80), (512, F64, 16, False, 80),
+    (100, F64, 1, True, 80), (1 << 18, F64, 1, True, 80),
+    # beyond them a pass is faster from 64 steps on
+    (1025, F32, 1, False, 64), (100, F32, 8192, False, 64), (1000, F32, 1024, False, 64),
+    (513, F64, 1, False, 64), (1 << 19, F64, 1, True, 64), (100, F32, 1, True, 64),
+    (1 << 26, F32, 1, False, 64),
+    # thousands of short rods on narrow tiles, by the blocks of 256 points of a rod
+    (256, F32, 4097, False, 64), (257, F32, 4097, False, 80), (700, F32, 16384, False, 112),
+    (1000, F32, 16384, False, 144), (1024, F32, 4097, False, 64), (1000, F64, 16384, False, 64),
+])
+def test_band_passes_begin_where_they_are_faster(N, dtype, rods, ring, steps):
+    opts = dict(nrods=rods, boundary=RING if ring else 0)
+    assert described(N, dtype, opts)["band_from"] == str(steps)

@@ -471,7 +471,8 @@ int heat1d_autotune_batched(heat1d_plan_t plan, const void *u0, void *uK, const 
  * passes use fused 4-step sweeps, so uK equals heat1d_run_sync's result to
  * within rounding (not bit for bit) and depends on S only through rounding.
  * uK may be NULL.  FP64 plans that leave opts.sync_kernel open run it as band
- * passes (HEAT1D_SYNC_AUTO) and leave, in place of the states, the one vector
+ * passes (HEAT1D_SYNC_AUTO) from 24 steps on (56 for 512 or more rods of 257 to
+ * 1023 points) and leave, in place of the states, the one vector
  * D A^(K-1) u(0) that dL/dr needs: A, the step, and D, the second difference,
  * commute, so that all K terms of dL/dr are gK . D A^(K-1) u(0). */
 int heat1d_forward_checkpointed(heat1d_plan_t plan, const void *u0, void *uK, double r,

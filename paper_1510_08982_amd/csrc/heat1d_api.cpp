@@ -317,9 +317,18 @@ struct BandAdjLayout {
   size_t z_off, ping_off, spare_off, scr_off, part_off, rod_off, total;
 };
 
-bool band_adjoint(heat1d_plan_t p) {
+// Few steps are as fast from the checkpoints: forward and backward together, in
+// us, stepped / by passes, at K = 16 / 24 / 32 / 48: 100 points 28/34, 33/34,
+// 33/34, 43/34; 4096 rods of 1025 points 105/105, 168/127, 182/128, 265/151;
+// 2^22 points 75/76, 119/85, 122/87, 171/102.  Rods of 257 to 1023 points in
+// numbers that fill the chip take a block of eight wavefronts per 256 points:
+// 4096 of 700 points 66/127, 104/143, 108/145, 152/164 (64: 194/168).
+int64_t band_adjoint_from(heat1d_plan_t p) {
+  return p->N > 256 && p->N < 1024 && p->nrods >= 512 ? 56 : 24;
+}
+bool band_adjoint(heat1d_plan_t p, int64_t K) {
   return p->dtype == HEAT1D_F64 && p->opts.sync_kernel == HEAT1D_SYNC_AUTO &&
-         band_applies(p->dtype, p->N, p->nrods);
+         K >= band_adjoint_from(p) && band_applies(p->dtype, p->N, p->nrods);
 }
 
 BandAdjLayout band_adjoint_layout(heat1d_plan_t p, int64_t K) {
@@ -799,7 +808,10 @@ size_t heat1d_async_workspace_bytes(heat1d_plan_t p) {
 
 size_t heat1d_adjoint_workspace_bytes(heat1d_plan_t p, int64_t K) {
   if (!p || p->batched || K < 0) return 0;
-  return band_adjoint(p) ? band_adjoint_layout(p, K).total : adjoint_layout(p, K).total;
+  if (!band_adjoint(p, K)) return adjoint_layout(p, K).total;
+  // a workspace for K steps also serves fewer, whose checkpoints take more room
+  return std::max(band_adjoint_layout(p, K).total,
+                  adjoint_layout(p, band_adjoint_from(p) - 1).total);
 }
 
 // Batched workspace: the three queues (int32, 256-byte aligned) and three heads.
@@ -1804,7 +1816,7 @@ int heat1d_forward_checkpointed(heat1d_plan_t p, const void* u0, void* uK, doubl
   if (!p || p->batched || !u0 || !workspace || !r_ok(r) || K < 0) return HEAT1D_EINVAL;
   if (periodic(p)) return HEAT1D_EUNSUPPORTED;
   if (K > INT32_MAX) return HEAT1D_EUNSUPPORTED;
-  const bool band = band_adjoint(p);
+  const bool band = band_adjoint(p, K);
   const AdjLayout L = adjoint_layout(p, K);
   if (!band && L.g.tiles_per_rod <= 0) return HEAT1D_EUNSUPPORTED;
   const size_t bytes = (size_t)p->N * p->nrods * esize(p->dtype);
@@ -1815,13 +1827,12 @@ int heat1d_forward_checkpointed(heat1d_plan_t p, const void* u0, void* uK, doubl
     return HEAT1D_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   const int64_t N = p->N, B = p->nrods;
-  if (band && K > 0) {
+  if (band) {
     const BandAdjLayout Z = band_adjoint_layout(p, K);
     const bool one = band_run(p->dtype, r, K).passes <= 1;
     return run_band(p, B, u0, uK || one ? uK : ws + Z.spare_off, r, c1, cN, K, ws + Z.ping_off,
                     ws + Z.scr_off, ws + Z.z_off, nullptr, nullptr, s);
   }
-  if (band) return uK ? hip_status(launch_impose_ends(p->dtype, u0, uK, N, B, c1, cN, s)) : HEAT1D_OK;
   hipError_t e = launch_impose_ends(p->dtype, u0, ws + L.ckpt_off, N, B, c1, cN, s);
   if (e != hipSuccess) return hip_status(e);
   if (K == 0) {
@@ -1848,7 +1859,7 @@ int heat1d_backward_checkpointed(heat1d_plan_t p, const void* gK, double r, doub
     return HEAT1D_EINVAL;
   if (periodic(p)) return HEAT1D_EUNSUPPORTED;
   if (K > INT32_MAX) return HEAT1D_EUNSUPPORTED;
-  const bool band = band_adjoint(p);
+  const bool band = band_adjoint(p, K);
   const AdjLayout L = adjoint_layout(p, K);
   if (!band &&
       (L.g.tiles_per_rod <= 0 || L.gs.tiles_per_rod <= 0 || L.gsub.tiles_per_rod <= 0))
@@ -1864,7 +1875,7 @@ int heat1d_backward_checkpointed(heat1d_plan_t p, const void* gK, double r, doub
   hipStream_t s = (hipStream_t)stream;
   const int64_t N = p->N, B = p->nrods;
   const int S2 = stretch_steps(p->dtype);
-  if (band && K > 0) {
+  if (band) {
     const BandAdjLayout Z = band_adjoint_layout(p, K);
     double* part = (double*)(ws + Z.part_off);
     const int st = run_band(p, B, gK, grad_u0, r, 0.0, 0.0, K, ws + Z.ping_off, ws + Z.scr_off,
@@ -1875,7 +1886,7 @@ int heat1d_backward_checkpointed(heat1d_plan_t p, const void* gK, double r, doub
     return hip_status(p->opts.grad_sum ? launch_reduce_partials(part, tiles * B, 1, grad_r, s)
                                        : launch_reduce_partials(part, tiles, B, grad_r, s));
   }
-  double* partials = (double*)(ws + (band ? band_adjoint_layout(p, K).part_off : L.part_off));
+  double* partials = (double*)(ws + L.part_off);
   if (K == 0) {
     hipError_t e = launch_impose_ends(p->dtype, gK, grad_u0, N, B, 0.0, 0.0, s);
     if (e != hipSuccess) return hip_status(e);
@@ -1983,8 +1994,12 @@ int heat1d_adjoint_ends(heat1d_plan_t p, const void* gK, double r, int64_t K, do
   } else if (tile_geometry(p->dtype, 4, 32, p->N).tiles_per_rod > 0) {
     kern = HEAT1D_SYNC_TILED, T = 32, M = 4;
   }
+  // By passes beyond two launches of 64 steps: 100 FP64 points, K = 64 / 128 / 200,
+  // 29 / 33 / 42 us stepped, 36 by passes; from 2^21 points on it is the state's
+  // traffic that counts: 2^22 points, K = 64 / 96, 67 / 89 us stepped, 71 / 77 by passes.
+  const int64_t from = p->N >= (int64_t(1) << 21) ? 80 : 129;
   const int st =
-      band_adjoint(&one) && K >= kBandFrom
+      band_adjoint(&one, K) && K >= from
           ? run_band(&one, 1, ws + L.z_off, ws + L.w_off, r, 1.0, 0.0, K, ws + L.ping_off,
                      ws + L.scr_off, nullptr, nullptr, nullptr, s)
           : run_sync_impl(&one, ws + L.z_off, ws + L.w_off, r, 1.0, 0.0, K, ws + L.ping_off, s,

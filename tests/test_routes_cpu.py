@@ -31,3 +31,25 @@ def described(N, dtype, opts):
 def test_band_passes_begin_where_they_are_faster(N, dtype, rods, ring, steps):
     opts = dict(nrods=rods, boundary=RING if ring else 0)
     assert described(N, dtype, opts)["band_from"] == str(steps)
+
+
+def adjoint_bytes(N, dtype, opts, steps):
+    p = abi.heat1d_plan_create(N, dtype, opts)
+    try:
+        return [abi.heat1d_adjoint_workspace_bytes(p, K) for K in steps]
+    finally:
+        abi.heat1d_plan_destroy(p)
+
+
+@pytest.mark.parametrize("N,rods,first", [
+    (3, 1, 24), (100, 4096, 24), (256, 4096, 24), (257, 511, 24), (257, 512, 56),
+    (1000, 4096, 56), (1024, 4096, 24), (1 << 20, 1, 24),
+])
+def test_fp64_adjoint_of_few_steps_keeps_checkpoints(N, rods, first):
+    """Below the line a plan's workspace is that of a plan which names a stepping
+    kernel; and the workspace of a run serves every shorter one."""
+    steps = list(range(0, 130)) + [1000, 10 ** 6]
+    auto = adjoint_bytes(N, F64, dict(nrods=rods), steps)
+    named = adjoint_bytes(N, F64, dict(nrods=rods, sync_kernel=abi.HEAT1D_SYNC_STEP), steps)
+    assert auto[:first] == named[:first] and auto[-2] != named[-2]
+    assert all(a <= b for a, b in zip(auto, auto[1:]))

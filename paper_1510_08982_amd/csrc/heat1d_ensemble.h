@@ -11,7 +11,9 @@ struct EnsembleLaunch {
   int dtype;              // 0 FP32, 1 FP64
   const void* u0;         // E rods of N points, back to back
   void* uK;               // E rods of N points, or nullptr
-  void* traj = nullptr;   // E x (K+1) states of N points (updated points written), or nullptr
+  // E x (K+1) x N, or nullptr: the states (updated points written), or, where the
+  // adjoint of this many short rods takes them, the second differences of the steps
+  void* traj = nullptr;
   const uint64_t* seeds;  // E delay seeds (device)
   double* norms;          // E * (K/every + 1) doubles, or nullptr
   int64_t E;
@@ -39,7 +41,7 @@ hipError_t launch_ensemble(const EnsembleLaunch& a, hipStream_t s);
 // launch stored (EnsembleLaunch::traj).
 struct EnsembleAdjointLaunch {
   int dtype;
-  const void* traj;       // E x (K+1) states of N points
+  const void* traj;       // as the forward launch of the same members left it
   const void* gK;         // E x N: dL/du(K)
   const uint64_t* seeds;  // E
   void* grad_u0;          // E x N (ends 0)

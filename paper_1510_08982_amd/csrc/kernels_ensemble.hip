@@ -565,16 +565,36 @@ struct WaveShape {
 
 // Points per lane with which a rod runs on one stepping wavefront, 0: it does
 // not.  The delays must end inside the chunk before (kHist states are kept).  At
-// kWaveMaxM points a lane the adjoint's tables take 109 KiB of LDS, and what a
-// lane steps by itself catches up with a barrier a step: 512 members, N = P =
-// 258, d = 3, K = 1000, FP64: 730 -> 623 us, both passes 1797 -> 1552 us, where
-// 8 members of N = P = 20 go from 390 to 98 and from 966 to 217 us.
+// kWaveMaxM points a lane what a lane steps by itself catches up with a barrier a
+// step: 512 members, N = P = 258, d = 3, K = 1000, FP64: 730 -> 623 us, where
+// 8 members of N = P = 20 go from 390 to 98.
 static int ensemble_wave_m(int64_t N, int d, bool ring) {
   const int64_t count = ring ? N : N - 2;
   if (d >= kChunk || count < 1) return 0;
   // the ring's adjoint keeps a copy of point 0 behind point N-1
   const int64_t m = (count + (ring ? 1 : 0) + kWave - 1) / kWave;
   return m <= kWaveMaxM ? (int)m : 0;
+}
+
+// The same for a run whose trajectory the adjoint takes, and for that adjoint; both
+// ask here, as the kernels above keep another trajectory.  From three points a lane
+// on the adjoint holds up to 256 registers and 110 KiB of LDS, so that members which
+// share a compute unit run one after the other, where two of the kernels above run
+// side by side.  Time against theirs, both passes, K = 300, d = 0 / 3, 64 to 256
+// members, 300 to 512, 768 to 2048: three points, FP64 ring of 190 points 0.76 /
+// 0.6, 1.01 / 0.9, 1.3 / 1.1 (rods and FP32 at most 0.93 anywhere); four points,
+// FP32 rods 0.65 / 0.55, 0.86 / 0.8, 1.1 / 1.0, FP32 rings 0.84 / 0.7, 1.19 / 1.0,
+// 1.5 / 1.2, FP64 rods 0.79 / 0.67, 1.12 / 0.94, 1.4 / 1.15, FP64 rings 1.06 /
+// 0.82, 1.6 / 1.2, 2.0 / 1.5.
+static int ensemble_wave_adjoint_m(int dtype, int64_t N, int d, bool ring, int64_t members) {
+  const int m = ensemble_wave_m(N, d, ring);
+  if (m < 3) return m;
+  const bool f64 = dtype != 0;
+  int64_t most = 1;  // members a compute unit takes
+  if (m == 3) most = f64 && ring ? 2 : members;
+  else if (!ring) most = f64 && d == 0 ? 1 : 2;
+  else if (f64 && d == 0) most = 0;
+  return members <= 256 * most ? m : 0;
 }
 
 // A thread's way through the (step, item) pairs t, t + nt, ... of a chunk with m
@@ -1103,7 +1123,8 @@ hipError_t launch_ensemble(const EnsembleLaunch& L, hipStream_t s) {
   for (int j = 0; j < kEnsembleMaxSnaps; ++j) a.snap_steps[j] = j < L.nsnap ? L.snap_steps[j] : -1;
   const dim3 grid((unsigned)L.E), block((unsigned)kFwdThreads);
   // a trajectory is written in the form that the adjoint's kernel takes
-  const int wm = ensemble_wave_m(L.N, L.d, L.periodic != 0);
+  const int wm = L.traj ? ensemble_wave_adjoint_m(L.dtype, L.N, L.d, L.periodic != 0, L.E)
+                        : ensemble_wave_m(L.N, L.d, L.periodic != 0);
   if (wm > 0) {
     if (L.periodic)
       return L.dtype == 0 ? ensemble_wave_dispatch<float, true>(wm, grid, s, a)
@@ -1166,7 +1187,7 @@ hipError_t launch_ensemble_adjoint(const EnsembleAdjointLaunch& L, hipStream_t s
     return hipErrorInvalidValue;
   const int64_t lds = ensemble_adjoint_lds_bytes(L.dtype, L.N, L.P, L.d);
   if (lds > kEnsembleMaxLds) return hipErrorInvalidValue;
-  if (const int m = ensemble_wave_m(L.N, L.d, L.periodic != 0); m > 0) {
+  if (const int m = ensemble_wave_adjoint_m(L.dtype, L.N, L.d, L.periodic != 0, L.E); m > 0) {
     if (L.periodic)
       return L.dtype == 0 ? ensemble_wave_adjoint_launch<float, true>(L, m, s)
                           : ensemble_wave_adjoint_launch<double, true>(L, m, s);

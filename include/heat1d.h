@@ -407,7 +407,8 @@ int heat1d_run_async_ensemble_adjoint(heat1d_plan_t plan, const void *u0, const 
  * and, for the points next to the P-1 subdomain edges only, every step; the
  * backward pass replays each stretch of S steps from its checkpoint.  Both run
  * in lockstep, one launch per step, or, where every subdomain has 144 points or
- * more (and opts.sync_kernel is not HEAT1D_SYNC_STEP), one per 32 steps,
+ * more (and opts.sync_kernel is not HEAT1D_SYNC_STEP), one per 32 steps (from 2
+ * to 12 steps on, by the sizes),
  * with the states at as many of those launches' starts kept as the same
  * workspace holds (all of them up to K = 32 (ceil(K/S) + S - 1)): grad_u0 and uK
  * are the same bit for bit.  In the emulated mode the delays are a

@@ -388,6 +388,7 @@ AdjLayout adjoint_layout(heat1d_plan_t p, int64_t K) {
 struct AsyncAdjLayout {
   int S;
   int64_t nck;
+  bool tiled;      // register tiles, else one launch per step
   int64_t nparts;  // dL/dr partials: one per workgroup of a step launch or per tile
   size_t state_bytes, rec_bytes;
   size_t ck_off, st_off, fin_off, lam_off, E_off, LE_off, lo_off, part_off, ends_off, ord_off,
@@ -411,10 +412,14 @@ AsyncAdjLayout async_adjoint_layout(heat1d_plan_t p, int64_t K, int P) {
   a.LE_off = a.E_off + a.rec_bytes;
   a.lo_off = a.LE_off + a.rec_bytes;
   a.part_off = a.lo_off + align_up((size_t)(P + 1) * 8);
-  a.nparts = std::max<int64_t>(async_adjoint_blocks(p->N), async_tiled_tiles(p->dtype, p->N, P));
-  a.ends_off = a.part_off + align_up((size_t)a.nparts * 8);
+  const int64_t blocks = async_adjoint_blocks(p->N);
+  const int64_t tiles =
+      async_tiled_from(p->N, P) > 0 ? async_tiled_tiles(p->dtype, p->N, P) : 0;
+  a.tiled = p->opts.sync_kernel != HEAT1D_SYNC_STEP && tiles > 0 && K >= async_tiled_from(p->N, P);
+  a.nparts = a.tiled ? tiles : blocks;
+  a.ends_off = a.part_off + align_up((size_t)std::max(blocks, tiles) * 8);
   a.ord_off = a.ends_off + align_up(16);
-  a.ord_bytes = align_up((size_t)std::max<int64_t>(async_tiled_tiles(p->dtype, p->N, P), 0) * 4);
+  a.ord_bytes = align_up((size_t)tiles * 4);
   a.total = a.ord_off + 2 * a.ord_bytes;
   return a;
 }
@@ -1493,10 +1498,10 @@ int heat1d_run_async_adjoint(heat1d_plan_t p, const void* u0, const void* gK, do
                   : launch_impose_ends(p->dtype, u0, u0s, N, 1, c1, cN, s));
   HEAT1D_TRY(launch_async_edges(p->dtype, u0s, A.E, A.lo, P, N, A.ring, s));
   // Register tiles of up to T steps per launch where every subdomain is
-  // long enough (ring tiles on a ring; opts.sync_kernel =
-  // HEAT1D_SYNC_STEP asks for one launch per step); both give the same values
-  // bit for bit.
-  const bool tiled = p->opts.sync_kernel != HEAT1D_SYNC_STEP && async_tiled_applies(N, P, d);
+  // long enough and the run has steps for it (ring tiles on a ring;
+  // opts.sync_kernel = HEAT1D_SYNC_STEP asks for one launch per step); both give
+  // the same values bit for bit.
+  const bool tiled = L.tiled;
   const int T = async_tiled_depth();
   if (tiled)
     HEAT1D_TRY(launch_async_tiled_order(A, (int*)A.ord_lock, (int*)A.ord_adj, s));

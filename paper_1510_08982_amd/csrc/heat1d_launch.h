@@ -158,6 +158,8 @@ hipError_t launch_async_lockstep(const AsyncAdjStep& a, const void* cur, void* n
 // for bit the per-step launches): from the state `in` of step k0, `steps` steps,
 // the last state to `out`.
 bool async_tiled_applies(int64_t N, int P, int d);
+// Steps from which a run takes the tiles; 0: never.
+int async_tiled_from(int64_t N, int P);
 int async_tiled_depth();
 hipError_t launch_async_lockstep_tiled(const AsyncAdjStep& a, const void* in, void* out, int k0,
                                        int steps, int record, hipStream_t s);

@@ -997,6 +997,23 @@ bool async_tiled_applies(int64_t N, int P, int d) {
   return d + 2 <= kHistQ && (P == 1 || N / P >= kFitMin);
 }
 
+// A launch of tiles costs about as much for one step as for ten, being mostly halo
+// where the subdomains are short and the rod long: FP32, 2^24 points in subdomains
+// of 144 / 300 / 1000, K = 1 / 3 / 6 in us: a launch a step 211 / 464 / 815, 215 /
+// 494 / 913, 197 / 424 / 729; tiles 681 / 890 / 1214, 389 / 493 / 650, 318 / 365 /
+// 441.  2^20 points of 144: 48 / 88 / 151 against 77 / 93 / 118.  Up to 2^18 the
+// launches are what counts, and tiles have fewer (50 / 70 / 124, 45 / 46 / 45).  A
+// single step of long subdomains reads less by a launch a step (FP64, 2^22 points:
+// 106 against 114; two 126 against 116).
+int async_tiled_from(int64_t N, int P) {
+  if (!async_tiled_applies(N, P, 0)) return 0;
+  if (N <= (int64_t(1) << 18)) return 1;
+  if (!fitted(N, P)) return 2;
+  const int64_t sub = N / P;
+  const int from = sub < 200 ? 12 : sub < 600 ? 8 : 4;
+  return N <= (int64_t(1) << 21) ? from / 2 : from;
+}
+
 // Tiles of a piece (of at most N/P + 1 + 4 points), in whole vectors.
 static int fit_parts(int64_t N, int P) { return (int)((N / P + 5 + kFitOwn - 5) / (kFitOwn - 4)); }
 

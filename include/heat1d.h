@@ -256,7 +256,7 @@ int heat1d_run_sync_observed(heat1d_plan_t plan, const void *u0, void *uK, doubl
  *     function; reads before step 0 read step 0.  Deterministic.
  *     On plans that leave opts.sync_kernel and opts.jitter open, runs of 448
  *     steps or more without `stats`, whose subdomains are longer than twice the
- *     reach of a stage of steps, go as independent strips about the subdomain
+ *     reach of a stage of seven steps or more (from 16 points on), go as independent strips about the subdomain
  *     edges instead of subdomains that trade values (the same values: delays are
  *     a function of the seed), the points between them by band passes
  *     (HEAT1D_SYNC_AUTO) to rounding; a point that is not finite sends the run

@@ -272,6 +272,13 @@ __global__ __launch_bounds__(128) void strip_kernel(const StripArgs<F> a) {
   }
 }
 
+// Shortest stage.  A stage takes 7 us or more, the persistent kernel 1.0 to 1.3 us a
+// step: 4096 points, d = 4, K = 2000, FP32, subdomains of 6 / 8 / 12 / 16 / 24 points
+// (stages of 2, 3, 5, 7 and 11 steps): 2498 / 2335 / 2462 / 2241 / 2447 us there, 5236
+// / 3537 / 2416 / 1742 / 1222 as strips; with d = 50, whose reads wait least, 460
+// against 567 at 12 points and 442 against 411 at 16 (K = 448).
+constexpr int kStripMinSteps = 7;
+
 constexpr int kStripM[] = {4, 5, 6, 7, 8, 10, 12, 14, 16, 18, 20};
 
 template <typename F>
@@ -346,7 +353,7 @@ StripPlan strip_plan(int dtype, int64_t N, int P, double r, int64_t K, int d, in
         const int64_t mid = lo + (hi - lo) / 2;
         (band_reach_bound(dtype, r, mid) <= reach ? lo : hi) = mid;
       }
-      if (lo < 1) continue;
+      if (lo < kStripMinSteps) continue;
       const int64_t stages = (K + lo - 1) / lo, T = (K + stages - 1) / stages;
       if (stages > most) continue;
       const int64_t R = band_reach_bound(dtype, r, T);

@@ -71,3 +71,16 @@ def test_edge_values_are_right_where_four_points_a_lane_trade(dt, N, P, d, K, r,
         run_against_oracle(dt, N, P, d, K, r, ring, u0, 0.0, 1.0, plan)
         _, T, M = strips_of(plan)
         assert M == 4 and T > 32
+
+
+@pytest.mark.parametrize("ring", [False, True])
+@pytest.mark.parametrize("dt,sub,strips", [("f64", 4, False), ("f32", 6, False), ("f32", 15, False),
+                                           ("f64", 16, True), ("f32", 17, True)])
+def test_stages_of_few_steps_are_left_to_the_persistent_kernel(dt, sub, strips, ring):
+    N, d, K = 1000, 4, 500
+    f = np_dtype(dt)
+    u0 = workloads.as_dtype(np.random.default_rng(sub).uniform(-1, 1, N), f)
+    r = workloads.as_dtype(0.45, f)
+    with AsyncPlan(N, N // sub, torch_dtype(dt), max_delay=d, periodic=ring) as plan:
+        run_against_oracle(dt, N, N // sub, d, K, r, ring, u0, 1.0, -1.0, plan)
+        assert ("strips=" in plan.describe()) == strips

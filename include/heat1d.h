@@ -221,7 +221,10 @@ int heat1d_run_sync(heat1d_plan_t plan, const void *u0, void *uK, double r, doub
 
 /* Time every candidate synchronous kernel configuration on the caller's
  * buffers for `K_probe` steps, keep the fastest in the plan and return its
- * time in *best_ms (may be NULL).  Synchronises `stream`.  uK is overwritten. */
+ * time in *best_ms (may be NULL).  A plan that may take band passes keeps them
+ * for the runs that are long enough: from the times of a pass and of the fastest
+ * kernel's step (heat1d_plan_describe: band_from).  Synchronises `stream`.  uK
+ * is overwritten. */
 int heat1d_autotune_sync(heat1d_plan_t plan, const void *u0, void *uK, double r, int64_t K_probe,
                          void *workspace, void *stream, double *best_ms);
 
@@ -235,7 +238,8 @@ int heat1d_autotune_sync(heat1d_plan_t plan, const void *u0, void *uK, double r,
  * run); it must not overlap the other buffers.  every >= 1.  The state after
  * each multiple of `every` steps is the plan's own kernel's, so uK equals
  * heat1d_run_sync's for the same plan when `every` is a multiple of the
- * plan's pass depth (else the passes are cut at the multiples of `every`).
+ * plan's pass depth (else the passes are cut at the multiples of `every`, as band
+ * passes are: those agree with heat1d_run_sync to rounding).
  * workspace: heat1d_observed_workspace_bytes(plan) bytes. */
 size_t heat1d_observed_workspace_bytes(heat1d_plan_t plan);
 int heat1d_run_sync_observed(heat1d_plan_t plan, const void *u0, void *uK, double r, double c1,

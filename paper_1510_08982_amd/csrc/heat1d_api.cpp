@@ -1015,21 +1015,28 @@ int heat1d_autotune_sync(heat1d_plan_t p, const void* u0, void* uK, double r, in
       win = c;
     }
   }
-  // band passes against the best of them, where the plan may take them
-  if (status == HEAT1D_OK && takes_band(p, r, K_probe, K_probe, workspace)) {
+  // Band passes against the best of them, where the plan may take them.  A pass
+  // costs nearly the same whatever its steps, stepping in proportion to them: the
+  // probe says from how many steps on passes are faster, not whether they are.
+  if (status == HEAT1D_OK && p->band_from > 0) {
     char* scr = (char*)workspace + sync_state_bytes(p);
-    float ms = 0.f;
-    for (int rep = 0; rep < 2 && status == HEAT1D_OK; ++rep) {
+    const int32_t least = band_from_steps(p->dtype, p->N, p->nrods, ring);
+    const int64_t Kb = fp32_drifts(p->dtype, r, K_probe) ? least : std::max<int64_t>(K_probe, least);
+    double pass = 1e300;
+    for (int rep = 0; rep < 3 && status == HEAT1D_OK; ++rep) {
       hipEventRecord(a, s);
-      status = run_band(p, p->nrods, u0, uK, r, 0.0, 0.0, K_probe, workspace, scr, nullptr,
-                        nullptr, nullptr, s);
+      status = run_band(p, p->nrods, u0, uK, r, 0.0, 0.0, Kb, workspace, scr, nullptr, nullptr,
+                        nullptr, s);
       hipEventRecord(b, s);
       if (status == HEAT1D_OK && hipEventSynchronize(b) != hipSuccess) status = HEAT1D_EHIP;
+      float ms = 0.f;
       if (status == HEAT1D_OK) hipEventElapsedTime(&ms, a, b);
+      if (rep > 0) pass = std::min(pass, (double)ms);
     }
     if (status == HEAT1D_OK) {
-      if (ms < best) best = ms;
-      else p->band_from = 0;
+      const double from = std::ceil(pass * (double)K_probe / best);
+      p->band_from = (int32_t)std::min(std::max(from, (double)least), 2147483647.0);
+      if (Kb == K_probe && pass < best) best = pass;
     }
   }
   hipEventDestroy(a);

@@ -302,6 +302,31 @@ __device__ __forceinline__ F band_point(const BandRod<F>& a, int64_t q) {
   return a.in[q];
 }
 
+// A quarter of band_point(a, q) in double, which no finite state takes out of range
+// (an image is up to three times the largest value), and of the line.
+template <typename F>
+__device__ __forceinline__ double band_line_quarter(const BandRod<F>& a, int64_t i) {
+  const double c1 = 0.25 * (double)a.c1, cN = 0.25 * (double)a.cN;
+  return c1 + (cN - c1) * ((double)i / (double)(a.N - 1));
+}
+template <typename F>
+__device__ double band_point_quarter(const BandRod<F>& a, int64_t q) {
+  const int64_t N = a.N;
+  if (a.straight) {
+    const int64_t P = 2 * (N - 1);
+    q %= P;
+    if (q < 0) q += P;
+    if (q == 0 || q == N - 1) return 0.0;
+    return q < N - 1 ? 0.25 * (double)a.in[q] - band_line_quarter(a, q)
+                     : band_line_quarter(a, P - q) - 0.25 * (double)a.in[P - q];
+  }
+  if (q <= 0) return q == 0 ? 0.25 * (double)a.c1 : 0.5 * (double)a.c1 - 0.25 * (double)a.in[-q];
+  if (q >= N - 1)
+    return q == N - 1 ? 0.25 * (double)a.cN
+                      : 0.5 * (double)a.cN - 0.25 * (double)a.in[2 * (N - 1) - q];
+  return 0.25 * (double)a.in[q];
+}
+
 // The value a step reads at point j of the rod.
 template <typename F>
 __device__ __forceinline__ F band_value(const BandRod<F>& a, int64_t j) {
@@ -338,7 +363,7 @@ __device__ __forceinline__ void band_tile(const BandRod<F>& a, int64_t t0, BandR
   constexpr int kThreads = WO * WS * kWave;
   constexpr int kStride = 16 + B::pad;  // of 16 points in LDS
   constexpr int kOut = NT * WO * kBandTile;
-  __shared__ int s_first, s_last;
+  __shared__ int s_first, s_last, s_lost;
   __shared__ double s_dot[WO * WS];
   const int span = kOut + 2 * a.Hp;            // points of the tile with its halos
   F* wl = xs + span / 16 * kStride;            // weights, w(d) at d + Hp + 15
@@ -348,6 +373,7 @@ __device__ __forceinline__ void band_tile(const BandRod<F>& a, int64_t t0, BandR
   if (tid == 0) {
     s_first = 0x7fffffff;
     s_last = -1;
+    s_lost = 0;
   }
   for (int j = tid; j < 2 * a.Hp + 32; j += kThreads) {
     int d = j - a.Hp - 15;
@@ -357,7 +383,7 @@ __device__ __forceinline__ void band_tile(const BandRod<F>& a, int64_t t0, BandR
   }
   __syncthreads();
 
-  // the state, with zeros for points that are not finite: their cones are
+  // the state, with zeros for points that are not finite: what they reach is
   // written by band_cone
   const int64_t q0 = t0 - a.Hp;  // rod point of xs[0]
   const bool aligned = ((uintptr_t)(a.in + q0) & 15u) == 0;
@@ -384,7 +410,10 @@ __device__ __forceinline__ void band_tile(const BandRod<F>& a, int64_t t0, BandR
       for (int e = 0; e < V; ++e) {
         const bool own = p + e >= a.Hp && p + e < a.Hp + kOut && q + e < N;
         const bool bad = own && !band_finite(band_value(a, q + e));
-        if (!band_finite(pv[e])) pv[e] = F(0);
+        if (!band_finite(pv[e])) {
+          pv[e] = F(0);
+          s_lost = 1;
+        }
         if (bad) {
           atomicMin(&s_first, (int)(q + e - t0));
           atomicMax(&s_last, (int)(q + e - t0));
@@ -396,7 +425,8 @@ __device__ __forceinline__ void band_tile(const BandRod<F>& a, int64_t t0, BandR
   __syncthreads();
   if (tid == 0) {
     if (rec != nullptr) *rec = BandRec{s_first, s_last};
-    if (s_last >= 0) atomicOr(flag, 1);
+    // (an image of a finite point that is out of range counts too)
+    if (s_last >= 0 || s_lost) atomicOr(flag, 1);
   }
 
   const int n = lane & 15, g = lane >> 4;
@@ -560,7 +590,10 @@ __device__ __forceinline__ void band_tile(const BandRod<F>& a, int64_t t0, BandR
 // it one point a step each way, NaN inside the cone (the step subtracts an
 // infinity from itself) and, at exactly T steps' distance, the infinity itself.
 // Writes those cones into the tile of kout points at index `tile` of one rod
-// with `tiles` of them (rec: one record each).
+// with `tiles` of them (rec: one record each).  And where an image of a point about
+// an end (or the point less the ends' line) is out of the type's range though the
+// state is not, as 2 c1 - u with c1 = 1e38 and u = -2e38: the product took 0 for it,
+// and the points that it reaches are summed here from quarters.
 template <typename F>
 __device__ void band_cone(const BandRod<F>& a, int64_t tile, int64_t tiles, int kout,
                           const BandRec* rec, int64_t T) {
@@ -602,7 +635,22 @@ __device__ void band_cone(const BandRod<F>& a, int64_t tile, int64_t tiles, int 
       }
     }
     const int64_t near = min(dist[0], dist[1]);
-    if (near > T) continue;
+    if (near > T) {
+      if (a.ring || (!a.straight && i >= a.H && i + a.H <= N - 1)) continue;
+      bool lost = false;
+      for (int64_t q = i - a.H; q <= i + a.H && !lost; ++q) lost = !band_finite(band_point(a, q));
+      if (!lost) continue;
+      double sum = 0.0, sum2 = 0.0;
+      for (int d = -a.H; d <= a.H; ++d) {
+        const double v = band_point_quarter(a, i + d);
+        sum = __builtin_fma((double)a.w[d < 0 ? -d : d], v, sum);
+        if (a.z != nullptr) sum2 = __builtin_fma((double)a.w2[d < 0 ? -d : d], v, sum2);
+      }
+      if (a.straight) sum += band_line_quarter(a, i);
+      if (a.out != nullptr) a.out[i] = (F)(4.0 * sum);
+      if (a.z != nullptr) a.z[i] = (F)(4.0 * sum2);
+      continue;
+    }
     F y = (F)__builtin_nan("");
     if (near == T) y = (dist[0] == T ? val[0] : F(0)) + (dist[1] == T ? val[1] : F(0));
     if (a.out != nullptr) a.out[i] = y;

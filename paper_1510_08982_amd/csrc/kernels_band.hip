@@ -225,7 +225,9 @@ __device__ __forceinline__ void band_weights(F* w, int H, double T, double r, bo
       k += d;
       if (k >= M) k -= M;
     }
-    w[d] = (F)(sum / (double)M);
+    // The sum is off by some 1e-17 whatever the weight is.  The weights of steps are
+    // means of means, none is negative, and a state without negative points keeps none.
+    w[d] = (F)(lap ? sum / (double)M : fmax(sum / (double)M, 0.0));
   }
 }
 

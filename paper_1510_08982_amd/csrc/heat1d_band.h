@@ -58,8 +58,8 @@ struct BandPass {
   int32_t* flag = nullptr;  // raise this flag instead, and keep no records: the
                             // caller does without launch_band_cones, and scratch
                             // needs kBandWeightBytes only
-  // z, when not NULL, receives D A^(T-1) applied to the state (D the second
-  // difference): K z is du(K)/dr, see heat1d_backward_checkpointed
+  // z, when not NULL (FP64 only), receives D A^(T-1) applied to the state (D the
+  // second difference): K z is du(K)/dr, see heat1d_backward_checkpointed
   void* z = nullptr;
   // dot, when not NULL: dot_scale times the sum of in . dot_with over each
   // tile's inner points, one double per tile (band_tiles per rod)

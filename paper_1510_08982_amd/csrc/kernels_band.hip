@@ -14,11 +14,10 @@
 //
 // What bounds it: FP32 (FP64) matrix rate, 2 Hp + 16 multiply-adds per point,
 // and below a reach of about 60 points the copy of the state.  One rod of 2^26
-// FP32 points, K = 2000, r = 0.25 (Hp = 208): 0.52 ms, where eight passes of the
-// autotuned wide register tiles took 5.5 ms; the products alone need 0.38 ms at
-// the matrix rate and the copy 0.10 ms.  2^25 FP64 points: 0.70 ms, from 11.7
-// ms stepped (untuned).  4096 FP64 points, K = 20000: 15 us, from 8.5 ms on one
-// compute unit.
+// FP32 points, K = 2000, r = 0.25 (Hp = 192): 0.455 ms, where eight passes of the
+// autotuned wide register tiles took 5.8 ms; the products alone need 0.35 ms at
+// the rate of large matrix products (154 TFLOP/s) and the copy 0.10 ms.  4096 FP64
+// points, K = 20000: 16 us, from 8.3 ms on one compute unit.
 #include <cmath>
 #include <algorithm>
 
@@ -40,10 +39,6 @@ template <> struct Band<float> {
   // hundred times at the size of the result (3.5e-7 of it against 64 bits on
   // the 2^26-point rod, where stepping has 0.9e-7)
   static constexpr int group = 4;
-  // tiles of 256 outputs a wavefront: 4 leave room for five wavefronts a SIMD where
-  // 8, which read each weight half as often, leave three (N = 2^26, K = 2000 491 ->
-  // 455 us, on uniform noise 549 -> 538; N = 2^22, K = 300 37.0 -> 35.2 us)
-  static constexpr int nt_large = 4;
   static __device__ __forceinline__ Acc mma(float a, float b, Acc c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
@@ -55,7 +50,6 @@ template <> struct Band<double> {
   using Sum = f64x4;
   static constexpr int pad = 2;
   static constexpr int group = 1 << 20;  // one running sum
-  static constexpr int nt_large = 4;
   static __device__ __forceinline__ Acc mma(double a, double b, Acc c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
@@ -64,6 +58,11 @@ template <> struct Band<double> {
 };
 
 constexpr int kBandTile = 256;    // outputs of one MFMA tile
+// Tiles of 256 outputs a wavefront of the largest blocks: in FP32 4 leave room for
+// five wavefronts a SIMD where 8, which read each weight half as often, leave three
+// (N = 2^26, K = 2000 491 -> 455 us, on uniform noise 549 -> 538; N = 2^22, K = 300
+// 37.0 -> 35.2 us); 3, and FP64 with other counts, were within noise.
+constexpr int kBandLarge = 4;
 constexpr int kStepWeights = 64;  // runs whose weights are stepped
 
 // Record of the points of a tile that are not finite: first and last of them,
@@ -707,15 +706,15 @@ __global__ __launch_bounds__(256) void band_cone_kernel(const BandArgs<F> a, int
   }
 }
 
-// Outputs of a block.  Large tiles (the weights are read once per 8 or 4
-// products, the halos are a twentieth of the tile) where they still give every
+// Outputs of a block.  Large tiles (a weight is read once per 4 products, the
+// halos are a twentieth to a tenth of the tile) where they still give every
 // CU two blocks and pad a rod by no more than an eighth; else 2048 outputs; else
 // 256, eight wavefronts sharing the K range, so that a rod of a few thousand
 // points still spreads over the chip.
 // Passes that also write z hold twice the sums: half as many tiles.
 template <typename F>
 static int band_out(int64_t N, int64_t nrods, bool two = false) {
-  const int64_t large = (int64_t)Band<F>::nt_large / (two ? 2 : 1) * 4 * kBandTile;
+  const int64_t large = (int64_t)kBandLarge / (two ? 2 : 1) * 4 * kBandTile;
   const int64_t nl = (N + large - 1) / large, nm = (N + 2047) / 2048;
   if (nl * nrods >= 512 && nl * large * 8 <= nm * 2048 * 9) return (int)large;
   if (nm * nrods >= 512 && N >= 1024) return 2048;
@@ -811,13 +810,13 @@ static hipError_t band_dispatch(const BandPass& p, hipStream_t s) {
   const int o = band_out<F>(p.N, p.nrods, kTwo);
   if (o == kBandTile) return band_launch<F, 1, 1, 8, kTwo>(a, p.nrods, s);
   if (o == 2048) return band_launch<F, 2, 4, 1, kTwo>(a, p.nrods, s);
-  return band_launch<F, Band<F>::nt_large / (kTwo ? 2 : 1), 4, 1, kTwo>(a, p.nrods, s);
+  return band_launch<F, kBandLarge / (kTwo ? 2 : 1), 4, 1, kTwo>(a, p.nrods, s);
 }
 
 hipError_t launch_band_pass(const BandPass& p, hipStream_t s) {
-  if (p.dtype == 0)
-    return p.z != nullptr ? band_dispatch<float, true>(p, s) : band_dispatch<float, false>(p, s);
-  return p.z != nullptr ? band_dispatch<double, true>(p, s) : band_dispatch<double, false>(p, s);
+  if (p.z == nullptr)
+    return p.dtype == 0 ? band_dispatch<float, false>(p, s) : band_dispatch<double, false>(p, s);
+  return p.dtype == 0 ? hipErrorInvalidValue : band_dispatch<double, true>(p, s);
 }
 
 template <typename F>

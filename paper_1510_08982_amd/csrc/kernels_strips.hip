@@ -176,22 +176,21 @@ __device__ __forceinline__ void strip_run(F (&u)[M], const StripArgs<F>& a, int 
       }
       __syncthreads();
       since = 0;
-      // The handover of this step again, for the points that changed: with M = 4 the
-      // wrong values have just come as far as the edge point of the other side (with r^32
-      // of what lies beyond the cut end), and a delay of 0 and the ring took it.  What a
-      // delayed read of this step brought is older and stands.
+      // The handover of this step again, for the points that changed.  Where the trade
+      // comes as late as the overlap allows, the wrong values have just reached the edge
+      // point of the other side (with r^32 of what lies beyond the cut end at M = 4),
+      // and a delay of 0 and the ring took it.  What a delayed read of this step brought
+      // is older and stands.
       const F l = from_lower_lane(u[M - 1]), rr = from_upper_lane(u[0]);
-      if constexpr (kEdge) {
+      bool stands = kEdge;
+      if constexpr (kEdge && 32 * kSwap == kOver * M) {
         const int now = ((kb + 32) & (kRing - 1)) * kSlot;
-        const bool late = table[(kb + 32) & (kRing - 1)][side] != now + side * (int)sizeof(F);
-        left = late && lane == la + 1 ? left : l;
-        right = late && lane == la ? right : rr;
+        stands = table[(kb + 32) & (kRing - 1)][side] != now + side * (int)sizeof(F);
         *reinterpret_cast<F*>(rb + now + own) = side ? u[M - 1] : u[0];
         old = *reinterpret_cast<F*>(rb + slot);
-      } else {
-        left = l;
-        right = rr;
       }
+      left = stands && lane == la + 1 ? left : l;
+      right = stands && lane == la ? right : rr;
     }
   }
 }

@@ -1016,28 +1016,38 @@ int heat1d_autotune_sync(heat1d_plan_t p, const void* u0, void* uK, double r, in
     }
   }
   // Band passes against the best of them, where the plan may take them.  A pass
-  // costs nearly the same whatever its steps, stepping in proportion to them: the
-  // probe says from how many steps on passes are faster, not whether they are.
+  // costs nearly the same whatever its steps, stepping a start and so much a step:
+  // the line through its times for two step counts says from how many steps on
+  // passes are faster, which the probe alone does not (32 steps of 4096 FP64 points
+  // are 9 us, 90 are 13, a pass is 15).
   if (status == HEAT1D_OK && p->band_from > 0) {
-    char* scr = (char*)workspace + sync_state_bytes(p);
+    // the better of two runs after a warm one, in ms; K < 0: passes of -K steps
+    auto timed = [&](int64_t K) {
+      double t = 1e300;
+      for (int rep = 0; rep < 3 && status == HEAT1D_OK; ++rep) {
+        hipEventRecord(a, s);
+        status = K > 0 ? run_sync_impl(p, u0, uK, r, 0.0, 0.0, K, workspace, s, win.kernel, win.T,
+                                       win.M, win.waves, win.fuse)
+                       : run_band(p, p->nrods, u0, uK, r, 0.0, 0.0, -K, workspace,
+                                  (char*)workspace + sync_state_bytes(p), nullptr, nullptr,
+                                  nullptr, s);
+        hipEventRecord(b, s);
+        if (status == HEAT1D_OK && hipEventSynchronize(b) != hipSuccess) status = HEAT1D_EHIP;
+        float ms = 0.f;
+        if (status == HEAT1D_OK) hipEventElapsedTime(&ms, a, b);
+        if (rep > 0) t = std::min(t, (double)ms);
+      }
+      return t;
+    };
     const int32_t least = band_from_steps(p->dtype, p->N, p->nrods, ring);
-    const int64_t Kb = fp32_drifts(p->dtype, r, K_probe) ? least : std::max<int64_t>(K_probe, least);
-    double pass = 1e300;
-    for (int rep = 0; rep < 3 && status == HEAT1D_OK; ++rep) {
-      hipEventRecord(a, s);
-      status = run_band(p, p->nrods, u0, uK, r, 0.0, 0.0, Kb, workspace, scr, nullptr, nullptr,
-                        nullptr, s);
-      hipEventRecord(b, s);
-      if (status == HEAT1D_OK && hipEventSynchronize(b) != hipSuccess) status = HEAT1D_EHIP;
-      float ms = 0.f;
-      if (status == HEAT1D_OK) hipEventElapsedTime(&ms, a, b);
-      if (rep > 0) pass = std::min(pass, (double)ms);
-    }
+    const double one = timed(least), two = timed(2 * (int64_t)least), pass = timed(-2 * (int64_t)least);
     if (status == HEAT1D_OK) {
-      const double from = std::ceil(pass * (double)K_probe / best);
-      p->band_from = (int32_t)std::min(std::max(from, (double)least), 2147483647.0);
-      if (Kb == K_probe && pass < best) best = pass;
+      double from = least;
+      if (two > one) from = least * std::max(1.0, 1.0 + (pass - one) / (two - one));
+      p->band_from = (int32_t)std::min(std::ceil(from), 2147483647.0);
     }
+    if (status == HEAT1D_OK && takes_band(p, r, K_probe, K_probe, workspace))
+      best = std::min(best, timed(-K_probe));
   }
   hipEventDestroy(a);
   hipEventDestroy(b);

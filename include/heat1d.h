@@ -195,8 +195,12 @@ void heat1d_plan_destroy(heat1d_plan_t plan);
 
 /* Bytes of workspace each call needs.  For the sync path this is one state
  * (N*B elements), and for a plan that may take band passes their weights and
- * tile records (33 KB, and 8 bytes per 256 points); the async path adds its halo ring and flags; the adjoint adds
- * its checkpoints for K steps; the batched path holds its work queues. */
+ * tile records (33 KB, and 8 bytes per 256 points); the async path has its halo
+ * ring and flags and, unless opts.sync_kernel or opts.jitter is set, what emulated
+ * runs by strips need: 33 KB of weights, 128 values per subdomain edge and, where
+ * that stays within 4 MiB, a second state; the adjoint has its checkpoints for K
+ * steps; the batched path its work queues, and for the rods that take band passes
+ * their tiles, records and weights (at most 2049 a rod). */
 size_t heat1d_sync_workspace_bytes(heat1d_plan_t plan);  /* any sync kernel */
 size_t heat1d_async_workspace_bytes(heat1d_plan_t plan);
 size_t heat1d_adjoint_workspace_bytes(heat1d_plan_t plan, int64_t K);
@@ -417,7 +421,8 @@ int heat1d_run_async_ensemble_adjoint(heat1d_plan_t plan, const void *u0, const 
  * workspace holds (all of them up to K = 32 (ceil(K/S) + S - 1)): grad_u0 and uK
  * are the same bit for bit.  In the emulated mode the delays are a
  * fixed function of the seed, so the forward values equal those of
- * heat1d_run_async bit for bit.  u0, gK: N elements (device, read only; they
+ * heat1d_run_async: bit for bit where that steps, to rounding where it takes
+ * strips and band passes (448 steps or more).  u0, gK: N elements (device, read only; they
  * may alias); uK: NULL or N elements, receives u(K); grad_u0: N elements;
  * grad_r, grad_c1, grad_cN: one device double each, summed in double in a
  * fixed order.  workspace: heat1d_async_adjoint_workspace_bytes(plan, K)
@@ -446,7 +451,9 @@ int heat1d_batched_prepare(heat1d_plan_t plan, void *workspace, void *stream);
  * r in (0, 0.5]); K: int32 device array equal to the plan's K_host.  Rods of
  * 448 steps or more (FP32: at most 5166) take a band pass (HEAT1D_SYNC_AUTO)
  * unless opts.waves or opts.sync_kernel is set; the others step, bit for bit as
- * one launch per step does. */
+ * one launch per step does.  (The FP32 limit does not depend on r here, as r is
+ * device memory: a rod of small r that heat1d_run_sync steps, with the drift that
+ * FP32 stepping has, takes the pass, which has none.) */
 int heat1d_run_batched(heat1d_plan_t plan, const void *u0, void *uK, const int64_t *offsets,
                        const double *r, const double *c1, const double *cN, const int32_t *K,
                        void *workspace, void *stream);

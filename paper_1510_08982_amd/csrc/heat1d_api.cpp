@@ -48,16 +48,20 @@ int32_t band_from_steps(int dtype, int64_t N, int64_t nrods, bool ring) {
 }
 
 // The same for the rods of a batch, and for the long rods of an emulated
-// asynchronous run.  Shorter runs there agree bit for bit with one launch per
-// step, which callers compare them with, and they are short either way.
+// asynchronous run: a line of contract, not of speed.  Shorter runs there give the
+// bits of one launch per step, which programs compare them with, and that costs
+// them: 4096 rods of 256 to 65536 FP32 points, K = 64 / 200 / 447, take 585 / 1166 /
+// 2325 us in the queues where passes would take 239 / 250 / 289; an emulated run of
+// 2^18 FP32 points, 1024 subdomains, 101 / 261 / 552 against 38 / 56 / 93.
 constexpr int32_t kBatchBandFrom = 448;
 
 // FP32 stepping drifts: late in a run the change of a point in one step is a
-// few roundings of its value, and they do not average out.  Against 64 bits
-// the single-step kernels are off by 1e-6 to 2e-5 of the state after K (1 +
-// 0.1 / r) = 6200 steps, growing to 8e-5 at 20000, where one pass stays at 2e-7.
-// Beyond this length FP32 runs keep stepping, or every result of theirs would
-// move by that much.
+// few roundings of its value, and they do not average out.  Against 64 bits the
+// single-step kernels are off by 1e-6 (noise) to 6e-5 (a smooth profile) of the
+// state after K (1 + 0.1 / r) = 6200 steps, and by 2e-4 to 5e-4 at 20000 steps,
+// where one pass stays at 2e-7.  FP32 runs beyond that length keep stepping, not
+// for speed or accuracy, but because results that programs have from them would
+// move by more than 2e-5.
 bool fp32_drifts(int dtype, double r, int64_t K) {
   return dtype == HEAT1D_F32 && (double)K * (1.0 + 0.1 / r) > 6200.0;
 }
@@ -604,9 +608,12 @@ void batched_split_band(heat1d_plan_t p) {
   for (int32_t b : p->by_work) {
     const int h = band_reach_bound(p->dtype, 0.5, std::max(p->Kh[b], 1));
     const int64_t nt = (p->Nh[b] + kBandBatchTile - 1) / kBandBatchTile;
-    // r is known to the run only; 1/2 drifts least
-    if (p->Kh[b] < kBatchBandFrom || fp32_drifts(p->dtype, 0.5, p->Kh[b]) || h > kBandMaxReach || tiles + nt > (1 << 22) ||
-        w + h + 1 > INT32_MAX) {
+    // r is known on the device only, when the rod's place has long been chosen: the
+    // line is that of r = 1/2, 5166 steps, whatever r is.  (A line by each rod's r
+    // would send rods of small r back to the queues, for results that are further off:
+    // a smooth rod, r = 0.05, K = 5000, is 1.4e-4 off there and 2e-7 by a pass.)
+    if (p->Kh[b] < kBatchBandFrom || fp32_drifts(p->dtype, 0.5, p->Kh[b]) ||
+        h > kBandMaxReach || tiles + nt > (1 << 22) || w + h + 1 > INT32_MAX) {
       rest.push_back(b);
       continue;
     }

@@ -84,3 +84,24 @@ def test_stages_of_few_steps_are_left_to_the_persistent_kernel(dt, sub, strips, 
     with AsyncPlan(N, N // sub, torch_dtype(dt), max_delay=d, periodic=ring) as plan:
         run_against_oracle(dt, N, N // sub, d, K, r, ring, u0, 1.0, -1.0, plan)
         assert ("strips=" in plan.describe()) == strips
+
+
+@pytest.mark.parametrize("dt,P,sub", [("f32", 5000, 4000), ("f64", 1900, 40)])
+def test_runs_that_would_take_strips_are_refused_before_any_launch(dt, P, sub):
+    """More subdomains than can be resident at once: the strips would not need that,
+    but the kernel behind them does, and the refusal leaves uK alone.  (At 1900 of
+    40 FP64 points all can be, and strips run.)"""
+    N, d, K = P * sub, 1, 448
+    x = torch.zeros(N, device=DEV, dtype=torch_dtype(dt))
+    out = torch.full_like(x, 7.0)
+    with AsyncPlan(N, P, torch_dtype(dt), max_delay=d) as plan:
+        print_case(test="strips_occupancy", dt=dt, N=N, P=P)
+        if dt == "f64":
+            plan.run(x, 0.4, 0.25, 0.25, K, d, 1, out=out)
+            assert strips_of(plan)[0] > 0 and float(out[0]) == 0.25
+            return
+        with pytest.raises(abi.Heat1dError) as refused:
+            plan.run(x, 0.4, 0.25, 0.25, K, d, 1, out=out)
+        assert refused.value.status == abi.HEAT1D_EOCCUPANCY
+        torch.cuda.synchronize()
+        assert bool((out == 7.0).all())

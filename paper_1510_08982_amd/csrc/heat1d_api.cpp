@@ -611,7 +611,7 @@ void batched_split_band(heat1d_plan_t p) {
     // r is known on the device only, when the rod's place has long been chosen: the
     // line is that of r = 1/2, 5166 steps, whatever r is.  (A line by each rod's r
     // would send rods of small r back to the queues, for results that are further off:
-    // a smooth rod, r = 0.05, K = 5000, is 1.4e-4 off there and 2e-7 by a pass.)
+    // a smooth rod, r = 0.05, K = 5000, is 1.0e-4 off there and 4e-7 by a pass.)
     if (p->Kh[b] < kBatchBandFrom || fp32_drifts(p->dtype, 0.5, p->Kh[b]) ||
         h > kBandMaxReach || tiles + nt > (1 << 22) || w + h + 1 > INT32_MAX) {
       rest.push_back(b);

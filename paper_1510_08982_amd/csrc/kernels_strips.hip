@@ -19,10 +19,10 @@
 // instructions of the lane's points and about ten more.
 //
 // What bounds it: VALU issue, two wavefronts a SIMD at 1024 strips (3.9 clocks an
-// instruction), latency below.  2^24 FP32 points, P = 1024, d = 4, K = 5000: 1.09 ms for
-// the strips (M = 16) and 0.14 for the points between, where the persistent kernel took
-// 10.8 ms; with one wavefront to a strip 1.67 ms.  4096 FP64 points, P = 16, d = 3, K =
-// 20000: 102 stages of 197 steps, 2.9 ms, from 25.5 ms.
+// instruction), latency below.  2^24 FP32 points, P = 1024, d = 4, K = 5000: 1.15 ms, of
+// which the strips (M = 16) take 1.02 and one band pass the rest, where the persistent
+// kernel took 10.8 ms; with one wavefront to a strip they took 1.67 ms.  4096 FP64
+// points, P = 16, d = 3, K = 20000: 102 stages of 197 steps, 3.0 ms, from 26 ms.
 #include <algorithm>
 #include <cmath>
 

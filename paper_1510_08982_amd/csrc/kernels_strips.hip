@@ -138,7 +138,9 @@ __device__ __forceinline__ void strip_run(F (&u)[M], const StripArgs<F>& a, int 
     old = *reinterpret_cast<F*>(rb + slot);
   }
   handover(a.k0, u[0], u[M - 1]);
-  constexpr int kSwap = kOver * M / 32;  // groups of 32 steps between two exchanges
+  constexpr int kSwap = kOver * M / 32;  // groups of 32 steps between two trades
+  // whether a trade comes as late as the overlap allows, with a weight that counts
+  constexpr bool kAgain = kEdge && 32 * kSwap == kOver * M && kOver * M < 57;
   int since = 0;
   for (int kb = a.k0; kb < kend; kb += 32) {
     const int n = min(32, kend - kb);
@@ -174,21 +176,22 @@ __device__ __forceinline__ void strip_run(F (&u)[M], const StripArgs<F>& a, int 
 #pragma unroll
         for (int j = 0; j < M; ++j) u[j] = swap[1 - wave][o + j];
       }
-      __syncthreads();
       since = 0;
       // The handover of this step again, for the points that changed.  Where the trade
-      // comes as late as the overlap allows, the wrong values have just reached the edge
-      // point of the other side (with r^32 of what lies beyond the cut end at M = 4),
-      // and a delay of 0 and the ring took it.  What a delayed read of this step brought
-      // is older and stands.
-      const F l = from_lower_lane(u[M - 1]), rr = from_upper_lane(u[0]);
+      // comes as late as the overlap allows, what lies beyond the cut ends has just
+      // reached the edge point of the other side, with r^(8 M), and a delay of 0 and the
+      // ring took it: 2^-32 of it at M = 4, where the edge's values are made anew.  (What
+      // a delayed read of this step brought is older and stands.  From M = 8 on it is
+      // 2^-64, less than the 2^-57 that is dropped elsewhere.)
       bool stands = kEdge;
-      if constexpr (kEdge && 32 * kSwap == kOver * M) {
+      if constexpr (kAgain) {
         const int now = ((kb + 32) & (kRing - 1)) * kSlot;
         stands = table[(kb + 32) & (kRing - 1)][side] != now + side * (int)sizeof(F);
         *reinterpret_cast<F*>(rb + now + own) = side ? u[M - 1] : u[0];
         old = *reinterpret_cast<F*>(rb + slot);
       }
+      __syncthreads();
+      const F l = from_lower_lane(u[M - 1]), rr = from_upper_lane(u[0]);
       left = stands && lane == la + 1 ? left : l;
       right = stands && lane == la ? right : rr;
     }

@@ -84,7 +84,11 @@ enum heat1d_sync_kernel {
                                  The same iteration with far fewer roundings: results
                                  agree with the stepping kernels within the stated
                                  tolerances, not bit for bit; a point that is not
-                                 finite spreads as steps spread it.  A run without a
+                                 finite spreads as steps spread it.  A pass takes at
+                                 most e^0.6 off a rod's slowest mode, e^(r T (pi/(N-1))^2)
+                                 in T steps: runs of short rods are cut into
+                                 more of them, and step beyond e^64 or where a cut would
+                                 be shorter than the line above.  A run without a
                                  workspace (allowed where the default is RESIDENT)
                                  steps */
     HEAT1D_SYNC_STEP = 1,     /* one launch per step, two global buffers          */
@@ -451,7 +455,8 @@ int heat1d_batched_prepare(heat1d_plan_t plan, void *workspace, void *stream);
  * r in (0, 0.5]); K: int32 device array equal to the plan's K_host.  Rods of
  * 448 steps or more (FP32: at most 5166) take a band pass (HEAT1D_SYNC_AUTO)
  * unless opts.waves or opts.sync_kernel is set; the others step, bit for bit as
- * one launch per step does.  (The FP32 limit does not depend on r here, as r is
+ * one launch per step does, and so does a rod whose slowest mode loses more than
+ * e^0.6 (HEAT1D_SYNC_AUTO).  (The FP32 limit does not depend on r here, as r is
  * device memory: a rod of small r that heat1d_run_sync steps, with the drift that
  * FP32 stepping has, takes the pass, which has none.) */
 int heat1d_run_batched(heat1d_plan_t plan, const void *u0, void *uK, const int64_t *offsets,
@@ -484,7 +489,7 @@ int heat1d_autotune_batched(heat1d_plan_t plan, const void *u0, void *uK, const 
  * within rounding (not bit for bit) and depends on S only through rounding.
  * uK may be NULL.  FP64 plans that leave opts.sync_kernel open run it as band
  * passes (HEAT1D_SYNC_AUTO) from 24 steps on (56 for 512 or more rods of 257 to
- * 1023 points) and leave, in place of the states, the one vector
+ * 1023 points; not rods of fewer than 21 points, nor K beyond 13 (N-1)^2) and leave, in place of the states, the one vector
  * D A^(K-1) u(0) that dL/dr needs: A, the step, and D, the second difference,
  * commute, so that all K terms of dL/dr are gK . D A^(K-1) u(0). */
 int heat1d_forward_checkpointed(heat1d_plan_t plan, const void *u0, void *uK, double r,

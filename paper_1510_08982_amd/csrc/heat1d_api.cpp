@@ -331,15 +331,20 @@ int64_t band_adjoint_from(heat1d_plan_t p) {
   return p->N > 256 && p->N < 1024 && p->nrods >= 512 ? 56 : 24;
 }
 bool band_adjoint(heat1d_plan_t p, int64_t K) {
-  return p->dtype == HEAT1D_F64 && p->opts.sync_kernel == HEAT1D_SYNC_AUTO &&
-         K >= band_adjoint_from(p) && band_applies(p->dtype, p->N, p->nrods);
+  const int64_t from = band_adjoint_from(p);
+  // r is known to the calls only: at 1/2 a rod decays fastest.  Passes cut for that
+  // are of `from` steps or more, whatever K is.
+  return p->dtype == HEAT1D_F64 && p->opts.sync_kernel == HEAT1D_SYNC_AUTO && K >= from &&
+         band_applies(p->dtype, p->N, p->nrods) &&
+         band_decay(0.5, (double)K, p->N, false) <= kBandDecayRun &&
+         band_decay(0.5, 2.0 * (double)from, p->N, false) <= kBandDecay;
 }
 
 BandAdjLayout band_adjoint_layout(heat1d_plan_t p, int64_t K) {
   BandAdjLayout a{};
   const size_t st = align_up((size_t)p->N * p->nrods * esize(p->dtype));
-  // r = 1/2 reaches furthest: no r takes more passes
-  const bool one = band_run(p->dtype, 0.5, K).passes <= 1;
+  // r = 1/2 reaches furthest and decays fastest: no r takes more passes
+  const bool one = band_run(p->dtype, 0.5, K, p->N, false).passes <= 1;
   a.z_off = 0;
   a.ping_off = st;
   a.spare_off = a.ping_off + (one ? 0 : st);
@@ -445,7 +450,7 @@ int run_band(heat1d_plan_t p, int64_t nrods, const void* in, void* out, double r
   b.dot_scale = (double)K;
   b.dtype = p->dtype;
   b.r = p->dtype == HEAT1D_F32 ? (double)(float)r : r;
-  const BandRun run = band_run(p->dtype, b.r, K);
+  const BandRun run = band_run(p->dtype, b.r, K, p->N, periodic(p));
   b.N = p->N;
   b.nrods = nrods;
   b.c1 = c1;
@@ -478,9 +483,15 @@ int run_band(heat1d_plan_t p, int64_t nrods, const void* in, void* out, double r
   return HEAT1D_OK;
 }
 
-// Whether K steps, of a run of `of` steps in all, take band passes.
+// Whether K steps, of a run of `of` steps in all, take band passes: not where they
+// would have to be cut, for what they take off the state, below the steps from which
+// a pass is faster.
 bool takes_band(heat1d_plan_t p, double r, int64_t K, int64_t of, const void* ws) {
-  return p->band_from > 0 && K >= p->band_from && ws != nullptr && !fp32_drifts(p->dtype, r, of);
+  if (p->band_from == 0 || K < p->band_from || ws == nullptr || fp32_drifts(p->dtype, r, of))
+    return false;
+  const bool ring = periodic(p);
+  return band_decay(r, (double)of, p->N, ring) <= kBandDecayRun &&
+         band_run(p->dtype, r, K, p->N, ring).T >= p->band_from;
 }
 
 int run_sync_impl(heat1d_plan_t p, const void* u0, void* uK, double r, double c1, double cN,
@@ -613,7 +624,8 @@ void batched_split_band(heat1d_plan_t p) {
     // would send rods of small r back to the queues, for results that are further off:
     // a smooth rod, r = 0.05, K = 5000, is 1.0e-4 off there and 4e-7 by a pass.)
     if (p->Kh[b] < kBatchBandFrom || fp32_drifts(p->dtype, 0.5, p->Kh[b]) ||
-        h > kBandMaxReach || tiles + nt > (1 << 22) || w + h + 1 > INT32_MAX) {
+        h > kBandMaxReach || tiles + nt > (1 << 22) || w + h + 1 > INT32_MAX ||
+        (p->Nh[b] > kBandBatchStep && band_decay(0.5, p->Kh[b], p->Nh[b], false) > kBandDecay)) {
       rest.push_back(b);
       continue;
     }
@@ -820,10 +832,12 @@ size_t heat1d_async_workspace_bytes(heat1d_plan_t p) {
 
 size_t heat1d_adjoint_workspace_bytes(heat1d_plan_t p, int64_t K) {
   if (!p || p->batched || K < 0) return 0;
-  if (!band_adjoint(p, K)) return adjoint_layout(p, K).total;
-  // a workspace for K steps also serves fewer, whose checkpoints take more room
-  return std::max(band_adjoint_layout(p, K).total,
-                  adjoint_layout(p, band_adjoint_from(p) - 1).total);
+  // a workspace for K steps also serves fewer, whichever way those go
+  const int64_t from = band_adjoint_from(p);
+  const bool band = band_adjoint(p, K);
+  size_t n = adjoint_layout(p, band ? from - 1 : K).total;
+  if (K >= from && band_adjoint(p, from)) n = std::max(n, band_adjoint_layout(p, K).total);
+  return n;
 }
 
 // Batched workspace: the three queues (int32, 256-byte aligned) and three heads.
@@ -1858,7 +1872,7 @@ int heat1d_forward_checkpointed(heat1d_plan_t p, const void* u0, void* uK, doubl
   const int64_t N = p->N, B = p->nrods;
   if (band) {
     const BandAdjLayout Z = band_adjoint_layout(p, K);
-    const bool one = band_run(p->dtype, r, K).passes <= 1;
+    const bool one = band_run(p->dtype, r, K, N, false).passes <= 1;
     return run_band(p, B, u0, uK || one ? uK : ws + Z.spare_off, r, c1, cN, K, ws + Z.ping_off,
                     ws + Z.scr_off, ws + Z.z_off, nullptr, nullptr, s);
   }
@@ -2028,7 +2042,7 @@ int heat1d_adjoint_ends(heat1d_plan_t p, const void* gK, double r, int64_t K, do
   // traffic that counts: 2^22 points, K = 64 / 96, 67 / 89 us stepped, 71 / 77 by passes.
   const int64_t from = p->N >= (int64_t(1) << 21) ? 80 : 129;
   const int st =
-      band_adjoint(&one, K) && K >= from
+      band_adjoint(&one, K) && K >= from && band_run(p->dtype, r, K, p->N, false).T >= 64
           ? run_band(&one, 1, ws + L.z_off, ws + L.w_off, r, 1.0, 0.0, K, ws + L.ping_off,
                      ws + L.scr_off, nullptr, nullptr, nullptr, s)
           : run_sync_impl(&one, ws + L.z_off, ws + L.w_off, r, 1.0, 0.0, K, ws + L.ping_off, s,

@@ -31,12 +31,29 @@ int band_reach(int dtype, double r, int64_t T);
 // 2^-64 at most: runs of many short passes use it.)
 int band_reach_bound(int dtype, double r, int64_t T);
 
-// How a run of K steps is cut into passes of at most T steps each.
+// What K steps take off the slowest mode of a Dirichlet rod of N points less its
+// ends' line, as a power of e.  (A ring's mean stays; 0.)
+__host__ __device__ inline double band_decay(double r, double K, int64_t N, bool ring) {
+  return ring ? 0.0 : 9.869604401089358 * r * K / ((double)(N - 1) * (double)(N - 1));
+}
+
+// A pass is off by a rounding of the state it reads, whatever it leaves of it, so
+// one of a short rod between zero ends (or a gradient's, which always has them) is
+// off by e^decay roundings of its result: N = 30, r = 1/2, decay 1 / 4 / 10 / 20: FP64
+// 6e-15, 2e-13, 5e-11, 1e-6, FP32 1.4e-6, 3e-5, 8e-3, 130, where steps, which lose a
+// little of a little, stay at 2e-15 and 1e-6.  No pass takes off more than this:
+// cut so, decays of 2 to 20 come out within 2e-15 to 2e-14 and 4e-7.
+constexpr double kBandDecay = 0.6;
+// A run of more than this keeps stepping: its passes' errors add up (FP64, N = 100,
+// decay 63: 9e-14).
+constexpr double kBandDecayRun = 64.0;
+
+// How a run of K steps of N points is cut into passes of at most T steps each.
 struct BandRun {
   int64_t passes = 0;
   int64_t T = 0;  // steps of every pass but the last, which takes the rest
 };
-BandRun band_run(int dtype, double r, int64_t K);
+BandRun band_run(int dtype, double r, int64_t K, int64_t N, bool ring);
 
 constexpr size_t kBandWeightBytes = ((size_t)2 * (kBandMaxReach + 1) * 8 + 16 + 255) / 256 * 256;
 
@@ -78,13 +95,15 @@ hipError_t launch_band_cones(const BandPass& p, hipStream_t s);
 struct BandSlot {
   int64_t off, N;
   double c1, cN;
-  int32_t H, woff;
+  int32_t H, woff;  // H < 0: the rod is stepped
 };
 constexpr size_t kBandSlotBytes = sizeof(BandSlot);
 
 // Rods of uneven length, step count and r: tiles of kBandBatchTile points, one
-// workgroup each.  All pointers are device memory.
+// workgroup each.  A rod that decays by more than kBandDecay, which is known when
+// its r is, has kBandBatchStep points at most and is stepped by its workgroup.  All pointers are device memory.
 constexpr int kBandBatchTile = 2048;
+constexpr int kBandBatchStep = 512;
 struct BandItem {
   int32_t slot;  // index into rods / woff
   int32_t tile;

@@ -136,7 +136,7 @@ int band_reach_bound(int dtype, double r, int64_t T) {
   return dtype == 0 ? band_bound_of<float>((double)(float)r, t) : band_bound_of<double>(r, t);
 }
 
-BandRun band_run(int dtype, double r, int64_t K) {
+BandRun band_run(int dtype, double r, int64_t K, int64_t N, bool ring) {
   BandRun b;
   if (K <= 0) return b;
   int64_t T = K;
@@ -148,6 +148,8 @@ BandRun band_run(int dtype, double r, int64_t K) {
     }
     T = lo;
   }
+  if (const double all = band_decay(r, (double)T, N, ring); all > kBandDecay)
+    T = std::max<int64_t>(1, (int64_t)((double)T * kBandDecay / all));
   b.passes = (K + T - 1) / T;
   b.T = (K + b.passes - 1) / b.passes;
   return b;
@@ -893,14 +895,38 @@ __global__ __launch_bounds__(256) void band_batch_weights_kernel(const BandBatch
   if (slot == 0 && threadIdx.x == 0) *a.flag = 0;
   double r;
   const bool ok = band_batch_r(a, rod, &r);
-  const int H = band_batch_reach(a, slot, r, a.K[rod]);
+  const int64_t N = a.offsets[rod + 1] - a.offsets[rod];
+  const bool steps = band_decay(r, (double)a.K[rod], N, false) > kBandDecay && N <= kBandBatchStep;
+  const int H = steps ? -1 : band_batch_reach(a, slot, r, a.K[rod]);
   F* w = a.w + a.woff[slot];
-  band_weights<F>(w, H, (double)a.K[rod], r, false, 0, 256, s_g, s_c);
+  if (!steps) band_weights<F>(w, H, (double)a.K[rod], r, false, 0, 256, s_g, s_c);
   if (threadIdx.x == 0) {
     if (!ok) w[0] = (F)__builtin_nan("");
-    a.slots[slot] = BandSlot{a.offsets[rod], a.offsets[rod + 1] - a.offsets[rod], a.c1[rod],
-                             a.cN[rod], H, a.woff[slot]};
+    a.slots[slot] = BandSlot{a.offsets[rod], N, a.c1[rod], a.cN[rod], H, a.woff[slot]};
   }
+}
+
+// K steps of a rod of at most kBandBatchStep points by one workgroup, in LDS: the
+// bits of one launch per step.  A step is a barrier and two points a thread, about
+// 0.1 us.
+template <typename F>
+__device__ __forceinline__ void band_batch_steps(const BandRod<F>& b, F r, int K, F* xs) {
+  const int N = (int)b.N;
+  F *cur = xs, *nxt = xs + kBandBatchStep;
+  for (int i = threadIdx.x; i < N; i += blockDim.x) {
+    cur[i] = i == 0 ? b.e1 : i == N - 1 ? b.eN : b.in[i];
+    nxt[i] = cur[i];
+  }
+  for (int k = 0; k < K; ++k) {
+    __syncthreads();
+    for (int i = threadIdx.x + 1; i < N - 1; i += blockDim.x)
+      nxt[i] = eq3_step(cur[i - 1], cur[i], cur[i + 1], r);
+    F* was = cur;
+    cur = nxt;
+    nxt = was;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < N; i += blockDim.x) b.out[i] = cur[i];
 }
 
 // With BandSlot (which also saves each tile computing its reach) the rods of the
@@ -912,8 +938,15 @@ __global__ __launch_bounds__(256) void band_batch_kernel(const BandBatchArgs<F> 
   extern __shared__ __align__(16) char band_lds[];
   const int i = band_block(blockIdx.x, gridDim.x);
   const BandItem it = a.items[i];
-  band_tile<F, 2, 4, 1, false>(band_batch_rod(a, uniform(it.slot)),
-                               (int64_t)uniform(it.tile) * kBandBatchTile, a.rec + i, a.flag,
+  const int slot = uniform(it.slot);
+  const BandRod<F> rod = band_batch_rod(a, slot);
+  if (rod.H < 0) {
+    if (threadIdx.x == 0) a.rec[i] = BandRec{0x7fffffff, -1};
+    const int which = a.rods[slot];
+    band_batch_steps(rod, (F)a.r[which], a.K[which], reinterpret_cast<F*>(band_lds));
+    return;
+  }
+  band_tile<F, 2, 4, 1, false>(rod, (int64_t)uniform(it.tile) * kBandBatchTile, a.rec + i, a.flag,
                                nullptr, nullptr, 0.0, reinterpret_cast<F*>(band_lds));
 }
 
@@ -923,6 +956,7 @@ __global__ __launch_bounds__(256) void band_batch_cone_kernel(const BandBatchArg
   for (int i = blockIdx.x; i < a.nitems; i += gridDim.x) {
     const BandItem it = a.items[i];
     const BandRod<F> rod = band_batch_rod(a, it.slot);
+    if (rod.H < 0) continue;
     band_cone(rod, it.tile, (rod.N + kBandBatchTile - 1) / kBandBatchTile, kBandBatchTile,
               a.rec + (i - it.tile), (int64_t)a.K[a.rods[it.slot]]);
   }

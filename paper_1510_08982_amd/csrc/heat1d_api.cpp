@@ -111,6 +111,7 @@ struct heat1d_plan_s {
   std::vector<BandItem> band_items;
   std::vector<int32_t> band_rods, band_woff;
   int32_t band_hmax = 0;
+  bool band_short = false;  // some of them may decay too much for a pass
   // timing of the dominant kernel
   bool timing = false;
   std::vector<EventPair> ev;
@@ -634,6 +635,7 @@ void batched_split_band(heat1d_plan_t p) {
     p->band_rods.push_back(b);
     p->band_woff.push_back((int32_t)w);
     p->band_hmax = std::max(p->band_hmax, h);
+    p->band_short |= band_decay(0.5, p->Kh[b], p->Nh[b], false) > kBandDecay;
     tiles += nt;
     w += h + 1;
   }
@@ -1725,6 +1727,7 @@ hipError_t launch_batch(heat1d_plan_t p, const void* u0, void* uK, const int64_t
     b.nitems = (int32_t)p->band_items.size();
     b.nslots = (int32_t)p->band_rods.size();
     b.hmax = p->band_hmax;
+    b.short_rods = p->band_short;
     e = launch_band_batch(b, s);
   }
   if (e == hipSuccess && !p->by_work.empty())

@@ -101,7 +101,7 @@ constexpr size_t kBandSlotBytes = sizeof(BandSlot);
 
 // Rods of uneven length, step count and r: tiles of kBandBatchTile points, one
 // workgroup each.  A rod that decays by more than kBandDecay, which is known when
-// its r is, has kBandBatchStep points at most and is stepped by its workgroup.  All pointers are device memory.
+// its r is, has kBandBatchStep points at most and is stepped by a workgroup.  All pointers are device memory.
 constexpr int kBandBatchTile = 2048;
 constexpr int kBandBatchStep = 512;
 struct BandItem {
@@ -126,6 +126,7 @@ struct BandBatch {
   void* rec = nullptr;              // 8 bytes per item
   int32_t nitems = 0, nslots = 0;
   int32_t hmax = 0;                 // the longest reach that woff leaves room for
+  bool short_rods = false;          // some rod may decay by more than kBandDecay
 };
 hipError_t launch_band_batch(const BandBatch& b, hipStream_t s);
 

@@ -212,6 +212,10 @@ __device__ __forceinline__ void band_weights(F* w, int H, double T, double r, bo
     s_g[j] = (j == 0 || j == half) ? g : 2.0 * g;
   }
   __syncthreads();
+  // At r = 1/2 the high angles mirror the low ones, w_d is 0 where T - d is odd and
+  // twice the low sum elsewhere: the zeros are exact, and what errs is one sum, not
+  // the mean of two (a ring of 14816 points, T = 3746: 2e-15 against 5e-16).
+  const bool mirror = !lap && r == 0.5 && jhigh <= half;
   for (int d = d0 + threadIdx.x; d <= H; d += step) {
     double sum = 0.0;
     int k = 0;  // j d mod M
@@ -220,11 +224,15 @@ __device__ __forceinline__ void band_weights(F* w, int H, double T, double r, bo
       k += d;
       if (k >= M) k -= M;
     }
-    k = (int)(((int64_t)jhigh * d) % M);
-    for (int j = jhigh; j <= half; ++j) {
-      sum = __builtin_fma(s_g[j], s_c[k > half ? M - k : k], sum);
-      k += d;
-      if (k >= M) k -= M;
+    if (mirror) {
+      sum = fmod(steps + (double)d, 2.0) != 0.0 ? 0.0 : 2.0 * sum;
+    } else {
+      k = (int)(((int64_t)jhigh * d) % M);
+      for (int j = jhigh; j <= half; ++j) {
+        sum = __builtin_fma(s_g[j], s_c[k > half ? M - k : k], sum);
+        k += d;
+        if (k >= M) k -= M;
+      }
     }
     // The sum is off by some 1e-17 whatever the weight is.  The weights of steps are
     // means of means, none is negative, and a state without negative points keeps none.
@@ -906,27 +914,28 @@ __global__ __launch_bounds__(256) void band_batch_weights_kernel(const BandBatch
   }
 }
 
-// K steps of a rod of at most kBandBatchStep points by one workgroup, in LDS: the
-// bits of one launch per step.  A step is a barrier and two points a thread, about
-// 0.1 us.
+// K steps of the slots' rods that are stepped, each of at most kBandBatchStep points by
+// a workgroup, in LDS: the bits of one launch per step.  A step is a barrier and two
+// points a thread, about 0.1 us.  A launch of its own, where a plan has such rods: in
+// the tiles' kernel it cost those 0.9 %.
 template <typename F>
-__device__ __forceinline__ void band_batch_steps(const BandRod<F>& b, F r, int K, F* xs) {
-  const int N = (int)b.N;
-  F *cur = xs, *nxt = xs + kBandBatchStep;
-  for (int i = threadIdx.x; i < N; i += blockDim.x) {
-    cur[i] = i == 0 ? b.e1 : i == N - 1 ? b.eN : b.in[i];
-    nxt[i] = cur[i];
-  }
+__global__ __launch_bounds__(256) void band_batch_step_kernel(const BandBatchArgs<F> a) {
+  __shared__ F s_u[2][kBandBatchStep];
+  const BandRod<F> b = band_batch_rod(a, blockIdx.x);
+  if (b.H >= 0) return;
+  const int rod = a.rods[blockIdx.x], N = (int)b.N, K = a.K[rod];
+  const F r = (F)a.r[rod];
+  for (int i = threadIdx.x; i < N; i += 256)
+    s_u[0][i] = s_u[1][i] = i == 0 ? b.e1 : i == N - 1 ? b.eN : b.in[i];
   for (int k = 0; k < K; ++k) {
     __syncthreads();
-    for (int i = threadIdx.x + 1; i < N - 1; i += blockDim.x)
+    const F* cur = s_u[k & 1];
+    F* nxt = s_u[1 - (k & 1)];
+    for (int i = threadIdx.x + 1; i < N - 1; i += 256)
       nxt[i] = eq3_step(cur[i - 1], cur[i], cur[i + 1], r);
-    F* was = cur;
-    cur = nxt;
-    nxt = was;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < N; i += blockDim.x) b.out[i] = cur[i];
+  for (int i = threadIdx.x; i < N; i += 256) b.out[i] = s_u[K & 1][i];
 }
 
 // With BandSlot (which also saves each tile computing its reach) the rods of the
@@ -938,12 +947,9 @@ __global__ __launch_bounds__(256) void band_batch_kernel(const BandBatchArgs<F> 
   extern __shared__ __align__(16) char band_lds[];
   const int i = band_block(blockIdx.x, gridDim.x);
   const BandItem it = a.items[i];
-  const int slot = uniform(it.slot);
-  const BandRod<F> rod = band_batch_rod(a, slot);
+  const BandRod<F> rod = band_batch_rod(a, uniform(it.slot));
   if (rod.H < 0) {
     if (threadIdx.x == 0) a.rec[i] = BandRec{0x7fffffff, -1};
-    const int which = a.rods[slot];
-    band_batch_steps(rod, (F)a.r[which], a.K[which], reinterpret_cast<F*>(band_lds));
     return;
   }
   band_tile<F, 2, 4, 1, false>(rod, (int64_t)uniform(it.tile) * kBandBatchTile, a.rec + i, a.flag,
@@ -993,6 +999,11 @@ static hipError_t band_batch(const BandBatch& b, hipStream_t s) {
                      a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (b.short_rods) {
+    hipLaunchKernelGGL(band_batch_step_kernel<F>, dim3((unsigned)b.nslots), dim3(256), 0, s, a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(band_batch_cone_kernel<F>, dim3((unsigned)std::min(b.nitems, 1024)),
                      dim3(256), 0, s, a);
   return hipGetLastError();

@@ -101,7 +101,7 @@ constexpr size_t kBandSlotBytes = sizeof(BandSlot);
 
 // Rods of uneven length, step count and r: tiles of kBandBatchTile points, one
 // workgroup each.  A rod that decays by more than kBandDecay, which is known when
-// its r is, has kBandBatchStep points at most and is stepped by a workgroup.  All pointers are device memory.
+// its r is, has kBandBatchStep points at most and is stepped by a wavefront.  All pointers are device memory.
 constexpr int kBandBatchTile = 2048;
 constexpr int kBandBatchStep = 512;
 struct BandItem {

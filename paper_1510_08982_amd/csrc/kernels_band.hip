@@ -23,6 +23,7 @@
 
 #include "heat1d_band.h"
 #include "heat1d_device.h"
+#include "heat1d_rod.h"
 
 namespace heat1d {
 
@@ -914,28 +915,28 @@ __global__ __launch_bounds__(256) void band_batch_weights_kernel(const BandBatch
   }
 }
 
-// K steps of the slots' rods that are stepped, each of at most kBandBatchStep points by
-// a workgroup, in LDS: the bits of one launch per step.  A step is a barrier and two
-// points a thread, about 0.1 us.  A launch of its own, where a plan has such rods: in
-// the tiles' kernel it cost those 0.9 %.
+// K steps of the slots' rods that are stepped, a wavefront each (at most
+// kBandBatchStep points, up to eight a lane, neighbours by DPP): the bits of one launch
+// per step.  A launch of its own, where a plan has such rods: in the tiles' kernel it
+// cost those 0.9 %, and a workgroup a rod, with a barrier a step, up to 2.2 times the
+// time (32768 rods of 3 points, K = 5000, FP32: 10.5 ms).
 template <typename F>
-__global__ __launch_bounds__(256) void band_batch_step_kernel(const BandBatchArgs<F> a) {
-  __shared__ F s_u[2][kBandBatchStep];
-  const BandRod<F> b = band_batch_rod(a, blockIdx.x);
+__global__ __launch_bounds__(256) void band_batch_step_kernel(const BandBatchArgs<F> a, int nslots) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int slot = uniform((int)blockIdx.x * 4 + (int)(threadIdx.x / kWave));
+  if (slot >= nslots) return;
+  const BandRod<F> b = band_batch_rod(a, slot);
   if (b.H >= 0) return;
-  const int rod = a.rods[blockIdx.x], N = (int)b.N, K = a.K[rod];
+  const int rod = a.rods[slot], n = uniform((int)b.N), K = uniform(a.K[rod]);
   const F r = (F)a.r[rod];
-  for (int i = threadIdx.x; i < N; i += 256)
-    s_u[0][i] = s_u[1][i] = i == 0 ? b.e1 : i == N - 1 ? b.eN : b.in[i];
-  for (int k = 0; k < K; ++k) {
-    __syncthreads();
-    const F* cur = s_u[k & 1];
-    F* nxt = s_u[1 - (k & 1)];
-    for (int i = threadIdx.x + 1; i < N - 1; i += 256)
-      nxt[i] = eq3_step(cur[i - 1], cur[i], cur[i + 1], r);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < N; i += 256) b.out[i] = s_u[K & 1][i];
+#define HEAT1D_SHORT(M)                                                                      \
+  return rod_resident<F, M, RodSync::kWave>(b.in, b.out, n, K, r, b.e1, b.eN, nullptr, 1, 0, \
+                                            lane, false)
+  if (n <= kWave) HEAT1D_SHORT(1);
+  if (n <= 2 * kWave) HEAT1D_SHORT(2);
+  if (n <= 4 * kWave) HEAT1D_SHORT(4);
+  HEAT1D_SHORT(8);
+#undef HEAT1D_SHORT
 }
 
 // With BandSlot (which also saves each tile computing its reach) the rods of the
@@ -1000,7 +1001,8 @@ static hipError_t band_batch(const BandBatch& b, hipStream_t s) {
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (b.short_rods) {
-    hipLaunchKernelGGL(band_batch_step_kernel<F>, dim3((unsigned)b.nslots), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(band_batch_step_kernel<F>, dim3((unsigned)((b.nslots + 3) / 4)), dim3(256),
+                       0, s, a, b.nslots);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -2045,7 +2045,7 @@ int heat1d_adjoint_ends(heat1d_plan_t p, const void* gK, double r, int64_t K, do
   // traffic that counts: 2^22 points, K = 64 / 96, 67 / 89 us stepped, 71 / 77 by passes.
   const int64_t from = p->N >= (int64_t(1) << 21) ? 80 : 129;
   const int st =
-      band_adjoint(&one, K) && K >= from && band_run(p->dtype, r, K, p->N, false).T >= 64
+      band_adjoint(&one, K) && band_run(p->dtype, r, K, p->N, false).T >= from
           ? run_band(&one, 1, ws + L.z_off, ws + L.w_off, r, 1.0, 0.0, K, ws + L.ping_off,
                      ws + L.scr_off, nullptr, nullptr, nullptr, s)
           : run_sync_impl(&one, ws + L.z_off, ws + L.w_off, r, 1.0, 0.0, K, ws + L.ping_off, s,
